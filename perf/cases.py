@@ -219,8 +219,10 @@ def run(s):
         return out
     else:
         ctx.run_sqn(case["R"], case["K"], seed, **s["kw"])
-        st, g = ctx.sqn_stats(), ctx.sqn_paths()
-        out = _stats(st)
+        out = _stats(ctx.sqn_stats())
+        if not case["split"]:       # many replications: the loss statistics are the result
+            return out
+        g = ctx.sqn_paths()
         out.update({k: g[k] for k in ("F", "F_ckpt", "w", "pairs")})
         out["S"], out["Y"] = np.stack(g["S"]), np.stack(g["Y"])
         return out
