@@ -79,7 +79,7 @@ def ops_per_path_step_dense(d: int, N: int, nu: int) -> float:
 
 # Sources whose compiled code the paper-scale step runs; a counter summary taken on other sources
 # no longer describes the kernel.
-KERNEL_SOURCES = ("paper_2404_11631_amd/csrc/fw_paths.hip", "paper_2404_11631_amd/csrc/device_rng.hpp",
+KERNEL_SOURCES = ("paper_2404_11631_amd/csrc/fw_paths.hpp", "paper_2404_11631_amd/csrc/device_rng.hpp",
                   "paper_2404_11631_amd/csrc/device_reduce.hpp", "paper_2404_11631_amd/csrc/sim_types.hpp")
 TRAFFIC_PROFILE = "profiles/hbm_traffic_paper_scale.md"
 

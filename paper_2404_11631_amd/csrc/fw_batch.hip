@@ -1,6 +1,6 @@
 // fw_batch.hip -- instances of uneven size and horizon, as wavefront tiles.
 //
-// Algorithm 1 (Section 3.1) as in fw_paths.hip, reorganised for a batch of instances with d up to
+// Algorithm 1 (Section 3.1) as in fw_paths.hpp, reorganised for a batch of instances with d up to
 // 32 in one kernel:
 //   * one wavefront per tile; every tile of the batch is in one launch, longest first, so the
 //     hardware dispatcher hands the heaviest tiles out first and fills in with the lighter ones;
