@@ -83,7 +83,10 @@ struct NvState {
     sim_nv_params params{};               // pointers cleared
     uint64_t R = 0, T = 0;
     uint32_t nwg = 0, P = 1;              // sample workgroups; lanes per quad
-    DevBuf prod_f, prod_d, S, cnt, tau, dec, wg_r, wg_j, wg_gx, cost_part, fval, stats, origin;
+    uint64_t seed = 0;
+    bool from_x0 = false;                 // the last run started from a given point
+    bool unsettled = false;               // the last run was cooperative and its failure word is unread
+    DevBuf prod_f, prod_d, S, cnt, tau, dec, wg_r, wg_j, wg_gx, cost_part, fval, stats, origin, words;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
 };
 

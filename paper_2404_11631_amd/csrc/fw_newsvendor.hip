@@ -333,7 +333,7 @@ __global__ void nv_finalize_kernel(NvArgs A, uint32_t n_ckpt)
     nv_stream_stats(A.fval, A.R, n_ckpt, A.stats);
     uint64_t origin = 0;
     for (uint32_t r = 0; r < A.R; ++r) origin += A.cnt[static_cast<uint64_t>(r) * (A.n + 1)];
-    *A.origin_total = origin;
+    *A.origin_total = A.fail && *A.fail ? kNvFailed : origin;
 }
 
 // ---- Algorithm 2 over X = {A x <= C, x >= 0} with M resource rows (Eq. (7)) --------------------

@@ -3,6 +3,7 @@
 // (nv_api.hip).
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 namespace fw {
@@ -48,8 +49,11 @@ struct NvArgs {
     double *cost_part;                          // [R][ceil(n / kNvCostChunk)][2] double-double partials
     double *fval;                               // [n_ckpt + 1][R]
     double *stats;                              // kMaxStreams x kStreamFields + 2
-    uint64_t *origin_total;
+    uint64_t *origin_total;                     // kNvFailed after a cooperative run that gave up
+    const uint32_t *fail;                       // its failure word (NULL: launch by launch)
 };
+
+constexpr uint64_t kNvFailed = ~0ull;
 
 // Iteration t's samples and workgroup partials; with fold_prev it first takes the step of iteration
 // t - 1 (whose partials the previous launch left in the other buffer).
@@ -58,6 +62,39 @@ int launch_nv_sample(const NvArgs &A, uint64_t t, uint32_t epoch, float cw, bool
 int launch_nv_step(const NvArgs &A, uint64_t t, hipStream_t s);
 int launch_nv_cost(const NvArgs &A, double c, uint32_t slot, hipStream_t s);
 int launch_nv_finalize(const NvArgs &A, uint32_t n_ckpt, hipStream_t s);
+
+// ---- many iterations in one cooperative launch (fw_newsvendor_run.hip) --------------------------
+// A run takes this form when its workgroups fit twice per compute unit and a lane's samples of an
+// epoch fit in registers (16 of them leave two wavefronts per SIMD, 32 one), which holds up to
+// n = 130,000 at S = 50 on one replication. Past that an iteration's samples outweigh its launch (n = 1e6:
+// 32 us against 2.7 us), and the launch-per-iteration kernels keep the chip full without an exchange.
+// Measured (S = 25, K = 1500): n = 1e4 7.7 -> 3.7 ms a call, n = 872 2.3 times, n = 48,000 (S = 30) 1.8 times.
+constexpr uint32_t kNvRunMaxNs = 16;            // samples per lane
+// 64-bit words per workgroup: a 64-byte line for each parity. Workgroups that share a line slow one
+// another's stores and polls: 157 of them exchange a word in 1.6 us at a line each, in 2.5 us at 8
+// bytes each.
+constexpr uint32_t kNvRunLine = 16;
+constexpr uint32_t kNvRunSteps = 1024;          // iterations per launch at most (the length of the gap log)
+
+struct NvRunArgs {
+    uint64_t t0, t1;                            // the iterations of this launch
+    uint32_t M;                                 // iterations per resample
+    uint32_t from_x0;                           // iteration 0 starts from x0_f
+    uint64_t *words;                            // [R][nwg][kNvRunLine] exchange slots, cleared before the run
+    uint32_t *fail;                             // raised by a wait that gave up; cleared before the run
+    float *gx_log;                              // [t1 - t0][R][nwg] parts of g'x
+    float *best_log;                            // [t1 - t0][R] smallest ratios
+};
+
+// Bytes of the slots and the failure word (cleared before a run), and of all the form's scratch.
+inline size_t nv_run_slot_bytes(uint64_t R, uint32_t nwg) { return sizeof(uint64_t) * (kNvRunLine * R * nwg + 1); }
+inline size_t nv_run_bytes(uint64_t R, uint32_t nwg, uint64_t T)
+{
+    return nv_run_slot_bytes(R, nwg) + sizeof(float) * (T < kNvRunSteps ? T : kNvRunSteps) * R * (nwg + 1);
+}
+
+bool nv_run_fits(uint32_t nwg, uint32_t R, uint32_t S, uint32_t P, int device);
+int launch_nv_run(const NvArgs &A, const NvRunArgs &Q, hipStream_t s);
 
 // ---- Algorithm 2 over X = {A x <= C, x >= 0} with M resource rows (Eq. (7)) --------------------
 // threads of the subproblem workgroup (one per replication): few products leave a pricing pass

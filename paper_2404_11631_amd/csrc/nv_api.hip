@@ -62,6 +62,82 @@ fw::NvArgs nv_args(NvState &w, const sim_nv_params *p, uint64_t R, uint64_t T, u
     return A;
 }
 
+// Enqueues the run that w describes (parameters, coefficients and buffers in place): the cooperative
+// form, one launch between cost evaluations, or a launch per iteration.
+int nv_enqueue(sim_ctx *ctx, NvState &w, bool one_launch)
+{
+    hipStream_t st = ctx->stream;
+    const sim_nv_params &p = w.params;
+    const uint64_t R = w.R, T = w.T, M = p.resample_every;
+    const uint32_t nc = p.n_checkpoints;
+    const size_t N = p.n;
+    HIP_TRY(ctx, hipMemsetAsync(w.S.ptr, 0, sizeof(uint64_t) * R * N, st));
+    HIP_TRY(ctx, hipMemsetAsync(w.cnt.ptr, 0, sizeof(uint32_t) * R * (N + 1), st));
+    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
+    if (one_launch) HIP_TRY(ctx, hipMemsetAsync(w.words.ptr, 0, fw::nv_run_slot_bytes(R, w.nwg), st));
+    fw::NvArgs A = nv_args(w, &p, R, T, w.seed);
+    A.fail = one_launch ? reinterpret_cast<const uint32_t *>(static_cast<uint64_t *>(w.words.ptr) + fw::kNvRunLine * R * w.nwg) : nullptr;
+    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
+    uint32_t ck = 0;
+    if (one_launch) {
+        fw::NvRunArgs Q{};
+        Q.M = static_cast<uint32_t>(M);
+        Q.from_x0 = w.from_x0 ? 1u : 0u;
+        Q.words = static_cast<uint64_t *>(w.words.ptr);
+        Q.fail = const_cast<uint32_t *>(A.fail);
+        Q.gx_log = reinterpret_cast<float *>(static_cast<char *>(w.words.ptr) + fw::nv_run_slot_bytes(R, w.nwg));
+        Q.best_log = Q.gx_log + std::min<uint64_t>(T, fw::kNvRunSteps) * R * w.nwg;
+        while (Q.t1 < T) {
+            Q.t0 = Q.t1;
+            Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kNvRunSteps);
+            if (fw::launch_nv_run(A, Q, st))
+                return set_err(ctx, SIM_EDEVICE, "newsvendor launch failed at t=%llu", (unsigned long long)Q.t0);
+            for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
+                if (fw::launch_nv_cost(A, 2.0 / (static_cast<double>(Q.t1) * static_cast<double>(Q.t1 + 1)), ck, st))
+                    return set_err(ctx, SIM_EDEVICE, "newsvendor cost launch failed");
+        }
+    } else {
+        // The step of iteration t runs inside the next iteration's sample launch unless a cost
+        // evaluation needs the updated signature first or t is the last iteration.
+        bool pending = false;
+        for (uint64_t t = 0; t < T; ++t) {
+            const float cw = t == 0 ? 0.0f : static_cast<float>(2.0 / (static_cast<double>(t) * static_cast<double>(t + 1)));
+            if (fw::launch_nv_sample(A, t, static_cast<uint32_t>(t / M), cw, t == 0 && w.from_x0, pending, st))
+                return set_err(ctx, SIM_EDEVICE, "newsvendor sample launch failed at t=%llu", (unsigned long long)t);
+            const bool cost_next = ck < nc && p.checkpoints[ck] == t + 1;
+            pending = !(cost_next || t + 1 == T);
+            if (!pending && fw::launch_nv_step(A, t, st))
+                return set_err(ctx, SIM_EDEVICE, "newsvendor step launch failed at t=%llu", (unsigned long long)t);
+            while (ck < nc && p.checkpoints[ck] == t + 1) {
+                const double c = 2.0 / (static_cast<double>(t + 1) * static_cast<double>(t + 2));
+                if (fw::launch_nv_cost(A, c, ck, st)) return set_err(ctx, SIM_EDEVICE, "newsvendor cost launch failed");
+                ++ck;
+            }
+        }
+    }
+    if (fw::launch_nv_cost(A, 2.0 / (static_cast<double>(T) * static_cast<double>(T + 1)), nc, st) ||
+        fw::launch_nv_finalize(A, nc, st))
+        return set_err(ctx, SIM_EDEVICE, "newsvendor finalize launch failed");
+    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
+    w.unsettled = one_launch;
+    return SIM_OK;
+}
+
+// Waits for the last run and reads the origin's total. A cooperative run whose workgroups gave up
+// waiting for one another left kNvFailed there and is repeated launch by launch.
+int nv_settle(sim_ctx *ctx, NvState &w, uint64_t &origin)
+{
+    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    if (origin == fw::kNvFailed) {
+        if (int rc = nv_enqueue(ctx, w, false)) return rc;
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+        HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    }
+    w.unsettled = false;
+    return SIM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -127,44 +203,21 @@ int sim_run_newsvendor(sim_ctx *ctx, const sim_nv_params *p, uint64_t R, uint64_
         (rc = ensure(ctx, w.origin, sizeof(uint64_t))) ||
         (rc = ensure(ctx, w.cost_part, sizeof(double) * 2 * R * ((N + fw::kNvCostChunk - 1) / fw::kNvCostChunk))))
         return rc;
+    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
+    const bool one_launch = fw::nv_run_fits(w.nwg, static_cast<uint32_t>(R), p->n_samples, w.P, ctx->device) &&
+                            ensure(ctx, w.words, fw::nv_run_bytes(R, w.nwg, T)) == SIM_OK;
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipMemcpyAsync(w.prod_f.ptr, pf.data(), sizeof(float) * pf.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.prod_d.ptr, pd.data(), sizeof(double) * pd.size(), hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.S.ptr, 0, sizeof(uint64_t) * R * N, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.cnt.ptr, 0, sizeof(uint32_t) * R * (N + 1), st));
-    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));   // the host vectors must outlive the copies
-
-    const fw::NvArgs A = nv_args(w, p, R, T, seed);
-    const uint64_t M = p->resample_every;
-    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
-    // The step of iteration t runs inside the next iteration's sample launch unless a cost
-    // evaluation needs the updated signature first or t is the last iteration.
-    uint32_t ck = 0;
-    bool pending = false;
-    for (uint64_t t = 0; t < T; ++t) {
-        const float cw = t == 0 ? 0.0f : static_cast<float>(2.0 / (static_cast<double>(t) * static_cast<double>(t + 1)));
-        if (fw::launch_nv_sample(A, t, static_cast<uint32_t>(t / M), cw, t == 0 && p->x0 != nullptr, pending, st))
-            return set_err(ctx, SIM_EDEVICE, "newsvendor sample launch failed at t=%llu", (unsigned long long)t);
-        const bool cost_next = ck < nc && p->checkpoints[ck] == t + 1;
-        pending = !(cost_next || t + 1 == T);
-        if (!pending && fw::launch_nv_step(A, t, st))
-            return set_err(ctx, SIM_EDEVICE, "newsvendor step launch failed at t=%llu", (unsigned long long)t);
-        while (ck < nc && p->checkpoints[ck] == t + 1) {
-            const double c = 2.0 / (static_cast<double>(t + 1) * static_cast<double>(t + 2));
-            if (fw::launch_nv_cost(A, c, ck, st)) return set_err(ctx, SIM_EDEVICE, "newsvendor cost launch failed");
-            ++ck;
-        }
-    }
-    if (fw::launch_nv_cost(A, 2.0 / (static_cast<double>(T) * static_cast<double>(T + 1)), nc, st) ||
-        fw::launch_nv_finalize(A, nc, st))
-        return set_err(ctx, SIM_EDEVICE, "newsvendor finalize launch failed");
-    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
 
     w.params = *p;
     w.params.mu = w.params.sigma = w.params.k = w.params.h = w.params.v = w.params.c = w.params.x0 = nullptr;
+    w.from_x0 = p->x0 != nullptr;
+    w.seed = seed;
     w.R = R;
     w.T = T;
+    if (int rc2 = nv_enqueue(ctx, w, one_launch)) return rc2;
     w.have = true;
     return SIM_OK;
 }
@@ -175,13 +228,12 @@ int sim_nv_stats(sim_ctx *ctx, sim_stats_out *out)
     NvState &w = ctx->nv;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no newsvendor run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
     const uint32_t nc = w.params.n_checkpoints, n_streams = 1 + 2 * nc;
     double F[fw::kMaxStreams * fw::kStreamFields + 2];
     uint64_t origin = 0;
     std::vector<uint32_t> tau(w.R);
+    if (int rc = nv_settle(ctx, w, origin)) return rc;
     HIP_TRY(ctx, hipMemcpy(F, w.stats.ptr, sizeof(double) * (n_streams * fw::kStreamFields + 2), hipMemcpyDeviceToHost));
-    HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
     HIP_TRY(ctx, hipMemcpy(tau.data(), w.tau.ptr, sizeof(uint32_t) * w.R, hipMemcpyDeviceToHost));
     float ms = 0.0f;
     HIP_TRY(ctx, hipEventElapsedTime(&ms, w.ev0, w.ev1));
@@ -202,7 +254,12 @@ int sim_nv_paths(sim_ctx *ctx, sim_wide_view *out)
     NvState &w = ctx->nv;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no newsvendor run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    if (w.unsettled) {
+        uint64_t origin;
+        if (int rc = nv_settle(ctx, w, origin)) return rc;
+    } else {
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    }
     std::memset(out, 0, sizeof(*out));
     out->R = w.R;
     out->T = w.T;

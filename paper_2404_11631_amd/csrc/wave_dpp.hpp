@@ -92,6 +92,19 @@ __device__ __forceinline__ uint32_t dpp_sum_lanes(uint32_t x, uint32_t P)
     return x;
 }
 
+// the smallest of the wavefront's unsigned values, in every lane
+__device__ __forceinline__ uint32_t dpp_min64(uint32_t x)
+{
+    x = min(x, dpp_move<0xB1>(x));
+    x = min(x, dpp_move<0x4E>(x));
+    x = min(x, dpp_move<0x141>(x));
+    x = min(x, dpp_move<0x140>(x));
+    const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = min(h[0], h[1]);
+    const auto w = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return min(w[0], w[1]);
+}
+
 __device__ __forceinline__ void argmin_take(float &g, uint32_t &j, float og, uint32_t oj)
 {
     if (og < g || (og == g && oj < j)) {

@@ -1,0 +1,52 @@
+"""The cooperative forms of the single-replication paths (many iterations in one launch, workgroups
+exchanging tagged words) against their launch-by-launch forms, record for record. The second is
+reached with a context whose memory cap leaves no room for the exchange slots, which a run
+allocates last."""
+import numpy as np
+import pytest
+
+from paper_2404_11631_amd import sim, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def both(run, records):
+    """The records of `run` on an uncapped context and on one without room for the exchange."""
+    out, used = [], 0
+    for cap in (0, 1):
+        ctx = sim.Sim(0, workspace_bytes=used - 32 if cap else 0)
+        try:
+            run(ctx)
+            out.append(records(ctx))
+            assert not cap or ctx.workspace_bytes() < used - 32      # the slots were not allocated
+            used = ctx.workspace_bytes()
+        finally:
+            ctx.close()
+    return out
+
+
+def same(a, b):
+    for f in a:
+        assert np.array_equal(np.asarray(a[f]), np.asarray(b[f]), equal_nan=True), f
+
+
+@pytest.mark.parametrize("n,S,M,R,T,x0,ckpt", [
+    (4, 1, 1, 1, 1, False, ()), (4, 3, 1, 1, 40, False, (1, 2, 40)), (64, 25, 1, 1, 1030, False, (1024,)),
+    (1000, 16, 3, 2, 60, True, (7,)), (260, 255, 1, 1, 30, False, ()), (4100, 33, 2, 3, 50, False, (50,)),
+    (16, 50, 1, 64, 30, True, (10,)), (40_000, 12, 1, 1, 30, False, (30,)), (120_000, 50, 1, 1, 12, False, (3,))])
+def test_newsvendor(n, S, M, R, T, x0, ckpt):
+    print(f"[one launch] newsvendor n={n} S={S} M={M} R={R} T={T}", flush=True)
+    inst = workloads.newsvendor_instance(3, 0, n)
+    inst["sigma"][::7] = 0.0                        # products of certain demand: infinite thresholds
+    start = 0.3 * inst["C"] / inst["c"] / n if x0 else None
+
+    def run(ctx):
+        ctx.run_newsvendor(inst, R, T, 5, S=S, M=M, x0=start, checkpoints=ckpt, gap_eps=1e3)
+
+    def records(ctx):
+        st = ctx.nv_stats()
+        return dict(ctx.nv_paths(), mean=st.mean, origin=st.decision_total[0], tau_count=st.tau_count)
+
+    a, b = both(run, records)
+    same(a, b)
+    assert a["cnt"].sum() == R * T
