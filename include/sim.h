@@ -400,8 +400,9 @@ int sim_cv_law(const sim_params *p, uint64_t T, double *probs, double *S2, doubl
  * Supported: 4 <= d <= SIM_WIDE_MAX_D with d a multiple of 4, diagonal Sigma (chol NULL), Gaussian
  * noise, FP32 state, 2 <= N <= SIM_WIDE_MAX_N, any M, 1 <= R <= SIM_WIDE_MAX_R, R T <= 2^30; flags
  * may hold SIM_KEEP_PATHS and SIM_DECISION_LOG, and the run keeps every per-path record and
- * decision either way. Asynchronous on the context's stream; the host enqueues 4 T (+ checkpoint)
- * launches before returning. */
+ * decision either way. Asynchronous on the context's stream. Up to d = 65,536 (N <= 63, no
+ * schedule, d R / 128 <= 512) a cooperative launch runs all iterations between two checkpoints, with the same
+ * results bit for bit; otherwise the host enqueues three launches per iteration before returning. */
 int sim_run_wide(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint64_t seed);
 
 /* Checks a parameter set exactly as sim_run_wide does, without a device. */
@@ -434,7 +435,8 @@ int sim_wide_paths(sim_ctx *ctx, sim_wide_view *out);
  * (replication, epoch) stream in domain 4; Algorithm 2 with the vertex of smallest g_j / c_j when it
  * is negative (else the origin, lowest index among equal values), step 2/(t+2). Y = f(x_T) and the
  * checkpoints f(x_c) in FP64 from Eq. (6) in closed form. The parallelism is inside a replication
- * (a thread per four products), two launches per iteration. */
+ * (a thread per up to four products; up to n = 130,000 one cooperative launch runs all iterations between
+ * two checkpoints, beyond that a launch per iteration). */
 typedef struct {
     uint32_t abi_version;       /* SIM_ABI_VERSION */
     uint32_t n;                 /* products, a multiple of 4 in [4, SIM_NV_MAX_N] */

@@ -70,10 +70,13 @@ struct WideState {
     bool have = false;
     sim_params params{};                  // pointers cleared
     uint64_t R = 0, T = 0;
+    uint64_t seed = 0;
     uint32_t nwg = 0;
     double fstar = 0.0;
+    bool from_w0 = false;                 // the last run started from a given point
+    bool unsettled = false;               // the last run was cooperative and its failure word is unread
     DevBuf asset_f, asset_d, S, cnt, tau, dec, s1, part_dot, part_qn, dot, qn, wg_g, wg_j, wg_gw, fval,
-        stats, origin;
+        stats, origin, words;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
 };
 

@@ -11,8 +11,8 @@
 // iteration t + 1 only after it has read every value of iteration t, so a slot is overwritten (at
 // t + 2) only after all have read it.
 //
-// Every wait is bounded: a poll that does not see its tag within kPollLimit rounds (seconds, where a
-// value arrives within microseconds) gives up, the workgroup raises the run's failure word and
+// Every wait is bounded: a poll that does not see its tag within kPollLimit rounds (about a second,
+// where a value arrives within microseconds) gives up, the workgroup raises the run's failure word and
 // leaves, and the others follow by their own limits; the host reports the failure or runs the
 // launch-by-launch form. The launches are cooperative, so all workgroups are resident together.
 #pragma once
@@ -20,9 +20,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "run_shape.hpp"
+#include "wave_dpp.hpp"
+
 namespace fw {
 
-constexpr uint32_t kPollLimit = 1u << 22;
+#ifndef FW_POLL_LIMIT
+#define FW_POLL_LIMIT (1u << 20)
+#endif
+constexpr uint32_t kPollLimit = FW_POLL_LIMIT;
 
 __device__ __forceinline__ void exchange_put(uint64_t *slot, uint32_t value, uint32_t tag)
 {
@@ -42,6 +48,116 @@ __device__ __forceinline__ uint32_t failure_get(const uint32_t *fail)
 __device__ __forceinline__ void failure_raise(uint32_t *fail)
 {
     __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A value as an unsigned key in the order of the values (negative ones below positive).
+__device__ __forceinline__ uint32_t value_key(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    return b ^ (static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u);
+}
+
+__device__ __forceinline__ float key_value(uint32_t k)
+{
+    return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k);
+}
+
+// The smallest key over the wavefront and the lowest index among the lanes that hold it; with SORTED
+// the lanes' indices ascend and the first such lane has it.
+template <bool SORTED>
+__device__ __forceinline__ void wave_min_key(uint32_t &key, uint32_t &j)
+{
+    const uint32_t m = dpp_min64(key);
+    if constexpr (SORTED)
+        j = __builtin_amdgcn_readlane(j, __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m)));
+    else
+        j = dpp_min64(key == m ? j : 0xFFFFFFFFu);
+    key = m;
+}
+
+// A workgroup's smallest value, its index (24 bits) and 8 bits of the tag in one word.
+__device__ __forceinline__ void vertex_put(uint64_t *lines, uint32_t g, uint64_t t, uint32_t key, uint32_t j)
+{
+    exchange_put(lines + static_cast<size_t>(g) * kRunLine + 8 * (t & 1), key, (j << 8) | ((static_cast<uint32_t>(t) + 1u) & 0xFFu));
+}
+
+// The smallest (key, index) over the nwg workgroups' words of iteration t, by a workgroup of BLOCK threads
+// with one barrier; st holds a word per wavefront. `fail` (LDS) is set when a word did not come, before
+// the barrier. All threads get the result: key in the high half, index (0xFFFFFF: none) in the low.
+template <int BLOCK>
+__device__ __forceinline__ uint64_t vertex_get(const uint64_t *lines, uint32_t nwg, uint64_t t, uint64_t *st, uint32_t *fail)
+{
+    const uint32_t tag = static_cast<uint32_t>(t) + 1u;
+    uint32_t key = 0xFFFFFFFFu, j = 0xFFFFFFFFu;
+    bool seen = true;
+    for (uint32_t i = threadIdx.x; i < nwg; i += BLOCK) {
+        const uint64_t *slot = lines + static_cast<size_t>(i) * kRunLine + 8 * (t & 1);
+        uint64_t w = exchange_get(slot);
+        for (uint32_t polls = 0; ((static_cast<uint32_t>(w) ^ tag) & 0xFFu) != 0u; w = exchange_get(slot))
+            if (++polls == kPollLimit) {
+                seen = false;
+                break;
+            }
+        const uint32_t xk = static_cast<uint32_t>(w >> 32), xj = static_cast<uint32_t>(w) >> 8;
+        if (xk < key || (xk == key && xj < j)) {
+            key = xk;
+            j = xj;
+        }
+    }
+    if (!seen) *fail = 1u;
+    wave_min_key<false>(key, j);
+    if ((threadIdx.x & 63u) == 0u) st[threadIdx.x / 64] = (static_cast<uint64_t>(key) << 32) | j;
+    __syncthreads();
+    uint64_t m = st[0];
+#pragma unroll
+    for (int w = 1; w < BLOCK / 64; ++w) m = min(m, st[w]);
+    return m;
+}
+
+// What a cooperative launch leaves for the gap, tau and the decision counts, and the launch that takes
+// them from it, an iteration per workgroup.
+struct RunLog {
+    const float *gx;            // [steps][R][nwg] the workgroups' parts of g'x
+    const float *best;          // [steps][R] smallest value of the linear subproblem
+    uint32_t nwg, R, n;
+    float scale, gap_eps;       // gap = g'x - min(0, scale best)
+    uint64_t t0, T;
+    const uint32_t *fail;       // the run's failure word: a run that gave up left no log
+    const uint32_t *dec;        // [R][T]
+    uint32_t *tau;              // [R]
+    uint32_t *cnt;              // [R][n + 1]
+};
+
+// 256 threads, the sum in the order of the launch-per-iteration kernels: strided over the threads,
+// the wavefront's butterfly, the wavefronts in order.
+static __global__ __launch_bounds__(256) void run_log_kernel(RunLog L)
+{
+    __shared__ float sm[4];
+    const uint32_t tid = threadIdx.x, r = blockIdx.y;
+    if (*L.fail) return;
+    const uint64_t row = static_cast<uint64_t>(blockIdx.x) * L.R + r;
+    float gs = 0.0f;
+    for (uint32_t i = tid; i < L.nwg; i += 256) gs += L.gx[row * L.nwg + i];
+    gs = dpp_sum64(gs);
+    if (tid % 64 == 0) sm[tid / 64] = gs;
+    __syncthreads();
+    if (tid == 0) {
+        float gsum = sm[0];
+        for (int w = 1; w < 4; ++w) gsum += sm[w];
+        const float best = L.best[row];
+        const float gap = gsum - (best < 0.0f ? L.scale * best : 0.0f);
+        const uint64_t t = L.t0 + blockIdx.x;
+        // kTauNone is the largest value: the minimum is the first iteration at or below the threshold
+        if (gap <= L.gap_eps) atomicMin(L.tau + r, static_cast<uint32_t>(t));
+        const uint32_t a = L.dec[static_cast<uint64_t>(r) * L.T + t];
+        if (a <= L.n) atomicAdd(L.cnt + static_cast<uint64_t>(r) * (L.n + 1) + a, 1u);
+    }
+}
+
+static inline int launch_run_log(const RunLog &L, uint64_t steps, hipStream_t s)
+{
+    hipLaunchKernelGGL(run_log_kernel, dim3(static_cast<uint32_t>(steps), L.R), dim3(256), 0, s, L);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 }  // namespace fw

@@ -23,35 +23,6 @@
 
 namespace fw {
 
-namespace {
-
-// The smallest ratio as an unsigned key in the order of the values (negative ones below positive).
-__device__ __forceinline__ uint32_t ratio_key(float x)
-{
-    const uint32_t b = __float_as_uint(x);
-    return b ^ (static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u);
-}
-
-__device__ __forceinline__ float key_ratio(uint32_t k)
-{
-    return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k);
-}
-
-// The smallest key over the wavefront and the lowest product among the lanes that hold it; with SORTED
-// the lanes' products ascend and the first such lane has it.
-template <bool SORTED>
-__device__ __forceinline__ void wave_min_key(uint32_t &key, uint32_t &j)
-{
-    const uint32_t m = dpp_min64(key);
-    if constexpr (SORTED)
-        j = __builtin_amdgcn_readlane(j, __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m)));
-    else
-        j = dpp_min64(key == m ? j : 0xFFFFFFFFu);
-    key = m;
-}
-
-}  // namespace
-
 // NS: samples per lane held in registers, at least ceil(S / P)
 template <int NS>
 __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
@@ -62,8 +33,8 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
     // this workgroup's parts of g'x and, in workgroup 0, the vertices and their ratios, per iteration:
     // written out after the last one (a global store or atomic in the loop is waited for at its next
     // barrier: 1.6 us an iteration where workgroup 0 recorded as it went)
-    __shared__ float log_gx[kNvRunSteps], log_best[kNvRunSteps];
-    __shared__ uint32_t log_dec[kNvRunSteps];
+    __shared__ float log_gx[kRunSteps], log_best[kRunSteps];
+    __shared__ uint32_t log_dec[kRunSteps];
     __shared__ uint32_t sm_fail;
     const uint32_t tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     if (tid == 0) sm_fail = failure_get(Q.fail);
@@ -114,7 +85,7 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
     draw(epoch);
     float cw = scale(Q.t0);
 
-    uint64_t *lines = Q.words + static_cast<size_t>(r) * A.nwg * kNvRunLine;
+    uint64_t *lines = Q.words + static_cast<size_t>(r) * A.nwg * kRunLine;    // this replication's slots
 
     for (uint64_t t = Q.t0; t < Q.t1; ++t) {
         float x[4], thr[4];
@@ -149,7 +120,7 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
                 gx = fmaf(gj, x[k], gx);
             }
         }
-        uint32_t key = ratio_key(rmin);
+        uint32_t key = value_key(rmin);
         wave_min_key<true>(key, jmin);
         gx = dpp_sum64(gx);
         if (lane == 0) {
@@ -157,7 +128,6 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
             sm_gx[wave] = gx;
         }
         __syncthreads();
-        const uint32_t tag = static_cast<uint32_t>(t) + 1u;
         if (tid == 0) {   // the wavefronts cover ascending product ranges: strict < keeps the lowest index
             uint2 m = sm_key[0];
             float gs = sm_gx[0];
@@ -166,8 +136,7 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
                 if (sm_key[w].x < m.x) m = sm_key[w];
                 gs += sm_gx[w];
             }
-            // the product number takes 24 bits beside 8 bits of the tag (0xFFFFFF: none)
-            exchange_put(lines + static_cast<size_t>(g) * kNvRunLine + 8 * (t & 1), m.x, (m.y << 8) | (tag & 0xFFu));
+            vertex_put(lines, g, t, m.x, m.y);
             log_gx[t - Q.t0] = gs;
         }
 
@@ -180,35 +149,12 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
         cw = scale(t + 1);
 
         // the vertex over the workgroups: the smallest ratio, the lowest product among equal ones
-        key = 0xFFFFFFFFu;
-        uint32_t jm = 0xFFFFFFFFu;
-        bool seen = true;
-        for (uint32_t i = tid; i < A.nwg; i += kNvBlock) {
-            const uint64_t *slot = lines + static_cast<size_t>(i) * kNvRunLine + 8 * (t & 1);
-            uint64_t w = exchange_get(slot);
-            for (uint32_t polls = 0; ((static_cast<uint32_t>(w) ^ tag) & 0xFFu) != 0u; w = exchange_get(slot))
-                if (++polls == kPollLimit) {
-                    seen = false;
-                    break;
-                }
-            const uint32_t xk = static_cast<uint32_t>(w >> 32), xj = static_cast<uint32_t>(w) >> 8;
-            if (xk < key || (xk == key && xj < jm)) {
-                key = xk;
-                jm = xj;
-            }
-        }
-        if (!seen) sm_fail = 1u;
-        wave_min_key<false>(key, jm);
-        if (lane == 0) st_key[wave] = (static_cast<uint64_t>(key) << 32) | jm;
-        __syncthreads();
+        const uint64_t m = vertex_get<kNvBlock>(lines, A.nwg, t, st_key, &sm_fail);
         if (sm_fail) {
             if (tid == 0) failure_raise(Q.fail);
             return;
         }
-        uint64_t m = st_key[0];
-#pragma unroll
-        for (int w = 1; w < kNvBlock / 64; ++w) m = min(m, st_key[w]);
-        const float best = key_ratio(static_cast<uint32_t>(m >> 32));
+        const float best = key_value(static_cast<uint32_t>(m >> 32));
         const uint32_t a = (best < 0.0f) ? static_cast<uint32_t>(m) + 1u : 0u;
         if (recorder) {
             log_best[t - Q.t0] = best;
@@ -235,30 +181,6 @@ __global__ __launch_bounds__(kNvBlock) void nv_run_kernel(NvArgs A, NvRunArgs Q)
     if (active && lead) {
         reinterpret_cast<ulonglong2 *>(sig)[0] = make_ulonglong2(S4[0], S4[1]);
         reinterpret_cast<ulonglong2 *>(sig)[1] = make_ulonglong2(S4[2], S4[3]);
-    }
-}
-
-// The gap, tau and decision count of iteration t0 + blockIdx.x from the logs, the gap in
-// nv_reduce_step's order.
-__global__ __launch_bounds__(kNvBlock) void nv_gap_kernel(NvArgs A, NvRunArgs Q)
-{
-    __shared__ float sm[kNvBlock / 64];
-    const uint32_t tid = threadIdx.x, r = blockIdx.y;
-    const uint64_t row = static_cast<uint64_t>(blockIdx.x) * A.R + r;
-    float gs = 0.0f;
-    for (uint32_t i = tid; i < A.nwg; i += kNvBlock) gs += Q.gx_log[row * A.nwg + i];
-    gs = dpp_sum64(gs);
-    if (tid % 64 == 0) sm[tid / 64] = gs;
-    __syncthreads();
-    if (tid == 0) {
-        float gsum = sm[0];
-        for (int w = 1; w < kNvBlock / 64; ++w) gsum += sm[w];
-        const float best = Q.best_log[row];
-        const float gap = gsum - (best < 0.0f ? A.C * best : 0.0f);
-        // kTauNone is the largest value: the minimum is the first iteration at or below the threshold
-        const uint64_t t = Q.t0 + blockIdx.x;
-        if (gap <= A.gap_eps) atomicMin(A.tau + r, static_cast<uint32_t>(t));
-        atomicAdd(A.cnt + static_cast<uint64_t>(r) * (A.n + 1) + A.dec[static_cast<uint64_t>(r) * A.T + t], 1u);
     }
 }
 
@@ -294,8 +216,8 @@ int launch_nv_run(const NvArgs &A, const NvRunArgs &Q, hipStream_t s)
     if (hipLaunchCooperativeKernel(nv_run_fn((A.S + A.P - 1) / A.P), dim3(A.nwg, A.R), dim3(kNvBlock), args, 0, s) !=
         hipSuccess)
         return -1;
-    hipLaunchKernelGGL(nv_gap_kernel, dim3(static_cast<uint32_t>(Q.t1 - Q.t0), A.R), dim3(kNvBlock), 0, s, A, Q);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    const RunLog L{Q.gx_log, Q.best_log, A.nwg, A.R, A.n, A.C, A.gap_eps, Q.t0, A.T, Q.fail, A.dec, A.tau, A.cnt};
+    return launch_run_log(L, Q.t1 - Q.t0, s);
 }
 
 }  // namespace fw

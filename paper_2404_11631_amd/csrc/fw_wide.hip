@@ -384,7 +384,7 @@ __global__ void wide_finalize_kernel(WideArgs A, uint32_t n_ckpt)
     }
     A.stats[n_streams * kStreamFields] = mn;
     A.stats[n_streams * kStreamFields + 1] = mx;
-    *A.origin_total = origin;
+    *A.origin_total = A.fail && *A.fail ? kWideFailed : origin;
 }
 
 int launch_wide_iteration(const WideArgs &A, uint64_t t, uint32_t epoch, const WideEpoch &E, float cw, bool from_w0,

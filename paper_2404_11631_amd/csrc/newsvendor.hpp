@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "run_shape.hpp"
+
 namespace fw {
 
 constexpr int kNvBlock = 256;                   // threads per workgroup: kNvBlock / P quads of products
@@ -70,27 +72,21 @@ int launch_nv_finalize(const NvArgs &A, uint32_t n_ckpt, hipStream_t s);
 // 32 us against 2.7 us), and the launch-per-iteration kernels keep the chip full without an exchange.
 // Measured (S = 25, K = 1500): n = 1e4 7.7 -> 3.7 ms a call, n = 872 2.3 times, n = 48,000 (S = 30) 1.8 times.
 constexpr uint32_t kNvRunMaxNs = 16;            // samples per lane
-// 64-bit words per workgroup: a 64-byte line for each parity. Workgroups that share a line slow one
-// another's stores and polls: 157 of them exchange a word in 1.6 us at a line each, in 2.5 us at 8
-// bytes each.
-constexpr uint32_t kNvRunLine = 16;
-constexpr uint32_t kNvRunSteps = 1024;          // iterations per launch at most (the length of the gap log)
-
 struct NvRunArgs {
     uint64_t t0, t1;                            // the iterations of this launch
     uint32_t M;                                 // iterations per resample
     uint32_t from_x0;                           // iteration 0 starts from x0_f
-    uint64_t *words;                            // [R][nwg][kNvRunLine] exchange slots, cleared before the run
+    uint64_t *words;                            // [R][nwg][kRunLine] exchange slots, cleared before the run
     uint32_t *fail;                             // raised by a wait that gave up; cleared before the run
     float *gx_log;                              // [t1 - t0][R][nwg] parts of g'x
     float *best_log;                            // [t1 - t0][R] smallest ratios
 };
 
 // Bytes of the slots and the failure word (cleared before a run), and of all the form's scratch.
-inline size_t nv_run_slot_bytes(uint64_t R, uint32_t nwg) { return sizeof(uint64_t) * (kNvRunLine * R * nwg + 1); }
+inline size_t nv_run_slot_bytes(uint64_t R, uint32_t nwg) { return sizeof(uint64_t) * (kRunLine * R * nwg + 1); }
 inline size_t nv_run_bytes(uint64_t R, uint32_t nwg, uint64_t T)
 {
-    return nv_run_slot_bytes(R, nwg) + sizeof(float) * (T < kNvRunSteps ? T : kNvRunSteps) * R * (nwg + 1);
+    return nv_run_slot_bytes(R, nwg) + sizeof(float) * (T < kRunSteps ? T : kRunSteps) * R * (nwg + 1);
 }
 
 bool nv_run_fits(uint32_t nwg, uint32_t R, uint32_t S, uint32_t P, int device);

@@ -76,7 +76,7 @@ int nv_enqueue(sim_ctx *ctx, NvState &w, bool one_launch)
     HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
     if (one_launch) HIP_TRY(ctx, hipMemsetAsync(w.words.ptr, 0, fw::nv_run_slot_bytes(R, w.nwg), st));
     fw::NvArgs A = nv_args(w, &p, R, T, w.seed);
-    A.fail = one_launch ? reinterpret_cast<const uint32_t *>(static_cast<uint64_t *>(w.words.ptr) + fw::kNvRunLine * R * w.nwg) : nullptr;
+    A.fail = one_launch ? reinterpret_cast<const uint32_t *>(static_cast<uint64_t *>(w.words.ptr) + fw::kRunLine * R * w.nwg) : nullptr;
     HIP_TRY(ctx, hipEventRecord(w.ev0, st));
     uint32_t ck = 0;
     if (one_launch) {
@@ -86,10 +86,10 @@ int nv_enqueue(sim_ctx *ctx, NvState &w, bool one_launch)
         Q.words = static_cast<uint64_t *>(w.words.ptr);
         Q.fail = const_cast<uint32_t *>(A.fail);
         Q.gx_log = reinterpret_cast<float *>(static_cast<char *>(w.words.ptr) + fw::nv_run_slot_bytes(R, w.nwg));
-        Q.best_log = Q.gx_log + std::min<uint64_t>(T, fw::kNvRunSteps) * R * w.nwg;
+        Q.best_log = Q.gx_log + std::min<uint64_t>(T, fw::kRunSteps) * R * w.nwg;
         while (Q.t1 < T) {
             Q.t0 = Q.t1;
-            Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kNvRunSteps);
+            Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kRunSteps);
             if (fw::launch_nv_run(A, Q, st))
                 return set_err(ctx, SIM_EDEVICE, "newsvendor launch failed at t=%llu", (unsigned long long)Q.t0);
             for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)

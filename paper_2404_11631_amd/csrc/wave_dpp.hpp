@@ -92,15 +92,20 @@ __device__ __forceinline__ uint32_t dpp_sum_lanes(uint32_t x, uint32_t P)
     return x;
 }
 
-// the smallest of the wavefront's unsigned values, in every lane
-__device__ __forceinline__ uint32_t dpp_min64(uint32_t x)
+// the smallest of each half wavefront's unsigned values, in every lane, and of the wavefront's
+__device__ __forceinline__ uint32_t dpp_min32(uint32_t x)
 {
     x = min(x, dpp_move<0xB1>(x));
     x = min(x, dpp_move<0x4E>(x));
     x = min(x, dpp_move<0x141>(x));
     x = min(x, dpp_move<0x140>(x));
     const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    x = min(h[0], h[1]);
+    return min(h[0], h[1]);
+}
+
+__device__ __forceinline__ uint32_t dpp_min64(uint32_t x)
+{
+    x = dpp_min32(x);
     const auto w = __builtin_amdgcn_permlane32_swap(x, x, false, false);
     return min(w[0], w[1]);
 }

@@ -3,7 +3,10 @@
 // arguments shared by the kernels (fw_wide.hip) and the host driver (wide_api.hip).
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
+
+#include "run_shape.hpp"
 
 namespace fw {
 
@@ -42,8 +45,48 @@ struct WideArgs {
     // outcomes
     double *fval;                               // [n_ckpt + 1][R] f(w_c) per checkpoint, then f(w_T)
     double *stats;                              // kMaxStreams x kStreamFields + 2 (min, max of Y)
-    uint64_t *origin_total;                     // [1] decisions for the origin over all replications
+    uint64_t *origin_total;                     // [1] decisions for the origin over all replications; kWideFailed
+                                                // after a cooperative run that gave up
+    const uint32_t *fail;                       // its failure word (NULL: launch by launch)
 };
+
+constexpr uint64_t kWideFailed = ~0ull;
+
+// ---- many iterations in one cooperative launch (fw_wide_run.hip) ---------------------------------
+// A run takes this form with one sample size, its samples in registers (N <= 63), and at most
+// kWideRunMaxUnits workgroups (units) per replication, all of them twice per compute unit.
+// Measured (N = 25, K = 1500, device ms): d = 216 16.9 -> 5.7, 3,000 17.1 -> 6.3, 10,000 16.8 -> 6.5,
+// 50,000 19.8 -> 9.5. Past 512 units the vertex exchange (units^2 words) outgrows the launches it saves.
+constexpr uint32_t kWideDirectUnits = 32;       // d <= 4,096: the dots in one exchange
+constexpr uint32_t kWideRunMaxUnits = 512;      // d <= 65,536
+constexpr uint32_t kWideRunMaxN = 63;
+
+// items (N samples and s1'v) per chunk the kernel holds: 2, 4 or 8
+inline uint32_t wide_run_ns(uint32_t N) { return N < 2 * kWideChunks ? 2 : N < 4 * kWideChunks ? 4 : 8; }
+
+struct WideRunArgs {
+    uint64_t t0, t1;                            // the iterations of this launch
+    uint32_t M;                                 // iterations per resample
+    uint32_t from_w0;                           // iteration 0 starts from w0_f
+    float inv_n;
+    uint64_t *words;                            // vertex words, [R][unit][kRunLine]; the units' parts of the
+                                                // items, [R][2][units][8 NS]; the items' sums, [R][2][8 NS][8];
+                                                // cleared before the run
+    uint32_t *fail;                             // raised by a wait that gave up; cleared before the run
+    float *gw_log;                              // [t1 - t0][R][nwg] parts of g'w
+    float *best_log;                            // [t1 - t0][R] smallest gradient entries
+};
+
+// Bytes of the slots and the failure word (cleared before a run), and of all the form's scratch.
+inline size_t wide_run_slot_bytes(uint64_t R, uint32_t nwg, uint32_t N)
+{
+    const size_t items = kWideChunks * wide_run_ns(N);
+    return sizeof(uint64_t) * (R * (nwg * kRunLine + 2 * items * nwg + 16 * items) + 1);
+}
+inline size_t wide_run_bytes(uint64_t R, uint32_t nwg, uint32_t N, uint64_t T)
+{
+    return wide_run_slot_bytes(R, nwg, N) + sizeof(float) * (T < kRunSteps ? T : kRunSteps) * R * (nwg + 1);
+}
 
 // The sample size of one epoch: N_k returns, 1/N_k, and the factors N0/N_k and (N0-1)/(N_k-1) that
 // turn the base coefficients c1, c2 into those of N_k (exactly 1 when N_k = N0).
@@ -92,6 +135,8 @@ int launch_wide_iteration(const WideArgs &A, uint64_t t, uint32_t epoch, const W
 int launch_wide_step(const WideArgs &A, uint64_t t, hipStream_t s);
 // f(w) at w = c S into fval[slot][r].
 int launch_wide_objective(const WideArgs &A, double c, uint32_t slot, hipStream_t s);
+bool wide_run_fits(uint32_t nwg, uint32_t R, uint32_t N, int device);
+int launch_wide_run(const WideArgs &A, const WideRunArgs &Q, hipStream_t s);
 // Cross-replication statistics of Y and of the n_ckpt checkpoints into stats.
 int launch_wide_finalize(const WideArgs &A, uint32_t n_ckpt, hipStream_t s);
 

@@ -77,6 +77,89 @@ fw::WideArgs wide_args(WideState &w, const sim_params *p, uint64_t R, uint64_t T
     return A;
 }
 
+// Enqueues the run that w describes (parameters, coefficients and buffers in place): the cooperative
+// form, one launch between objective evaluations, or the launch sequence. n_schedule: per-epoch
+// sample sizes (launch sequence only).
+int wide_enqueue(sim_ctx *ctx, WideState &w, const uint32_t *n_schedule, uint32_t Nmax, bool one_launch)
+{
+    hipStream_t st = ctx->stream;
+    const sim_params &p = w.params;
+    const uint64_t R = w.R, T = w.T;
+    const size_t D = p.d;
+    const uint32_t nc = p.n_checkpoints, N = p.n_samples;
+    HIP_TRY(ctx, hipMemsetAsync(w.S.ptr, 0, sizeof(uint64_t) * R * D, st));
+    HIP_TRY(ctx, hipMemsetAsync(w.cnt.ptr, 0, sizeof(uint32_t) * R * (D + 1), st));
+    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
+    fw::WideArgs A = wide_args(w, &p, R, T, w.seed);
+    A.N = Nmax;
+    const size_t slots = one_launch ? fw::wide_run_slot_bytes(R, w.nwg, N) : 0;
+    if (one_launch) {
+        HIP_TRY(ctx, hipMemsetAsync(w.words.ptr, 0, slots, st));
+        A.fail = reinterpret_cast<const uint32_t *>(static_cast<char *>(w.words.ptr) + slots - sizeof(uint64_t));
+    }
+    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
+    auto objective = [&](double c, uint32_t slot) {
+        return fw::launch_wide_objective(A, c, slot, st) ? set_err(ctx, SIM_EDEVICE, "wide objective launch failed") : 0;
+    };
+    if (one_launch) {
+        fw::WideRunArgs Q{};
+        Q.M = p.resample_every;
+        Q.from_w0 = w.from_w0 ? 1u : 0u;
+        Q.inv_n = static_cast<float>(1.0 / N);
+        Q.words = static_cast<uint64_t *>(w.words.ptr);
+        Q.fail = const_cast<uint32_t *>(A.fail);
+        Q.gw_log = reinterpret_cast<float *>(static_cast<char *>(w.words.ptr) + slots);
+        Q.best_log = Q.gw_log + std::min<uint64_t>(T, fw::kRunSteps) * R * w.nwg;
+        uint32_t ck = 0;
+        while (Q.t1 < T) {
+            Q.t0 = Q.t1;
+            Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kRunSteps);
+            if (fw::launch_wide_run(A, Q, st))
+                return set_err(ctx, SIM_EDEVICE, "wide launch failed at t=%llu", (unsigned long long)Q.t0);
+            for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
+                if (int rc = objective(2.0 / (static_cast<double>(Q.t1) * static_cast<double>(Q.t1 + 1)), ck)) return rc;
+        }
+    } else {
+        // The step of iteration t runs inside the next iteration's sample launch unless an objective
+        // evaluation needs the updated signature first or t is the last iteration.
+        const int lrc = fw::wide_sequence(
+            N, n_schedule, p.resample_every, T, w.from_w0, nc, p.checkpoints,
+            [&](uint64_t t, uint32_t e, const fw::WideEpoch &E, float cw, bool from_w0, bool fold_prev) {
+                return fw::launch_wide_iteration(A, t, e, E, cw, from_w0, fold_prev, st)
+                           ? set_err(ctx, SIM_EDEVICE, "wide launch failed at t=%llu", (unsigned long long)t)
+                           : 0;
+            },
+            [&](uint64_t t) {
+                return fw::launch_wide_step(A, t, st)
+                           ? set_err(ctx, SIM_EDEVICE, "wide step launch failed at t=%llu", (unsigned long long)t)
+                           : 0;
+            },
+            objective);
+        if (lrc) return lrc;
+    }
+    if (fw::launch_wide_objective(A, 2.0 / (static_cast<double>(T) * static_cast<double>(T + 1)), nc, st) ||
+        fw::launch_wide_finalize(A, nc, st))
+        return set_err(ctx, SIM_EDEVICE, "wide finalize launch failed");
+    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
+    w.unsettled = one_launch;
+    return SIM_OK;
+}
+
+// Waits for the last run and reads the origin's total. A cooperative run whose workgroups gave up
+// waiting for one another left kWideFailed there and is repeated launch by launch.
+int wide_settle(sim_ctx *ctx, WideState &w, uint64_t &origin)
+{
+    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    if (origin == fw::kWideFailed) {
+        if (int rc = wide_enqueue(ctx, w, nullptr, w.params.n_samples, false)) return rc;
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+        HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    }
+    w.unsettled = false;
+    return SIM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -137,45 +220,23 @@ int sim_run_wide(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint
         (rc = ensure(ctx, w.stats, sizeof(double) * (fw::kMaxStreams * fw::kStreamFields + 2))) ||
         (rc = ensure(ctx, w.origin, sizeof(uint64_t))))
         return rc;
+    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
+    const bool one_launch = !p->n_schedule && fw::wide_run_fits(w.nwg, static_cast<uint32_t>(R), N, ctx->device) &&
+                            ensure(ctx, w.words, fw::wide_run_bytes(R, w.nwg, N, T)) == SIM_OK;
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipMemcpyAsync(w.asset_f.ptr, af.data(), sizeof(float) * af.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.asset_d.ptr, ad.data(), sizeof(double) * ad.size(), hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.S.ptr, 0, sizeof(uint64_t) * R * D, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.cnt.ptr, 0, sizeof(uint32_t) * R * (D + 1), st));
-    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
     // the host vectors must outlive the copies
     HIP_TRY(ctx, hipStreamSynchronize(st));
-
-    const fw::WideArgs A = wide_args(w, p, R, T, seed);
-    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
-    // The step of iteration t runs inside the next iteration's sample launch unless an objective
-    // evaluation needs the updated signature first or t is the last iteration.
-    const int lrc = fw::wide_sequence(
-        N, p->n_schedule, p->resample_every, T, p->w0 != nullptr, nc, p->checkpoints,
-        [&](uint64_t t, uint32_t e, const fw::WideEpoch &E, float cw, bool from_w0, bool fold_prev) {
-            return fw::launch_wide_iteration(A, t, e, E, cw, from_w0, fold_prev, st)
-                       ? set_err(ctx, SIM_EDEVICE, "wide launch failed at t=%llu", (unsigned long long)t)
-                       : 0;
-        },
-        [&](uint64_t t) {
-            return fw::launch_wide_step(A, t, st)
-                       ? set_err(ctx, SIM_EDEVICE, "wide step launch failed at t=%llu", (unsigned long long)t)
-                       : 0;
-        },
-        [&](double c, uint32_t slot) {
-            return fw::launch_wide_objective(A, c, slot, st) ? set_err(ctx, SIM_EDEVICE, "wide objective launch failed") : 0;
-        });
-    if (lrc) return lrc;
-    if (fw::launch_wide_objective(A, 2.0 / (static_cast<double>(T) * static_cast<double>(T + 1)), nc, st) ||
-        fw::launch_wide_finalize(A, nc, st))
-        return set_err(ctx, SIM_EDEVICE, "wide finalize launch failed");
-    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
 
     w.params = *p;
     w.params.mu = w.params.sigma = w.params.chol = w.params.w0 = w.params.cv_ref = nullptr;
     w.params.n_schedule = nullptr;
+    w.from_w0 = p->w0 != nullptr;
+    w.seed = seed;
     w.R = R;
     w.T = T;
+    if (int rc2 = wide_enqueue(ctx, w, p->n_schedule, Nmax, one_launch)) return rc2;
     w.fstar = kkt_fstar(p->mu, p->sigma, d, p->risk_coef);
     w.have = true;
     return SIM_OK;
@@ -187,13 +248,12 @@ int sim_wide_stats(sim_ctx *ctx, sim_stats_out *out)
     WideState &w = ctx->wide;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no wide run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
     const uint32_t nc = w.params.n_checkpoints, n_streams = 1 + 2 * nc;
     double F[fw::kMaxStreams * fw::kStreamFields + 2];
     uint64_t origin = 0;
     std::vector<uint32_t> tau(w.R);
+    if (int rc = wide_settle(ctx, w, origin)) return rc;
     HIP_TRY(ctx, hipMemcpy(F, w.stats.ptr, sizeof(double) * (n_streams * fw::kStreamFields + 2), hipMemcpyDeviceToHost));
-    HIP_TRY(ctx, hipMemcpy(&origin, w.origin.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
     HIP_TRY(ctx, hipMemcpy(tau.data(), w.tau.ptr, sizeof(uint32_t) * w.R, hipMemcpyDeviceToHost));
     float ms = 0.0f;
     HIP_TRY(ctx, hipEventElapsedTime(&ms, w.ev0, w.ev1));
@@ -214,7 +274,12 @@ int sim_wide_paths(sim_ctx *ctx, sim_wide_view *out)
     WideState &w = ctx->wide;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no wide run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    if (w.unsettled) {
+        uint64_t origin;
+        if (int rc = wide_settle(ctx, w, origin)) return rc;
+    } else {
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    }
     std::memset(out, 0, sizeof(*out));
     out->R = w.R;
     out->T = w.T;

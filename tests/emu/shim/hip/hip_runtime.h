@@ -27,6 +27,9 @@ inline float4 make_float4(float x, float y, float z, float w) { return float4{x,
 struct uint4 { unsigned x, y, z, w; };
 struct double2 { double x, y; };
 struct ulonglong2 { unsigned long long x, y; };
+inline ulonglong2 make_ulonglong2(unsigned long long x, unsigned long long y) { return ulonglong2{x, y}; }
+struct uint2 { unsigned x, y; };
+inline uint2 make_uint2(unsigned x, unsigned y) { return uint2{x, y}; }
 template <class T> inline T atomicAdd(T *p, T v) { return std::atomic_ref<T>(*p).fetch_add(v); }
 inline double2 make_double2(double x, double y) { return double2{x, y}; }
 inline unsigned __umulhi(unsigned a, unsigned b) { return static_cast<unsigned>((static_cast<unsigned long long>(a) * b) >> 32); }
@@ -85,6 +88,18 @@ template <class T> inline T __shfl_down(T v, unsigned off, int width = 64)
 inline void __syncthreads() { g_block->bar->arrive_and_wait(); }
 // threads are not lockstep here: the wave barrier synchronizes the wavefront's 64 threads
 inline void __builtin_amdgcn_wave_barrier() { g_block->wave[threadIdx.x / 64]->arrive_and_wait(); }
+// the lanes of the wavefront for which p holds, and one lane's value for all of them
+inline uint64_t __builtin_amdgcn_ballot_w64(bool p)
+{
+    const int base = threadIdx.x / 64 * 64;
+    g_block->slot[threadIdx.x] = p;
+    g_block->wave[threadIdx.x / 64]->arrive_and_wait();
+    uint64_t m = 0;
+    for (int i = 0; i < 64; ++i) m |= static_cast<uint64_t>(g_block->slot[base + i] != 0) << i;
+    g_block->wave[threadIdx.x / 64]->arrive_and_wait();
+    return m;
+}
+inline uint32_t __builtin_amdgcn_readlane(uint32_t v, int lane) { return emu_exchange(v, threadIdx.x / 64 * 64 + lane); }
 // DPP: quad_perm (dpp_ctrl < 0x100), lane 4q + i reads lane 4q + ((ctrl >> 2i) & 3); row_mirror
 // (0x140), lane i of a 16-lane row reads lane 15 - i; row_half_mirror (0x141), lane i of an 8-lane
 // half row reads lane 7 - i
@@ -94,6 +109,7 @@ inline int __builtin_amdgcn_mov_dpp(int v, int ctrl, int, int, bool)
     int src;
     if (ctrl == 0x140) src = (lane & ~15) | (15 - (lane & 15));
     else if (ctrl == 0x141) src = (lane & ~7) | (7 - (lane & 7));
+    else if (ctrl > 0x120 && ctrl < 0x130) src = (lane & ~15) | ((lane - (ctrl & 15)) & 15);   // row rotation
     else src = (lane & ~3) | ((ctrl >> (2 * (lane & 3))) & 3);
     return emu_exchange(v, base + src, 32);   // within a half wavefront: a half may call it alone
 }

@@ -50,3 +50,24 @@ def test_newsvendor(n, S, M, R, T, x0, ckpt):
     a, b = both(run, records)
     same(a, b)
     assert a["cnt"].sum() == R * T
+
+
+@pytest.mark.parametrize("d,N,M,R,T,w0,ckpt", [
+    (4, 2, 1, 1, 1, False, ()), (128, 15, 1, 1, 40, False, (1, 40)), (132, 16, 3, 3, 1030, True, (1024,)),
+    (4096, 31, 1, 1, 30, False, (30,)), (4100, 32, 2, 2, 30, True, (7,)), (8192, 63, 1, 7, 20, False, ()),
+    (24_576, 8, 1, 1, 20, False, (20,)), (24_580, 25, 1, 1, 20, False, (3, 4)), (65_536, 50, 1, 1, 12, True, (12,))])
+def test_wide(d, N, M, R, T, w0, ckpt):
+    print(f"[one launch] wide d={d} N={N} M={M} R={R} T={T}", flush=True)
+    mu, sigma = workloads.diag_instance(3, 0, d, "paper")
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, w0=np.full(d, 0.5 / d) if w0 else None, checkpoints=ckpt, gap_eps=0.02)
+
+    def run(ctx):
+        ctx.run_wide(p, R, T, 5)
+
+    def records(ctx):
+        st = ctx.wide_stats()
+        return dict(ctx.wide_paths(), mean=st.mean, origin=st.decision_total[0], tau_count=st.tau_count)
+
+    a, b = both(run, records)
+    same(a, b)
+    assert a["cnt"].sum() == R * T
