@@ -479,6 +479,8 @@ int sim_nv_paths(sim_ctx *ctx, sim_wide_view *out);
  * samples as sim_run_newsvendor, compared with x_j in FP64. The iterate x is kept in FP64 and
  * updated as x + gamma (s - x) with gamma = 2/(t+2), separately rounded (no fused operations).
  * Y = f(x_T) and the checkpoints f(x_c) come from Eq. (6).
+ * Up to n = 15,360 (S <= 128 at most, few enough replications for the device to hold at once) a cooperative
+ * launch runs all iterations between two checkpoints, with the same vertices, iterates and pivots.
  * The params' c and C are not used (c may be NULL). Requires: 1 <= M <= SIM_NV_MAX_RES, A >= 0
  * with a positive entry in every column (X is then bounded), C > 0, x0 in X, n <= SIM_NV_LP_MAX_N,
  * R T <= 2^24. Asynchronous on the context's stream. Results: sim_nv_lp_stats (f_star NaN;

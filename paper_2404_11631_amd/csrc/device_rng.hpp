@@ -24,6 +24,10 @@
 #ifndef FW_PIN_VGPR
 #define FW_PIN_VGPR(x) asm volatile("" : "+v"(x))
 #endif
+// The same for a wavefront-uniform value in a scalar register.
+#ifndef FW_PIN_SGPR
+#define FW_PIN_SGPR(x) asm volatile("" : "+s"(x))
+#endif
 
 namespace fw {
 

@@ -8,6 +8,7 @@
 #include "../../include/sim.h"
 #include "host_core.hpp"
 #include "mlp.hpp"
+#include "newsvendor.hpp"
 #include "sim_types.hpp"
 
 namespace fw {
@@ -99,7 +100,9 @@ struct NvLpState {
     sim_nv_params params{};               // pointers cleared
     uint32_t M = 0, nwg = 0, P = 1;       // resource rows; gradient workgroups; lanes per quad
     uint64_t R = 0, T = 0;
-    DevBuf prod_d, Am, Cv, x, g, rec_basis, rec_value, rec_piv, tau, origin, cost_part, fval, stats, origin_total;
+    fw::NvLpArgs args{};                  // the last run's device arguments
+    bool unsettled = false;               // the last run was cooperative and its failure word is unread
+    DevBuf prod_d, Am, Cv, x, g, rec_basis, rec_value, rec_piv, tau, origin, cost_part, fval, stats, origin_total, words;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
 };
 

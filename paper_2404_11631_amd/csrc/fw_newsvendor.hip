@@ -24,6 +24,7 @@
 #include "device_reduce.hpp"
 #include "device_rng.hpp"
 #include "newsvendor.hpp"
+#include "newsvendor_device.hpp"
 #include "sim_types.hpp"
 #include "wave_dpp.hpp"
 
@@ -346,23 +347,6 @@ __global__ void nv_finalize_kernel(NvArgs A, uint32_t n_ckpt)
 
 namespace {
 
-// x + gamma (s - x) with each operation rounded on its own (contraction into a fused multiply-add is
-// off here), so that any other implementation of the same formula in FP64 gets the same bits.
-__device__ __forceinline__ double nv_lp_move(double x, double s, double gamma)
-{
-#pragma clang fp contract(off)
-    const double step = gamma * (s - x);
-    return x + step;
-}
-
-// Eq. (9): (k - v) + ((h + v) count) / S, each operation rounded on its own.
-__device__ __forceinline__ double nv_lp_grad(double km, double hv, uint32_t count, uint32_t S)
-{
-#pragma clang fp contract(off)
-    const double part = (hv * static_cast<double>(count)) / static_cast<double>(S);
-    return km + part;
-}
-
 // s_j of the vertex recorded for iteration t of replication r: the basic value where the basis
 // holds product j, else 0.
 __device__ __forceinline__ double nv_lp_vertex(const NvLpArgs &A, uint32_t r, uint64_t t, uint32_t j)
@@ -682,7 +666,7 @@ __global__ void nv_lp_finalize_kernel(NvLpArgs A, uint32_t n_ckpt)
     nv_stream_stats(A.fval, A.R, n_ckpt, A.stats);
     uint64_t origin = 0;
     for (uint32_t r = 0; r < A.R; ++r) origin += A.origin[r];
-    *A.origin_total = origin;
+    *A.origin_total = A.fail && *A.fail ? kNvFailed : origin;
 }
 
 int launch_nv_lp_gradient(const NvLpArgs &A, uint64_t t, uint32_t epoch, bool fold_prev, hipStream_t s)

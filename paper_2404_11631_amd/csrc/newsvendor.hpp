@@ -127,8 +127,36 @@ struct NvLpArgs {
     double *cost_part;                          // [R][ceil(n / kNvCostChunk)][2]
     double *fval;                               // [n_ckpt + 1][R]
     double *stats;                              // kMaxStreams x kStreamFields + 2
-    uint64_t *origin_total;
+    uint64_t *origin_total;                     // kNvFailed after a cooperative run that gave up
+    const uint32_t *fail;                       // its failure word (NULL: launch by launch)
 };
+
+// ---- many iterations in one cooperative launch (fw_newsvendor_lp_run.hip) ------------------------
+// A run takes this form when g fits in LDS, the samples of an epoch in a lane's registers, and the
+// sample workgroups and the simplex workgroup have a compute unit each. Faster at every such size.
+// 1,500 iterations, S = 25, launch by launch -> one launch, ms: n = 100, 3 rows 28.2 -> 10.8; n = 1,000
+// with 1 row 21.6 -> 8.0, 3 rows 45.6 -> 14.7, 6 rows 97.9 -> 26.3, 3 rows and 7 replications 59.5 ->
+// 14.9; n = 4,000, 3 rows 67.9 -> 32.0; n = 10,000, 3 rows 104.3 -> 61.9.
+constexpr uint32_t kLpRunMaxNs = 8;             // samples per lane
+constexpr uint32_t kLpRunSteps = 256;           // iterations per launch at most (the length of the LDS logs)
+constexpr uint32_t kLpVertexWords = 24;         // three words for each of up to 8 basic columns
+constexpr size_t kLpRunLds = 120 * 1024;        // g, and A where it fits: n (M + 1) <= 15,360
+
+struct NvLpRunArgs {
+    uint64_t t0, t1;                            // the iterations of this launch
+    uint32_t Mr;                                // iterations per resample
+    uint64_t *words;                            // [R][2][nq] counts, then [R][2][kLpVertexWords]; cleared before the run
+    uint32_t *fail;                             // raised by a wait that gave up; cleared before the run
+    double *gx_log;                             // [t1 - t0][R][nwg] parts of g'x
+    double *gs_log;                             // [t1 - t0][R] g's
+};
+
+// Bytes of the slots and the failure word (cleared before a run), and of all the form's scratch.
+inline size_t nv_lp_run_slot_bytes(uint64_t R, uint32_t nq) { return sizeof(uint64_t) * (R * 2 * (nq + kLpVertexWords) + 1); }
+inline size_t nv_lp_run_bytes(uint64_t R, uint32_t nq, uint32_t nwg, uint64_t T)
+{
+    return nv_lp_run_slot_bytes(R, nq) + sizeof(double) * (T < kLpRunSteps ? T : kLpRunSteps) * R * (nwg + 1);
+}
 
 // The launches of a run of T iterations (resample every M): for each t, gradient(t, epoch, fold_prev)
 // and subproblem(t); update(t) where the update cannot wait for the next gradient launch (a cost
@@ -155,6 +183,8 @@ int nv_lp_sequence(uint64_t M, uint64_t T, uint32_t n_ckpt, const uint64_t *chec
     return 0;
 }
 
+bool nv_lp_run_fits(const NvLpArgs &A, int device);
+int launch_nv_lp_run(const NvLpArgs &A, const NvLpRunArgs &Q, hipStream_t s);
 // Iteration t's gradient at x_t; with fold_prev it first moves x to x_t = x_{t-1} + gamma (s - x_{t-1})
 // with the vertex the previous subproblem launch recorded.
 int launch_nv_lp_gradient(const NvLpArgs &A, uint64_t t, uint32_t epoch, bool fold_prev, hipStream_t s);

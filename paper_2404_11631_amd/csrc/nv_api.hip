@@ -138,6 +138,91 @@ int nv_settle(sim_ctx *ctx, NvState &w, uint64_t &origin)
     return SIM_OK;
 }
 
+// Enqueues the general-constraint run that w describes: the cooperative form, one launch between cost
+// evaluations, or two launches per iteration. Every replication starts at x_0 (in prod_d).
+int nv_lp_enqueue(sim_ctx *ctx, NvLpState &w, bool one_launch)
+{
+    hipStream_t st = ctx->stream;
+    const sim_nv_params &p = w.params;
+    const uint64_t R = w.R, T = w.T;
+    const size_t N = p.n;
+    const uint32_t nc = p.n_checkpoints;
+    for (uint64_t r = 0; r < R; ++r)
+        HIP_TRY(ctx, hipMemcpyAsync(static_cast<double *>(w.x.ptr) + r * N, w.args.x0_d, sizeof(double) * N,
+                                    hipMemcpyDeviceToDevice, st));
+    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
+    HIP_TRY(ctx, hipMemsetAsync(w.origin.ptr, 0, sizeof(uint32_t) * R, st));
+    fw::NvLpArgs A = w.args;
+    A.fail = nullptr;
+    const size_t slots = fw::nv_lp_run_slot_bytes(R, A.nq);
+    if (one_launch) {
+        HIP_TRY(ctx, hipMemsetAsync(w.words.ptr, 0, slots, st));
+        A.fail = reinterpret_cast<const uint32_t *>(static_cast<char *>(w.words.ptr) + slots - sizeof(uint64_t));
+    }
+    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
+    auto cost = [&](uint32_t slot) {
+        return fw::launch_nv_lp_cost(A, slot, st) ? set_err(ctx, SIM_EDEVICE, "newsvendor cost launch failed") : 0;
+    };
+    if (one_launch) {
+        fw::NvLpRunArgs Q{};
+        Q.Mr = p.resample_every;
+        Q.words = static_cast<uint64_t *>(w.words.ptr);
+        Q.fail = const_cast<uint32_t *>(A.fail);
+        Q.gx_log = reinterpret_cast<double *>(static_cast<char *>(w.words.ptr) + slots);
+        Q.gs_log = Q.gx_log + std::min<uint64_t>(T, fw::kLpRunSteps) * R * A.nwg;
+        uint32_t ck = 0;
+        while (Q.t1 < T) {
+            Q.t0 = Q.t1;
+            Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kLpRunSteps);
+            if (fw::launch_nv_lp_run(A, Q, st))
+                return set_err(ctx, SIM_EDEVICE, "newsvendor launch failed at t=%llu", (unsigned long long)Q.t0);
+            for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
+                if (int rc = cost(ck)) return rc;
+        }
+    } else {
+        // The update of iteration t runs at the start of the next iteration's gradient launch unless a
+        // cost evaluation needs x_{t+1} first or t is the last iteration.
+        const int lrc = fw::nv_lp_sequence(
+            p.resample_every, T, nc, p.checkpoints,
+            [&](uint64_t t, uint32_t epoch, bool fold_prev) {
+                return fw::launch_nv_lp_gradient(A, t, epoch, fold_prev, st)
+                           ? set_err(ctx, SIM_EDEVICE, "newsvendor gradient launch failed at t=%llu", (unsigned long long)t)
+                           : 0;
+            },
+            [&](uint64_t t) {
+                return fw::launch_nv_lp_subproblem(A, t, st)
+                           ? set_err(ctx, SIM_EDEVICE, "newsvendor subproblem launch failed at t=%llu", (unsigned long long)t)
+                           : 0;
+            },
+            [&](uint64_t t) {
+                return fw::launch_nv_lp_update(A, t, st)
+                           ? set_err(ctx, SIM_EDEVICE, "newsvendor update launch failed at t=%llu", (unsigned long long)t)
+                           : 0;
+            },
+            cost);
+        if (lrc) return lrc;
+    }
+    if (fw::launch_nv_lp_cost(A, nc, st) || fw::launch_nv_lp_finalize(A, nc, st))
+        return set_err(ctx, SIM_EDEVICE, "newsvendor finalize launch failed");
+    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
+    w.unsettled = one_launch;
+    return SIM_OK;
+}
+
+// nv_settle for the general-constraint run.
+int nv_lp_settle(sim_ctx *ctx, NvLpState &w, uint64_t &origin)
+{
+    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    HIP_TRY(ctx, hipMemcpy(&origin, w.origin_total.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    if (origin == fw::kNvFailed) {
+        if (int rc = nv_lp_enqueue(ctx, w, false)) return rc;
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+        HIP_TRY(ctx, hipMemcpy(&origin, w.origin_total.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
+    }
+    w.unsettled = false;
+    return SIM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -339,11 +424,6 @@ int sim_run_newsvendor_lp(sim_ctx *ctx, const sim_nv_params *p, const sim_nv_con
     HIP_TRY(ctx, hipMemcpyAsync(w.prod_d.ptr, pd.data(), sizeof(double) * pd.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.Am.ptr, con->A, sizeof(double) * M * N, hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.Cv.ptr, con->C, sizeof(double) * M, hipMemcpyHostToDevice, st));
-    for (uint64_t r = 0; r < R; ++r)       // every replication starts at x_0
-        HIP_TRY(ctx, hipMemcpyAsync(static_cast<double *>(w.x.ptr) + r * N, pd.data() + 8 * N, sizeof(double) * N,
-                                    hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.tau.ptr, 0xFF, sizeof(uint32_t) * R, st));
-    HIP_TRY(ctx, hipMemsetAsync(w.origin.ptr, 0, sizeof(uint32_t) * R, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));   // the host vectors must outlive the copies
 
     fw::NvLpArgs A{};
@@ -386,39 +466,16 @@ int sim_run_newsvendor_lp(sim_ctx *ctx, const sim_nv_params *p, const sim_nv_con
     A.stats = static_cast<double *>(w.stats.ptr);
     A.origin_total = static_cast<uint64_t *>(w.origin_total.ptr);
 
-    HIP_TRY(ctx, hipEventRecord(w.ev0, st));
-    // The update of iteration t runs at the start of the next iteration's gradient launch unless a
-    // cost evaluation needs x_{t+1} first or t is the last iteration.
-    const int lrc = fw::nv_lp_sequence(
-        p->resample_every, T, nc, p->checkpoints,
-        [&](uint64_t t, uint32_t epoch, bool fold_prev) {
-            return fw::launch_nv_lp_gradient(A, t, epoch, fold_prev, st)
-                       ? set_err(ctx, SIM_EDEVICE, "newsvendor gradient launch failed at t=%llu", (unsigned long long)t)
-                       : 0;
-        },
-        [&](uint64_t t) {
-            return fw::launch_nv_lp_subproblem(A, t, st)
-                       ? set_err(ctx, SIM_EDEVICE, "newsvendor subproblem launch failed at t=%llu", (unsigned long long)t)
-                       : 0;
-        },
-        [&](uint64_t t) {
-            return fw::launch_nv_lp_update(A, t, st)
-                       ? set_err(ctx, SIM_EDEVICE, "newsvendor update launch failed at t=%llu", (unsigned long long)t)
-                       : 0;
-        },
-        [&](uint32_t slot) {
-            return fw::launch_nv_lp_cost(A, slot, st) ? set_err(ctx, SIM_EDEVICE, "newsvendor cost launch failed") : 0;
-        });
-    if (lrc) return lrc;
-    if (fw::launch_nv_lp_cost(A, nc, st) || fw::launch_nv_lp_finalize(A, nc, st))
-        return set_err(ctx, SIM_EDEVICE, "newsvendor finalize launch failed");
-    HIP_TRY(ctx, hipEventRecord(w.ev1, st));
-
+    w.args = A;
     w.params = *p;
     w.params.mu = w.params.sigma = w.params.k = w.params.h = w.params.v = w.params.c = w.params.x0 = nullptr;
     w.M = M;
     w.R = R;
     w.T = T;
+    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
+    const bool one_launch = fw::nv_lp_run_fits(A, ctx->device) &&
+                            ensure(ctx, w.words, fw::nv_lp_run_bytes(R, A.nq, A.nwg, T)) == SIM_OK;
+    if (int rc2 = nv_lp_enqueue(ctx, w, one_launch)) return rc2;
     w.have = true;
     return SIM_OK;
 }
@@ -429,13 +486,12 @@ int sim_nv_lp_stats(sim_ctx *ctx, sim_stats_out *out)
     NvLpState &w = ctx->nvlp;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no general-constraint newsvendor run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
     const uint32_t nc = w.params.n_checkpoints, n_streams = 1 + 2 * nc;
     double F[fw::kMaxStreams * fw::kStreamFields + 2];
     uint64_t origin = 0;
     std::vector<uint32_t> tau(w.R);
+    if (int rc = nv_lp_settle(ctx, w, origin)) return rc;
     HIP_TRY(ctx, hipMemcpy(F, w.stats.ptr, sizeof(double) * (n_streams * fw::kStreamFields + 2), hipMemcpyDeviceToHost));
-    HIP_TRY(ctx, hipMemcpy(&origin, w.origin_total.ptr, sizeof(uint64_t), hipMemcpyDeviceToHost));
     HIP_TRY(ctx, hipMemcpy(tau.data(), w.tau.ptr, sizeof(uint32_t) * w.R, hipMemcpyDeviceToHost));
     float ms = 0.0f;
     HIP_TRY(ctx, hipEventElapsedTime(&ms, w.ev0, w.ev1));
@@ -456,7 +512,12 @@ int sim_nv_lp_paths(sim_ctx *ctx, sim_nv_lp_view *out)
     NvLpState &w = ctx->nvlp;
     if (!w.have) return set_err(ctx, SIM_ESTATE, "no general-constraint newsvendor run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    if (w.unsettled) {
+        uint64_t origin;
+        if (int rc = nv_lp_settle(ctx, w, origin)) return rc;
+    } else {
+        HIP_TRY(ctx, hipEventSynchronize(w.ev1));
+    }
     std::memset(out, 0, sizeof(*out));
     out->R = w.R;
     out->T = w.T;

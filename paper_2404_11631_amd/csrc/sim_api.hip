@@ -217,7 +217,7 @@ void sim_destroy(sim_ctx *ctx)
         if (e) (void)hipEventDestroy(e);
     NvLpState &lp = ctx->nvlp;
     for (DevBuf *x : {&lp.prod_d, &lp.Am, &lp.Cv, &lp.x, &lp.g, &lp.rec_basis, &lp.rec_value, &lp.rec_piv,
-                      &lp.tau, &lp.origin, &lp.cost_part, &lp.fval, &lp.stats, &lp.origin_total})
+                      &lp.tau, &lp.origin, &lp.cost_part, &lp.fval, &lp.stats, &lp.origin_total, &lp.words})
         free_buf(*x);
     for (hipEvent_t e : {lp.ev0, lp.ev1})
         if (e) (void)hipEventDestroy(e);

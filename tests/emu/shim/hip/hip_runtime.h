@@ -99,6 +99,7 @@ inline uint64_t __builtin_amdgcn_ballot_w64(bool p)
     g_block->wave[threadIdx.x / 64]->arrive_and_wait();
     return m;
 }
+inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return emu_exchange(v, threadIdx.x / 64 * 64); }
 inline uint32_t __builtin_amdgcn_readlane(uint32_t v, int lane) { return emu_exchange(v, threadIdx.x / 64 * 64 + lane); }
 // DPP: quad_perm (dpp_ctrl < 0x100), lane 4q + i reads lane 4q + ((ctrl >> 2i) & 3); row_mirror
 // (0x140), lane i of a 16-lane row reads lane 15 - i; row_half_mirror (0x141), lane i of an 8-lane
@@ -155,6 +156,7 @@ inline float __builtin_amdgcn_rsqf(float x) { return 1.0f / std::sqrt(x); }
 // three-input bitwise function given by its 8-entry truth table, row index 4 a + 2 b + c
 // register pinning is an optimiser hint on the device; nothing to do on the host
 #define FW_PIN_VGPR(x) ((void)(x))
+#define FW_PIN_SGPR(x) ((void)(x))
 
 inline uint32_t __builtin_amdgcn_bitop3_b32(uint32_t a, uint32_t b, uint32_t c, uint32_t lut)
 {

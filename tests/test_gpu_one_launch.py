@@ -71,3 +71,26 @@ def test_wide(d, N, M, R, T, w0, ckpt):
     a, b = both(run, records)
     same(a, b)
     assert a["cnt"].sum() == R * T
+
+
+@pytest.mark.parametrize("n,m,S,M,R,T,x0,ckpt", [
+    (4, 1, 1, 1, 1, 1, False, ()), (8, 2, 7, 2, 3, 40, True, (1, 40)), (100, 8, 25, 1, 1, 60, False, (7,)),
+    (1000, 3, 25, 1, 7, 300, False, (256,)), (3840, 3, 16, 3, 1, 30, True, ()), (3844, 3, 31, 1, 1, 30, False, (3, 4)),
+    (15_360, 2, 5, 1, 1, 12, False, (12,)), (260, 5, 128, 1, 1, 20, False, ()), (332, 6, 23, 1, 1, 513, False, ())])
+def test_newsvendor_constraints(n, m, S, M, R, T, x0, ckpt):
+    print(f"[one launch] constraints n={n} rows={m} S={S} M={M} R={R} T={T}", flush=True)
+    inst = workloads.newsvendor_instance(3, 0, n)
+    inst["sigma"][::7] = 0.0
+    A, C = workloads.newsvendor_constraints(3, 0, n, m)
+    start = np.full(n, 0.25 * float(np.min(C / A.sum(axis=1)))) if x0 else None
+
+    def run(ctx):
+        ctx.run_newsvendor_lp(inst, A, C, R, T, 5, S=S, M=M, x0=start, checkpoints=ckpt, gap_eps=1e3)
+
+    def records(ctx):
+        st = ctx.nv_lp_stats()
+        return dict(ctx.nv_lp_paths(), mean=st.mean, origin=st.decision_total[0], tau_count=st.tau_count)
+
+    a, b = both(run, records)
+    same(a, b)
+    assert a["pivots"].max() <= sim.NV_LP_MAX_PIVOTS
