@@ -163,6 +163,9 @@ int run_impl(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint64_t
              const RunInto *into = nullptr);
 int set_err(sim_ctx *ctx, int code, const char *fmt, ...);
 int ensure(sim_ctx *ctx, DevBuf &b, size_t bytes);
+// A buffer the run can do without: false when there is no room. ensure gives it back when another
+// buffer needs the room.
+bool ensure_spare(sim_ctx *ctx, DevBuf &b, size_t bytes);
 void free_buf(DevBuf &b);
 }  // namespace host
 }  // namespace fw

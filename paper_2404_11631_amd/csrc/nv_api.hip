@@ -290,7 +290,7 @@ int sim_run_newsvendor(sim_ctx *ctx, const sim_nv_params *p, uint64_t R, uint64_
         return rc;
     // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
     const bool one_launch = fw::nv_run_fits(w.nwg, static_cast<uint32_t>(R), p->n_samples, w.P, ctx->device) &&
-                            ensure(ctx, w.words, fw::nv_run_bytes(R, w.nwg, T)) == SIM_OK;
+                            ensure_spare(ctx, w.words, fw::nv_run_bytes(R, w.nwg, T));
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipMemcpyAsync(w.prod_f.ptr, pf.data(), sizeof(float) * pf.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.prod_d.ptr, pd.data(), sizeof(double) * pd.size(), hipMemcpyHostToDevice, st));
@@ -474,7 +474,7 @@ int sim_run_newsvendor_lp(sim_ctx *ctx, const sim_nv_params *p, const sim_nv_con
     w.T = T;
     // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
     const bool one_launch = fw::nv_lp_run_fits(A, ctx->device) &&
-                            ensure(ctx, w.words, fw::nv_lp_run_bytes(R, A.nq, A.nwg, T)) == SIM_OK;
+                            ensure_spare(ctx, w.words, fw::nv_lp_run_bytes(R, A.nq, A.nwg, T));
     if (int rc2 = nv_lp_enqueue(ctx, w, one_launch)) return rc2;
     w.have = true;
     return SIM_OK;

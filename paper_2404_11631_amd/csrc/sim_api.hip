@@ -25,10 +25,24 @@ int set_err(sim_ctx *ctx, int code, const char *fmt, ...)
     return code;
 }
 
+namespace {
+
+// Gives back the buffers a run can do without (hipFree waits for the launches that use them).
+void release_spare(sim_ctx *ctx)
+{
+    for (DevBuf *b : {&ctx->wide.words, &ctx->nv.words, &ctx->nvlp.words}) {
+        ctx->ws_used -= b->bytes;
+        free_buf(*b);
+    }
+}
+
+}  // namespace
+
 int ensure(sim_ctx *ctx, DevBuf &b, size_t bytes)
 {
     if (bytes == 0) bytes = 8;
     if (b.bytes >= bytes) return SIM_OK;
+    if (ctx->ws_limit && ctx->ws_used - b.bytes + bytes > ctx->ws_limit) release_spare(ctx);
     if (ctx->ws_limit && ctx->ws_used - b.bytes + bytes > ctx->ws_limit)
         return set_err(ctx, SIM_ENOMEM, "the context's workspace limit of %llu bytes cannot hold a buffer of %zu bytes "
                        "(%llu in use)", (unsigned long long)ctx->ws_limit, bytes, (unsigned long long)ctx->ws_used);
@@ -40,12 +54,33 @@ int ensure(sim_ctx *ctx, DevBuf &b, size_t bytes)
     }
     hipError_t e = hipMalloc(&b.ptr, bytes);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
+        release_spare(ctx);
+        e = hipMalloc(&b.ptr, bytes);
+    }
+    if (e != hipSuccess) {
         b.ptr = nullptr;
         return set_err(ctx, SIM_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
     }
     b.bytes = bytes;
     ctx->ws_used += bytes;
     return SIM_OK;
+}
+
+bool ensure_spare(sim_ctx *ctx, DevBuf &b, size_t bytes)
+{
+    if (b.bytes >= bytes) return true;
+    ctx->ws_used -= b.bytes;
+    free_buf(b);
+    if (ctx->ws_limit && ctx->ws_used + bytes > ctx->ws_limit) return false;
+    if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        b.ptr = nullptr;
+        return false;
+    }
+    b.bytes = bytes;
+    ctx->ws_used += bytes;
+    return true;
 }
 
 void free_buf(DevBuf &b)

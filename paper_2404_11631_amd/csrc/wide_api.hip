@@ -222,7 +222,7 @@ int sim_run_wide(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint
         return rc;
     // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
     const bool one_launch = !p->n_schedule && fw::wide_run_fits(w.nwg, static_cast<uint32_t>(R), N, ctx->device) &&
-                            ensure(ctx, w.words, fw::wide_run_bytes(R, w.nwg, N, T)) == SIM_OK;
+                            ensure_spare(ctx, w.words, fw::wide_run_bytes(R, w.nwg, N, T));
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipMemcpyAsync(w.asset_f.ptr, af.data(), sizeof(float) * af.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(ctx, hipMemcpyAsync(w.asset_d.ptr, ad.data(), sizeof(double) * ad.size(), hipMemcpyHostToDevice, st));

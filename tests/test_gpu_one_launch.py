@@ -52,6 +52,29 @@ def test_newsvendor(n, S, M, R, T, x0, ckpt):
     assert a["cnt"].sum() == R * T
 
 
+def test_exchange_slots_give_way():
+    # a context that the first run fills to its cap, slots included: the second run's records need
+    # the slots' room, which a context of that cap has
+    inst = workloads.newsvendor_instance(3, 0, 4000)
+
+    def two(ctx):
+        for T in (40, 400):
+            ctx.run_newsvendor(inst, 1, T, 5, S=16)
+        return ctx.nv_paths()
+
+    free, capped = sim.Sim(0), None
+    try:
+        free.run_newsvendor(inst, 1, 40, 5, S=16)
+        cap = free.workspace_bytes()
+        capped = sim.Sim(0, workspace_bytes=cap)
+        same(two(free), two(capped))
+        assert capped.workspace_bytes() <= cap
+    finally:
+        free.close()
+        if capped:
+            capped.close()
+
+
 @pytest.mark.parametrize("d,N,M,R,T,w0,ckpt", [
     (4, 2, 1, 1, 1, False, ()), (128, 15, 1, 1, 40, False, (1, 40)), (132, 16, 3, 3, 1030, True, (1024,)),
     (4096, 31, 1, 1, 30, False, (30,)), (4100, 32, 2, 2, 30, True, (7,)), (8192, 63, 1, 7, 20, False, ()),
