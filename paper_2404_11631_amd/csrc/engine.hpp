@@ -9,6 +9,7 @@
 #include "host_core.hpp"
 #include "mlp.hpp"
 #include "newsvendor.hpp"
+#include "sqn_split.hpp"
 #include "sim_types.hpp"
 
 namespace fw {
@@ -117,6 +118,9 @@ struct SqnState {
     DevBuf X, z, S, Y, wprev, acc, wsnap, wt, pairs, loss_part, fval, stats;
     DevBuf H, hscratch;                   // sim_sqn_hessian: the n x n matrix and its work space
     DevBuf sw, sg, sxpart, sdpart, shpart, sypart, ssmall;   // sim_run_sqn_split: iterate, gradient, partial sums, small matrices
+    DevBuf words;                         // its exchange slots, one launch (spare)
+    fw::SqnSplit split{};                 // the arguments of the last split run
+    bool unsettled = false;               // it ran in one launch and its failure word has not been read
     hipEvent_t ev0 = nullptr, ev1 = nullptr, ev2 = nullptr, ev3 = nullptr, ev4 = nullptr;
 };
 

@@ -833,6 +833,7 @@ __global__ void sqn_stats_kernel(SqnArgs A)
     }
     A.stats[n_streams * kStreamFields] = mn;
     A.stats[n_streams * kStreamFields + 1] = mx;
+    if (A.fail && *A.fail) A.stats[4] = -1.0;
 }
 
 int launch_sqn_run(const SqnArgs &A, hipStream_t s)

@@ -20,52 +20,21 @@
 
 #include "sqn.hpp"
 #include "sqn_device.hpp"
+#include "sqn_slice.hpp"
 #include "sqn_split.hpp"
 
 namespace fw {
 
 namespace {
 
-constexpr uint32_t kSliceWords = 8;                      // bitmap words of a slice's 256 features
 constexpr uint32_t kBitsCap = kSqnMaxB * kSliceWords;    // staged words: every row's slice
 constexpr uint32_t kInFlight = 8;                        // loads per thread per batch of a copy
 constexpr uint32_t kVecPerWave = 2 * kSqnMaxM / kSplitWaves;   // stored vectors a thread holds (16)
-constexpr uint32_t kPairPerWave = kSqnMaxM / kSplitWaves;      // stored pairs a thread holds (8)
 static_assert(kSqnMaxB >= static_cast<int>(SIM_SQN_MAX_B) && kSqnMaxM >= static_cast<int>(SIM_SQN_MAX_M) &&
                   kSqnMaxN >= SIM_SQN_MAX_N,
               "the LDS arrays hold the largest b, b_H, M and n that validation admits");
 static_assert(kSplitMaxSlices * kSplitQuads * 4 >= SIM_SQN_MAX_N, "slices cover every feature");
 static_assert(2 * kSqnMaxM <= kSplitQuads, "a thread per stored vector in the column sums");
-
-struct Slice {
-    uint32_t s, rep, tid, ql, wv;    // slice, replication, thread, quad within the slice, wavefront
-    uint32_t q, qc;                  // the quad, and the quad clamped into range (for loads)
-    bool own, owner;                 // q < nq; own and in the first wavefront (stores)
-};
-
-__device__ __forceinline__ Slice slice_of(const SqnSplit &P)
-{
-    Slice c;
-    c.s = blockIdx.x;
-    c.rep = blockIdx.y;
-    c.tid = threadIdx.x;
-    c.ql = c.tid % kSplitQuads;
-    c.wv = c.tid / kSplitQuads;
-    c.q = c.s * kSplitQuads + c.ql;
-    c.own = c.q < P.A.nq;
-    c.owner = c.own && c.wv == 0;
-    c.qc = c.own ? c.q : P.A.nq - 1;
-    return c;
-}
-
-// v's slice (zero past n) into sv[256], by the first wavefront
-__device__ __forceinline__ void stage_slice(const Slice &c, const double (&v)[4], double *sv)
-{
-    if (c.wv == 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sv[4 * c.ql + e] = c.own ? v[e] : 0.0;
-    }
-}
 
 // dst[0..count) = src[0..count), global to LDS, kInFlight loads per thread at a time. count >= 1.
 __device__ __forceinline__ void to_lds(const double *src, uint32_t count, double *dst)
@@ -139,43 +108,6 @@ __device__ __forceinline__ void slice_row_dots(const SqnSplit &P, const Slice &c
         for (uint32_t wd = 0; wd < kSliceWords; ++wd) a += word_dot(bits[i * kSliceWords + wd], sv, 32u * wd);
         out[static_cast<size_t>(i) * P.W + c.s] = a;
     }
-}
-
-// The sum over the rows of coef[i] times the quad's four bits: each wavefront sums a contiguous
-// quarter of the rows in order, then every thread adds the four quarters in order (part: LDS
-// [kSplitWaves][64][4]). Every thread of the workgroup must call it; it synchronises.
-__device__ __forceinline__ void slice_bit_sum(const Slice &c, const uint32_t *bits, const double *coef, uint32_t count,
-                                              double (*part)[kSplitQuads][4], double (&out)[4])
-{
-    const uint32_t per = (count + kSplitWaves - 1) / kSplitWaves;
-    const uint32_t i0 = min(count, c.wv * per), i1 = min(count, i0 + per);
-    const uint32_t wq = c.ql >> 3, sh = 4 * (c.ql & 7);
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-    for (uint32_t i = i0; i < i1; ++i) {
-        const uint32_t x = (bits[i * kSliceWords + wq] >> sh) & 0xFu;
-        const double r = coef[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if ((x >> e) & 1u) a[e] += r;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) part[c.wv][c.ql][e] = a[e];
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        double t = part[0][c.ql][e];
-        for (uint32_t u = 1; u < kSplitWaves; ++u) t += part[u][c.ql][e];
-        out[e] = t;
-    }
-}
-
-__device__ __forceinline__ double dot4(const double (&a)[4], const double (&b)[4])
-{
-    double p = 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) p += a[e] * b[e];
-    return p;
 }
 
 // Column sums of red[v][64] for v < count (the 64 quads' products, in order) into out[v W + s].

@@ -30,7 +30,7 @@ namespace {
 // Gives back the buffers a run can do without (hipFree waits for the launches that use them).
 void release_spare(sim_ctx *ctx)
 {
-    for (DevBuf *b : {&ctx->wide.words, &ctx->nv.words, &ctx->nvlp.words}) {
+    for (DevBuf *b : {&ctx->wide.words, &ctx->nv.words, &ctx->nvlp.words, &ctx->sqn.words}) {
         ctx->ws_used -= b->bytes;
         free_buf(*b);
     }
@@ -269,7 +269,8 @@ void sim_destroy(sim_ctx *ctx)
     for (hipEvent_t e : {nv.ev0, nv.ev1})
         if (e) (void)hipEventDestroy(e);
     SqnState &sq = ctx->sqn;
-    for (DevBuf *x : {&sq.X, &sq.z, &sq.S, &sq.Y, &sq.wprev, &sq.acc, &sq.wsnap, &sq.wt, &sq.H, &sq.hscratch, &sq.pairs, &sq.loss_part, &sq.fval, &sq.stats})
+    for (DevBuf *x : {&sq.X, &sq.z, &sq.S, &sq.Y, &sq.wprev, &sq.acc, &sq.wsnap, &sq.wt, &sq.H, &sq.hscratch, &sq.pairs, &sq.loss_part, &sq.fval, &sq.stats,
+                      &sq.sw, &sq.sg, &sq.sxpart, &sq.sdpart, &sq.shpart, &sq.sypart, &sq.ssmall, &sq.words})
         free_buf(*x);
     for (hipEvent_t e : {sq.ev0, sq.ev1, sq.ev2, sq.ev3, sq.ev4})
         if (e) (void)hipEventDestroy(e);

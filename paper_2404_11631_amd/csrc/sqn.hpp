@@ -45,7 +45,9 @@ struct SqnArgs {
     double *loss_part;                      // [n_ckpt + 1][R][nblk][2] double-double partial sums
     uint32_t nblk;                          // loss workgroups per snapshot
     double *fval;                           // [n_ckpt + 1][R] F at the checkpoints, then F(w^{K+1})
-    double *stats;                          // kMaxStreams x kStreamFields + 2
+    double *stats;                          // kMaxStreams x kStreamFields + 2; a first count of -1 after a
+                                            // cooperative run that gave up
+    const uint32_t *fail;                   // its failure word (NULL: launch by launch)
 };
 
 int launch_sqn_run(const SqnArgs &A, hipStream_t s);

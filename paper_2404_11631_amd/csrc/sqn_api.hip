@@ -90,7 +90,7 @@ static int sqn_prepare(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64
     if (!q.have_data) return set_err(ctx, SIM_ESTATE, "no data set loaded (sim_sqn_load)");
     if (int rc = validate_sqn(ctx->err, p, q.N, q.n, R, K)) return rc;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    q.have = false;
+    q.have = q.unsettled = false;
     for (hipEvent_t *e : {&q.ev0, &q.ev1, &q.ev2})
         if (!*e) HIP_TRY(ctx, hipEventCreate(e));
     const uint32_t nc = p->n_checkpoints;
@@ -178,6 +178,36 @@ int sim_run_sqn(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_t K, u
     return sqn_finish(ctx, p, A, R, K);
 }
 
+// The iterations of a split run, launch by launch.
+static int sqn_split_sequenced(sim_ctx *ctx, const fw::SqnSplit &P)
+{
+    const fw::SqnArgs &A = P.A;
+    const int lrc = fw::sqn_split_sequence(A.K, A.L, A.M, A.n_ckpt, A.ckpt,
+                                           [&](fw::SqnSplitKernel kind, const fw::SqnSplitStep &step) {
+                                               return fw::launch_sqn_split(P, kind, step, ctx->stream);
+                                           });
+    return lrc ? set_err(ctx, SIM_EDEVICE, "SQN split launch failed: %s", hipGetErrorString(hipGetLastError())) : SIM_OK;
+}
+
+// Waits for the last run. One in one launch whose wait gave up is run again launch by launch.
+static int sqn_settle(sim_ctx *ctx)
+{
+    SqnState &q = ctx->sqn;
+    HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    if (!q.unsettled) return SIM_OK;
+    double count = 0.0;
+    HIP_TRY(ctx, hipMemcpy(&count, static_cast<const double *>(q.stats.ptr) + 4, sizeof(count), hipMemcpyDeviceToHost));
+    q.unsettled = false;
+    if (count >= 0.0) return SIM_OK;
+    q.split.A.fail = nullptr;
+    HIP_TRY(ctx, hipEventRecord(q.ev0, ctx->stream));
+    if (int rc = sqn_split_sequenced(ctx, q.split)) return rc;
+    const sim_sqn_params p = q.params;
+    if (int rc = sqn_finish(ctx, &p, q.split.A, q.R, q.K)) return rc;
+    HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    return SIM_OK;
+}
+
 int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_t K, uint64_t seed)
 {
     if (!ctx) return SIM_EINVAL;
@@ -208,11 +238,26 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
     P.small = static_cast<double *>(q.ssmall.ptr);
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipEventRecord(q.ev0, st));
-    const int lrc = fw::sqn_split_sequence(K, A.L, A.M, A.n_ckpt, A.ckpt,
-                                           [&](fw::SqnSplitKernel kind, const fw::SqnSplitStep &step) {
-                                               return fw::launch_sqn_split(P, kind, step, st);
-                                           });
-    if (lrc) return set_err(ctx, SIM_EDEVICE, "SQN split launch failed: %s", hipGetErrorString(hipGetLastError()));
+    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
+    const size_t words = fw::sqn_split_run_bytes(A, P.W);
+    const bool one_launch = fw::sqn_split_run_fits(P, ctx->device) && ensure_spare(ctx, q.words, words);
+    if (one_launch) {
+        HIP_TRY(ctx, hipMemsetAsync(q.words.ptr, 0, words, st));
+        fw::SqnSplitRun Q{};
+        Q.words = static_cast<uint64_t *>(q.words.ptr);
+        Q.fail = reinterpret_cast<uint32_t *>(static_cast<char *>(q.words.ptr) + words - sizeof(uint64_t));
+        P.A.fail = Q.fail;
+        for (Q.k0 = 1; Q.k0 <= K; Q.k0 = Q.k1) {
+            Q.k1 = std::min(K + 1, Q.k0 + fw::kSqnRunSteps);
+            if (fw::launch_sqn_split_run(P, Q, st))
+                return set_err(ctx, SIM_EDEVICE, "SQN split launch failed: %s", hipGetErrorString(hipGetLastError()));
+        }
+        if (int rc2 = sqn_finish(ctx, p, P.A, R, K)) return rc2;
+        q.split = P;
+        q.unsettled = true;
+        return SIM_OK;
+    }
+    if (int rc2 = sqn_split_sequenced(ctx, P)) return rc2;
     return sqn_finish(ctx, p, A, R, K);
 }
 
@@ -222,7 +267,7 @@ int sim_sqn_stats(sim_ctx *ctx, sim_stats_out *out)
     SqnState &q = ctx->sqn;
     if (!q.have) return set_err(ctx, SIM_ESTATE, "no SQN run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    if (int rc = sqn_settle(ctx)) return rc;
     const uint32_t nc = q.params.n_checkpoints, n_streams = 1 + 2 * nc;
     double F[fw::kMaxStreams * fw::kStreamFields + 2];
     HIP_TRY(ctx, hipMemcpy(F, q.stats.ptr, sizeof(double) * (n_streams * fw::kStreamFields + 2), hipMemcpyDeviceToHost));
@@ -240,7 +285,7 @@ int sim_sqn_paths(sim_ctx *ctx, sim_sqn_view *out)
     SqnState &q = ctx->sqn;
     if (!q.have) return set_err(ctx, SIM_ESTATE, "no SQN run yet");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    if (int rc = sqn_settle(ctx)) return rc;
     std::memset(out, 0, sizeof(*out));
     const uint32_t nc = q.params.n_checkpoints;
     out->R = q.R;
@@ -269,7 +314,7 @@ int sim_sqn_hessian(sim_ctx *ctx, uint64_t rep, sim_sqn_hessian_view *out)
     if (!q.have) return set_err(ctx, SIM_ESTATE, "no SQN run yet");
     if (rep >= q.R) return set_err(ctx, SIM_EINVAL, "rep=%llu outside [0, %llu)", (unsigned long long)rep, (unsigned long long)q.R);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    if (int rc = sqn_settle(ctx)) return rc;
     uint32_t P = 0;
     HIP_TRY(ctx, hipMemcpy(&P, static_cast<const uint32_t *>(q.pairs.ptr) + rep, sizeof(uint32_t), hipMemcpyDeviceToHost));
     const uint32_t M = q.params.M;

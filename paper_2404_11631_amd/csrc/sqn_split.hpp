@@ -111,4 +111,46 @@ int sqn_split_sequence(uint64_t K, uint32_t L, uint32_t M, uint32_t n_ckpt, cons
 
 int launch_sqn_split(const SqnSplit &P, SqnSplitKernel kind, const SqnSplitStep &st, hipStream_t s);
 
+// ---- many iterations in one cooperative launch (fw_sqn_split_run.hip) -----------------------------
+// A run takes this form when the device holds its workgroups, one per compute unit, at once, and their
+// LDS. Faster at every such size. us per iteration, M = 25, L = 10, b = 50, b_H = 300, launch by launch ->
+// one launch: n = 50 20.2 -> 13.5, 300 21.7 -> 12.1, 1,000 20.6 -> 11.5, 5,000 20.6 -> 12.4, 8,192
+// 21.8 -> 13.0, 7 replications of n = 5,000 21.6 -> 12.4; b = 100, b_H = 600, n = 5,000 22.7 -> 15.9.
+constexpr uint64_t kSqnRunSteps = 4096;         // iterations per launch at most
+
+struct SqnSplitRun {
+    uint64_t k0, k1;                            // the iterations of this launch
+    uint64_t *words;                            // [R][slots], cleared before the run
+    uint32_t *fail;                             // raised by a wait that gave up; cleared before the run
+};
+
+// The exchange slots of a replication, in 64-bit words: a slice's block of n values is 2 pad(n) words,
+// the high halves and the low, on 64-byte lines of its own.
+struct SqnSplitSlots {
+    uint32_t bp, dp, hp, yp, cp;                // padded values of a block
+    size_t x, d, h, y, cx, ch, total;           // [2][W] rows; [W] S'g, Y'g; [W] Hessian rows; [W] new pair; coefficients
+};
+
+__host__ __device__ inline SqnSplitSlots sqn_split_slots(uint32_t M, uint32_t b, uint32_t bH, uint32_t W)
+{
+    SqnSplitSlots s{};
+    auto pad = [](uint32_t n) { return (n + 7) / 8 * 8; };
+    s.bp = pad(b), s.dp = pad(2 * M), s.hp = pad(2 * bH), s.yp = pad(3 * M), s.cp = pad(bH);
+    s.d = s.x + static_cast<size_t>(2 * W) * 2 * s.bp;
+    s.h = s.d + static_cast<size_t>(W) * 2 * s.dp;
+    s.y = s.h + static_cast<size_t>(W) * 2 * s.hp;
+    s.cx = s.y + static_cast<size_t>(W) * 2 * s.yp;
+    s.ch = s.cx + 2 * s.bp;
+    s.total = s.ch + 2 * s.cp;
+    return s;
+}
+
+inline size_t sqn_split_run_bytes(const SqnArgs &A, uint32_t W)
+{
+    return sizeof(uint64_t) * (A.R * sqn_split_slots(A.M, A.b, A.bH, W).total + 1);
+}
+
+bool sqn_split_run_fits(const SqnSplit &P, int device);
+int launch_sqn_split_run(const SqnSplit &P, const SqnSplitRun &Q, hipStream_t s);
+
 }  // namespace fw

@@ -99,6 +99,8 @@ inline uint64_t __builtin_amdgcn_ballot_w64(bool p)
     g_block->wave[threadIdx.x / 64]->arrive_and_wait();
     return m;
 }
+inline int __builtin_amdgcn_sbfe(int x, uint32_t at, uint32_t bits) { return static_cast<int>(static_cast<uint32_t>(x) << (32 - at - bits)) >> (32 - bits); }
+inline void __builtin_amdgcn_sched_barrier(int) {}
 inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return emu_exchange(v, threadIdx.x / 64 * 64); }
 inline uint32_t __builtin_amdgcn_readlane(uint32_t v, int lane) { return emu_exchange(v, threadIdx.x / 64 * 64 + lane); }
 // DPP: quad_perm (dpp_ctrl < 0x100), lane 4q + i reads lane 4q + ((ctrl >> 2i) & 3); row_mirror

@@ -117,3 +117,27 @@ def test_newsvendor_constraints(n, m, S, M, R, T, x0, ckpt):
     a, b = both(run, records)
     same(a, b)
     assert a["pivots"].max() <= sim.NV_LP_MAX_PIVOTS
+
+
+@pytest.mark.parametrize("n,rows,b,bH,M,L,R,K,fp32,ckpt", [
+    (1, 64, 1, 1, 1, 1, 1, 1, False, ()), (50, 400, 20, 30, 4, 3, 7, 40, False, (7, 22)), (256, 300, 64, 64, 5, 2, 1, 30, True, ()),
+    (260, 500, 65, 24, 32, 1, 2, 60, False, (5,)), (1000, 700, 300, 600, 25, 10, 1, 60, False, (41,)),
+    (5000, 900, 50, 300, 25, 10, 3, 300, False, (20, 300)), (8192, 600, 50, 301, 2, 3, 1, 20, False, ()),
+    (300, 500, 10, 12, 3, 2, 1, 4100, False, (4096, 4097))])
+def test_sqn_split(n, rows, b, bH, M, L, R, K, fp32, ckpt):
+    print(f"[one launch] sqn n={n} b={b} bH={bH} M={M} L={L} R={R} K={K} fp32={fp32}", flush=True)
+    rng = np.random.default_rng(3)
+    X = (rng.random((rows, n)) < min(0.5, 25.0 / n)).astype(np.uint8)
+    z = rng.integers(0, 2, rows).astype(np.uint8)
+
+    def run(ctx):
+        ctx.sqn_load(X, z)
+        ctx.run_sqn(R, K, 5, L=L, M=M, b=b, bH=bH, checkpoints=ckpt, pairs_fp32=fp32, split=True)
+
+    def records(ctx):
+        st = ctx.sqn_stats()
+        return dict(ctx.sqn_paths(), mean=st.mean)
+
+    a, b2 = both(run, records)
+    same(a, b2)
+    assert a["pairs"].tolist() == [max(K // L - 1, 0)] * R
