@@ -22,6 +22,8 @@
 //     the order in which tiles ran.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_reduce.hpp"
 #include "device_rng.hpp"
 #include "sim_types.hpp"
@@ -41,11 +43,26 @@ constexpr int kStageFloats = kBatchStageFloats;   // max over Pa of (64 / Pa) x 
 // rows of a tile's coefficient table in LDS (binary32, indexed by asset, zero past d)
 constexpr int kCoefSz = 0, kCoefC1 = 1, kCoefC2 = 2, kCoefMu = 3, kCoefW0 = 4, kCoefRows = 5;
 __device__ __forceinline__ uint32_t stage_stride(uint32_t Pa) { return 32u * Pa + (Pa == 4u ? 3u : 1u); }
+// A lane reads kLaneAssets floats of a sample also where it has fewer assets: up to 14 past its
+// sub-group's area (the neighbour's, or this pad), finite values that meet a zero coefficient.
+constexpr int kStagePad = 16;
 
-__device__ __forceinline__ float bfly_sum(float x, uint32_t lo, uint32_t hi)
+// x of this lane and of lane ^ M, added, by DPP moves and lane swaps
+template <int M>
+__device__ __forceinline__ float xor_sum(float x)
 {
-    for (uint32_t m = lo; m < hi; m <<= 1) x += __shfl_xor(x, m, kWave);
-    return x;
+    if constexpr (M == 1) return x + dpp_move<0xB1>(x);
+    if constexpr (M == 2) return x + dpp_move<0x4E>(x);
+    if constexpr (M == 4) return x + dpp_move<0x1B>(dpp_move<0x141>(x));   // 7 - i, then 3 - i within the quad
+    if constexpr (M == 8) return x + dpp_move<0x128>(x);                   // a 16-lane row rotated by 8
+    if constexpr (M == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
+    if constexpr (M == 32) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    }
 }
 
 __device__ __forceinline__ double bfly_sum(double x, uint32_t lo, uint32_t hi)
@@ -76,12 +93,13 @@ __device__ __forceinline__ void wave_lds_order()
 }
 
 // f(w) at w = c S over this lane's assets, FP64 (Eq. (3), diagonal Sigma), summed over the Pa lanes
-__device__ __forceinline__ double tile_objective(const InstanceDesc *__restrict__ P, const uint32_t (&S)[kLaneAssets],
+template <int K>
+__device__ __forceinline__ double tile_objective(const InstanceDesc *__restrict__ P, const uint32_t (&S)[K],
                                                  uint32_t hibits, uint32_t a0, uint32_t acnt, uint32_t Pa, double c)
 {
     double quad = 0.0, lin = 0.0;
 #pragma unroll
-    for (int k = 0; k < kLaneAssets; ++k) {
+    for (int k = 0; k < K; ++k) {
         if (static_cast<uint32_t>(k) < acnt) {
             const double sj = static_cast<double>(S[k]) + ((hibits >> k) & 1u ? 4294967296.0 : 0.0);
             const double w = sj * c;
@@ -95,11 +113,23 @@ __device__ __forceinline__ double tile_objective(const InstanceDesc *__restrict_
     return fma(P->lambda, quad, -lin);
 }
 
+// PA asset lanes; a lane holds up to K assets (kLaneAssets with several lanes). What bounds it is the
+// vector instructions issued (2.5e10 for 5.7e10 normals, of which the draws are about two thirds), and
+// for the longest tiles an iteration's serial chain. Hence K for narrow instances, no draw past the last
+// sample of a round, reads without a guard per asset, two samples side by side, the sums over lanes by
+// lane moves instead of the LDS crossbar, and the step scales 64 iterations at a time. 64 instances of
+// d 2..32, N 2..50, T to 10,000, 1,024 replications each: 61.5 -> 56.4 ms; a tile alone, us per
+// iteration: d = 13, N = 43 over 32 lanes 4.0 -> 3.2, d = 30, N = 39 over 16 lanes 8.4 -> 6.1, d = 7,
+// N = 39 on one lane 21.3 -> 14.9. Four wavefronts per SIMD instead of three (128 registers, 36 bytes
+// spilled) and wave priorities by length changed nothing; tiles ordered to even out the SIMDs' loads
+// gained 6 % here and lost 8 % elsewhere.
+template <int PA, int K>
 __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile, float *stage, float (*coef)[kBatchMaxD])
 {
     const InstanceDesc *P = B.inst + tile.inst;
     const uint32_t lane = threadIdx.x;
-    const uint32_t Pl = tile.P, Pa = tile.Pa;
+    constexpr uint32_t Pa = PA;
+    const uint32_t Pl = tile.P;
     const uint32_t g = lane / Pl;                  // replication within the tile
     const uint32_t ps = (lane % Pl) / Pa;          // sample chunk
     const uint32_t pa = lane % Pa;                 // asset slice
@@ -109,7 +139,7 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
     const uint32_t r = tile.rep0 + g;
     const uint32_t d = P->d;
     const uint32_t a0 = pa * kLaneAssets;
-    const uint32_t acnt = a0 < d ? (d - a0 < kLaneAssets ? d - a0 : kLaneAssets) : 0u;
+    const uint32_t acnt = a0 < d ? (d - a0 < K ? d - a0 : K) : 0u;
     const uint32_t N = P->N, M = P->M;
     const uint64_t T = P->T;
     const uint32_t k0 = static_cast<uint32_t>(P->seed), k1 = static_cast<uint32_t>(P->seed >> 32);
@@ -133,6 +163,7 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
         coef[kCoefMu][lane] = in ? P->mu_f[lane] : 0.0f;
         coef[kCoefW0][lane] = (in && has_w0) ? P->w0_f[lane] : 0.0f;
     }
+    for (uint32_t i = lane; i < kStageFloats + kStagePad; i += kWave) stage[i] = 0.0f;
     wave_lds_order();
 
     // G = 4/gcd(d,4) samples hold a whole number of Philox blocks; lane chunks start on such a
@@ -149,29 +180,37 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
     uint32_t Gr = (32u * Pa) / d / G * G;
     Gr = Gr < G ? G : Gr;
     Gr = Gr > chunk ? chunk : Gr;                  // chunk is a multiple of G
-    const uint32_t rounds = (chunk + Gr - 1) / Gr;
-    const uint32_t nb = Gr * d / 4;                // blocks per round
-    const uint32_t mb = (nb + Pa - 1) / Pa;        // blocks per lane per round (uniform)
+    // the samples of the longest chunk, and whether some lanes have fewer than it or none
+    const uint32_t longest = chunk < N ? chunk : N;
+    const bool ragged = Ps * chunk != N;
+    const uint32_t rounds = (longest + Gr - 1) / Gr;
     float *sub = stage + (lane / Pa) * stage_stride(Pa);   // this sub-group's staging area
 
-    uint32_t S[kLaneAssets], cnt[kLaneAssets];
+    uint32_t S[K], cnt[K];
 #pragma unroll
-    for (int k = 0; k < kLaneAssets; ++k) S[k] = cnt[k] = 0u;
+    for (int k = 0; k < K; ++k) S[k] = cnt[k] = 0u;
     uint32_t cnt0 = 0u, hibits = 0u;
     uint32_t tau = kTauNone;
     uint32_t ck = 0;
     uint64_t next_ckpt = n_ckpt ? P->ckpt[0] : 0;
     uint32_t epoch = 0, m_in_epoch = 0;
+    const bool narrow = T <= kMaxNarrowT;          // S stays below 2^32
+    float cw_lane = 0.0f;                          // lane i: the scale 2 / (t (t + 1)) of t = 64 floor(t / 64) + i
 
     for (uint64_t t = 0; t < T; ++t) {
-        const float cw = t == 0 ? 0.0f
-                                : static_cast<float>(2.0 / (static_cast<double>(t) * static_cast<double>(t + 1)));
+        const uint32_t tl = static_cast<uint32_t>(t) % kWave;
+        if (tl == 0) {
+            const uint64_t u = t + lane;
+            cw_lane = u == 0 ? 0.0f : static_cast<float>(2.0 / (static_cast<double>(u) * static_cast<double>(u + 1)));
+        }
+        const float cw = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cw_lane), tl));
         // past this lane's assets S = 0 and the coefficients are 0: w = v = 0 there, as required
-        float w[kLaneAssets], v[kLaneAssets], s1[kLaneAssets], s2[kLaneAssets];
+        float w[K], v[K], s1[K], s2[K];
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) {
+        for (int k = 0; k < K; ++k) {
             const float wk = (t == 0) ? coef[kCoefW0][a0 + k]
-                                      : (static_cast<float>(S[k]) + ((hibits >> k) & 1u ? 4294967296.0f : 0.0f)) * cw;
+                                      : narrow ? static_cast<float>(S[k]) * cw
+                                               : (static_cast<float>(S[k]) + ((hibits >> k) & 1u ? 4294967296.0f : 0.0f)) * cw;
             w[k] = wk;
             v[k] = coef[kCoefSz][a0 + k] * wk;
             s1[k] = 0.0f;
@@ -182,77 +221,108 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
         for (uint32_t rd = 0; rd < rounds; ++rd) {
             const uint32_t ib = i0 + rd * Gr;                // first sample of the round
             const uint32_t blk0 = ib * d / 4;                // its first Philox block
+            const uint32_t left = longest - rd * Gr, ns = left < Gr ? left : Gr;   // samples some chunk has here
+            const uint32_t nb = (ns * d + 3) / 4;            // their blocks
+            const uint32_t mb = (nb + Pa - 1) / Pa;          // a lane's
             // draw: blocks pa, pa + Pa, ... of the round, two at a time
-            for (uint32_t m = 0; m < mb; m += 2) {
+            auto put = [&](uint32_t b, const Block4<float> &q) {
+                if (Pa == 1 || b < nb) {
+                    sub[4 * b + 0] = q.z[0];
+                    sub[4 * b + 1] = q.z[1];
+                    sub[4 * b + 2] = q.z[2];
+                    sub[4 * b + 3] = q.z[3];
+                }
+            };
+            uint32_t m = 0;
+            for (; m + 2 <= mb; m += 2) {
                 const uint32_t b0 = pa + m * Pa, b1 = b0 + Pa;
                 const Block4<float> q0 = normals_block_row(row, blk0 + b0, dom, k0, k1);
                 const Block4<float> q1 = normals_block_row(row, blk0 + b1, dom, k0, k1);
-                if (b0 < nb) {
-                    sub[4 * b0 + 0] = q0.z[0];
-                    sub[4 * b0 + 1] = q0.z[1];
-                    sub[4 * b0 + 2] = q0.z[2];
-                    sub[4 * b0 + 3] = q0.z[3];
-                }
-                if (b1 < nb) {
-                    sub[4 * b1 + 0] = q1.z[0];
-                    sub[4 * b1 + 1] = q1.z[1];
-                    sub[4 * b1 + 2] = q1.z[2];
-                    sub[4 * b1 + 3] = q1.z[3];
-                }
+                put(b0, q0);
+                put(b1, q1);
+            }
+            if (m < mb) {
+                const uint32_t b0 = pa + m * Pa;
+                put(b0, normals_block_row(row, blk0 + b0, dom, k0, k1));
             }
             wave_lds_order();
-            for (uint32_t sidx = 0; sidx < Gr; ++sidx) {
-                const uint32_t i = ib + sidx;
-                const bool valid = i < i_end;
-                float z[kLaneAssets];
-                const float *src = sub + sidx * d + a0;
+            // NS samples from sidx on, their reads and dot products side by side
+            auto take = [&](auto n_samples, uint32_t sidx) {
+                constexpr int NS = decltype(n_samples)::value;
+                float z[NS][K], dot[NS];
 #pragma unroll
-                for (int k = 0; k < kLaneAssets; ++k) z[k] = static_cast<uint32_t>(k) < acnt ? src[k] : 0.0f;
+                for (int e = 0; e < NS; ++e) {
+                    const float *src = sub + (sidx + e) * d + a0;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) z[e][k] = src[k];
+                }
                 if (tnoise) {
-                    NormalCursor<float> ext;
-                    ext.seek(N * d + nu * i, epoch, r, dom, k0, k1);
-                    float ss = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < NS; ++e) {
+                        NormalCursor<float> ext;
+                        ext.seek(N * d + nu * (ib + sidx + e), epoch, r, dom, k0, k1);
+                        float ss = 0.0f;
 #pragma unroll 1
-                    for (uint32_t q = 0; q < nu; ++q) {
-                        const float e = ext.next(epoch, r, dom, k0, k1);
-                        ss = fmaf(e, e, ss);
-                    }
-                    const float a = tscale * __builtin_amdgcn_rsqf(ss);
+                        for (uint32_t q = 0; q < nu; ++q) {
+                            const float x = ext.next(epoch, r, dom, k0, k1);
+                            ss = fmaf(x, x, ss);
+                        }
+                        const float a = tscale * __builtin_amdgcn_rsqf(ss);
 #pragma unroll
-                    for (int k = 0; k < kLaneAssets; ++k) z[k] *= a;
-                }
-                float dot = 0.0f;
-#pragma unroll
-                for (int k = 0; k < kLaneAssets; ++k) dot = fmaf(z[k], v[k], dot);
-                dot = quad_group_sum(dot, Pa);
-                if (valid) {
-#pragma unroll
-                    for (int k = 0; k < kLaneAssets; ++k) {
-                        s1[k] += z[k];
-                        s2[k] = fmaf(z[k], dot, s2[k]);
+                        for (int k = 0; k < K; ++k) z[e][k] *= a;
                     }
                 }
-            }
+#pragma unroll
+                for (int e = 0; e < NS; ++e) {
+                    dot[e] = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) dot[e] = fmaf(z[e][k], v[k], dot[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < NS; ++e) dot[e] = quad_group_sum(dot[e], Pa);
+#pragma unroll
+                for (int e = 0; e < NS; ++e) {
+                    if (!ragged || ib + sidx + e < i_end) {
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            s1[k] += z[e][k];
+                            s2[k] = fmaf(z[e][k], dot[e], s2[k]);
+                        }
+                    }
+                }
+            };
+            uint32_t sidx = 0;
+            for (; sidx + 2 <= ns; sidx += 2) take(std::integral_constant<int, 2>{}, sidx);
+            if (sidx < ns) take(std::integral_constant<int, 1>{}, sidx);
             wave_lds_order();
         }
         // combine the Ps sample chunks (lanes holding the same assets)
-        for (uint32_t m = Pa; m < Pl; m <<= 1) {
+        auto combine = [&](auto lanes) {
+            constexpr int M = decltype(lanes)::value;
+            if (M >= PA && static_cast<uint32_t>(M) < Pl) {
 #pragma unroll
-            for (int k = 0; k < kLaneAssets; ++k) {
-                s1[k] += __shfl_xor(s1[k], m, kWave);
-                s2[k] += __shfl_xor(s2[k], m, kWave);
+                for (int k = 0; k < K; ++k) {
+                    s1[k] = xor_sum<M>(s1[k]);
+                    s2[k] = xor_sum<M>(s2[k]);
+                }
             }
-        }
+        };
+        combine(std::integral_constant<int, 1>{});
+        combine(std::integral_constant<int, 2>{});
+        combine(std::integral_constant<int, 4>{});
+        combine(std::integral_constant<int, 8>{});
+        combine(std::integral_constant<int, 16>{});
+        combine(std::integral_constant<int, 32>{});
 
         // gradient, linear subproblem over the vertices of W, Frank-Wolfe gap
         float dot1 = 0.0f;
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) dot1 = fmaf(s1[k], v[k], dot1);
-        dot1 = bfly_sum(dot1, 1u, Pa);
+        for (int k = 0; k < K; ++k) dot1 = fmaf(s1[k], v[k], dot1);
+        dot1 = quad_group_sum(dot1, Pa);
         const float qn = dot1 * inv_n;
-        float c1[kLaneAssets], c2[kLaneAssets], mu[kLaneAssets];
+        float c1[K], c2[K], mu[K];
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) {
+        for (int k = 0; k < K; ++k) {
             c1[k] = coef[kCoefC1][a0 + k];
             c2[k] = coef[kCoefC2][a0 + k];
             mu[k] = coef[kCoefMu][a0 + k];
@@ -260,7 +330,7 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
         float gmin = INFINITY, gw = 0.0f;
         uint32_t jmin = 0xFFFFFFFFu;
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) {
+        for (int k = 0; k < K; ++k) {
             if (static_cast<uint32_t>(k) < acnt) {
                 const uint32_t j = a0 + k;
                 const float gj = fmaf(-c1[k], s1[k], fmaf(c2[k], fmaf(-s1[k], qn, s2[k]), -mu[k]));
@@ -271,15 +341,15 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
                 gw = fmaf(gj, w[k], gw);
             }
         }
-        for (uint32_t m = 1; m < Pa; m <<= 1) {
-            const float og = __shfl_xor(gmin, m, kWave);
-            const uint32_t oj = __shfl_xor(jmin, m, kWave);
+        auto smaller = [&](float og, uint32_t oj) {
             if (og < gmin || (og == gmin && oj < jmin)) {
                 gmin = og;
                 jmin = oj;
             }
-        }
-        gw = bfly_sum(gw, 1u, Pa);
+        };
+        if (Pa >= 2) smaller(dpp_move<0xB1>(gmin), dpp_move<0xB1>(jmin));
+        if (Pa >= 4) smaller(dpp_move<0x4E>(gmin), dpp_move<0x4E>(jmin));
+        gw = quad_group_sum(gw, Pa);
         const uint32_t a = (gmin < 0.0f) ? jmin + 1 : 0u;
         const float gap = gw - (gmin < 0.0f ? gmin : 0.0f);
         if (tau == kTauNone && gap <= gap_eps) tau = static_cast<uint32_t>(t);
@@ -288,10 +358,10 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
         // step 2/(t+2): the signature absorbs the update
         cnt0 += (a == 0u) ? 1u : 0u;
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) {
+        for (int k = 0; k < K; ++k) {
             if (a == a0 + k + 1) {
                 const uint32_t now = S[k] + static_cast<uint32_t>(t + 1);
-                if (now < S[k]) hibits |= 1u << k;
+                if (!narrow && now < S[k]) hibits |= 1u << k;
                 S[k] = now;
                 cnt[k] += 1u;
             }
@@ -318,7 +388,7 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
             B.cnt[P->cnt_base + r] = cnt0;
         }
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k) {
+        for (int k = 0; k < K; ++k) {
             if (static_cast<uint32_t>(k) < acnt) {
                 const uint64_t j = a0 + k;
                 B.cnt[P->cnt_base + (j + 1) * R + r] = cnt[k];
@@ -377,7 +447,7 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
     for (uint32_t j = 0; j < static_cast<uint32_t>(kBatchMaxD); ++j) {
         uint32_t c = 0u;
 #pragma unroll
-        for (int k = 0; k < kLaneAssets; ++k)
+        for (int k = 0; k < K; ++k)
             if (a0 + k == j) c = cnt[k];
         const uint64_t tot = wave_sum_u64((owner && j < d) ? c : 0u);
         if (lane == 0) out.dec[j + 1] = tot;
@@ -585,10 +655,16 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
 // One wavefront per tile, every tile of the batch, longest first.
 __global__ __launch_bounds__(kWave) void fw_tile_kernel(BatchBuffers B)
 {
-    __shared__ float stage[kStageFloats];
+    __shared__ float stage[kStageFloats + kStagePad];
     __shared__ float coef[kCoefRows][kBatchMaxD];
     const Tile tile = B.tiles[blockIdx.x];
-    run_tile(B, tile, stage, coef);
+    const uint32_t d = B.inst[tile.inst].d;
+    if (tile.Pa == 4) run_tile<4, kLaneAssets>(B, tile, stage, coef);
+    else if (tile.Pa == 2) run_tile<2, kLaneAssets>(B, tile, stage, coef);
+    else if (d > 6) run_tile<1, 8>(B, tile, stage, coef);
+    else if (d > 4) run_tile<1, 6>(B, tile, stage, coef);
+    else if (d > 2) run_tile<1, 4>(B, tile, stage, coef);
+    else run_tile<1, 2>(B, tile, stage, coef);
 }
 
 // One replication per workgroup of two wavefronts (the iteration, the next epoch's normals), every

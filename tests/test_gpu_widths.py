@@ -53,3 +53,25 @@ def test_features_same_paths(ctx, d, N):
     b = ctx.paths()
     for f in ("y", "f_ckpt", "cnt", "wsum", "tau"):
         assert np.array_equal(a[f], b[f]), f
+
+
+@pytest.mark.parametrize("split,N,noise", [(1, 5, sim.NOISE_GAUSS), (1, 9, sim.NOISE_T), (2, 6, sim.NOISE_GAUSS), (4, 13, sim.NOISE_GAUSS),
+                                           (8, 3, sim.NOISE_GAUSS), (8, 40, sim.NOISE_T), (16, 33, sim.NOISE_GAUSS)])
+def test_tile_widths(ctx, split, N, noise):
+    # every width at `split` sample lanes: last rounds shorter than the others, an odd number of blocks,
+    # chunks without samples
+    probs, P = [], []
+    for d in range(1, 33):
+        mu, sigma = workloads.diag_instance(13, d, d)
+        probs.append(sim.Problem(mu=mu, sigma=sigma, N=N, M=1 + d % 2, noise=noise, nu=3, checkpoints=(5, 70), gap_eps=0.05,
+                                 instance_id=d, log_reps=(0, 3)))
+        P.append(min(64, split * (1 if d <= 8 else 2 if d <= 16 else 4)))
+    print(f"[widths] tiles split={split} N={N} noise={noise}", flush=True)
+    ctx.run_batch(probs, [3] * 32, [70] * 32, 9, lanes_per_rep=P, keep_paths=True)
+    for i, p in enumerate(probs):
+        st, g = ctx.batch_stats(i), ctx.batch_paths(i)
+        op = parity.oracle_problem(p, 9)
+        for r in range(3):
+            parity.check_rep(op, g, r, 70, oracle.U32, decisions=g["decisions"][:, r])
+        assert list(st.decision_total)[:len(p.mu) + 1] == g["cnt"].sum(axis=1).tolist()
+        assert st.mean == pytest.approx(g["y"].mean(), rel=1e-12) and st.R == 3
