@@ -50,18 +50,6 @@ __device__ __forceinline__ void failure_raise(uint32_t *fail)
     __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A value as an unsigned key in the order of the values (negative ones below positive).
-__device__ __forceinline__ uint32_t value_key(float x)
-{
-    const uint32_t b = __float_as_uint(x);
-    return b ^ (static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u);
-}
-
-__device__ __forceinline__ float key_value(uint32_t k)
-{
-    return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k);
-}
-
 // The smallest key over the wavefront and the lowest index among the lanes that hold it; with SORTED
 // the lanes' indices ascend and the first such lane has it.
 template <bool SORTED>

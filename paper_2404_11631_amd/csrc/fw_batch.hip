@@ -33,6 +33,10 @@ namespace fw {
 
 constexpr int kWave = 64;
 constexpr int kBatchMaxD = 32;
+// Workgroups up to which fw_wave_kernel has three drawing wavefronts: two of four wavefronts per compute
+// unit. At 1,024 the fourth wavefronts wait for a place (d = 4, N = 250 5.4 -> 10.1 us per iteration).
+constexpr uint32_t kWaveManyDrawers = 512;
+constexpr uint32_t kWaveMaxThreads = 256;      // fw_wave_kernel: up to three drawing wavefronts
 constexpr int kLaneAssets = 8;                 // assets held by one lane
 // LDS staging of one wavefront: a sub-group of Pa lanes draws G d <= 4 d <= 32 Pa normals per
 // round, and a wavefront has 64 / Pa sub-groups. Sub-group areas are 32 Pa + 1 floats apart (131 at
@@ -465,7 +469,14 @@ __device__ __forceinline__ void run_tile(const BatchBuffers &B, const Tile tile,
 // swap (wave_dpp.hpp); the FP64 sum keeps the shuffle butterfly (checkpoints only).
 __device__ __forceinline__ float half_sum32(float x) { return dpp_sum32(x); }
 
-__device__ __forceinline__ void half_argmin32(float &g, uint32_t &j) { dpp_argmin32(g, j); }
+// The smallest of the first half wavefront's values and its lane, lowest among equal ones. Ordered as
+// keys, so -0.0 comes before 0.0; a decision only takes a negative minimum.
+__device__ __forceinline__ void first_argmin32(float &g, uint32_t &j)
+{
+    const uint32_t key = value_key(g), m = __builtin_amdgcn_readfirstlane(dpp_min32(key));
+    j = static_cast<uint32_t>(__builtin_ctzll(__builtin_amdgcn_ballot_w64(key == m) | (1ull << 32)));
+    g = key_value(m);
+}
 
 __device__ __forceinline__ double half_sum32(double x)
 {
@@ -479,18 +490,25 @@ __device__ __forceinline__ double half_sum32(double x)
 // Lane i forms sample i's dot product with v = sz .* w, lane j the sums over the samples of z_ij
 // and z_ij (z_i'v); the gradient, its minimum (lowest index among equal values) and g'w are reduced
 // over the first half wavefront. Same formulas as the tile kernel, summed in a different order.
-// A second wavefront of the workgroup draws the next epoch's N d normals (a Philox block per lane
-// at a time) into the other of two LDS buffers while the first runs the iteration on the current
-// one; one workgroup barrier per iteration hands the buffers over. The normals do not depend on
-// the iterate, so the draw leaves the iteration's dependent chain.
-__device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile, float *zs, float *vs, float *dots)
+// The workgroup's other wavefronts draw the normals two epochs ahead (a Philox block per lane at a time)
+// into the third of three LDS buffers; one workgroup barrier per epoch hands the buffers over. The
+// normals do not depend on the iterate, so the draw leaves the iteration's dependent chain.
+//
+// The chain is what bounds it (1,024 replications are a wavefront per SIMD). With up to DR assets and NC
+// samples a lane takes its sample's row and its asset's column into registers while the previous
+// iteration's reductions run, and v_j and the dot products reach the other lanes as scalars: no LDS round
+// trip is left in the chain. DR = 0: both go through LDS (more than 32 samples). us per iteration at
+// 1,024 replications: d = N = 10 1.15 -> 0.98, d = 17, N = 30 1.62 -> 1.44; at 52, d = 23, N = 15 1.61 ->
+// 1.07. Registers for 64 samples cost more in guards than the LDS they save (d = 8, N = 60 1.9 -> 7.8).
+template <int DR, int NC>
+__device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile, float *zs, uint32_t stage, float *vs, float *dots)
 {
     const InstanceDesc *P = B.inst + tile.inst;
     const uint32_t lane = threadIdx.x % kWave;
-    const bool drawer = threadIdx.x >= kWave;          // the second wavefront: the next epoch's normals
+    const bool drawer = threadIdx.x >= kWave;          // the other wavefronts: the normals of the next epochs
     const uint32_t r = tile.rep0;
     const uint32_t d = P->d, N = P->N, M = P->M, nd = N * d, nb = (nd + 3) / 4;
-    const uint64_t T = P->T;
+    const uint32_t T = static_cast<uint32_t>(P->T);    // at most kMaxBatchT
     const uint32_t k0 = static_cast<uint32_t>(P->seed), k1 = static_cast<uint32_t>(P->seed >> 32);
     const uint32_t dom = P->instance & 0xFFFFFFu;
     const uint32_t n_ckpt = P->n_ckpt;
@@ -505,8 +523,9 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
 
     uint32_t S = 0u, cnt = 0u, cnt0 = 0u, hib = 0u;
     uint32_t tau = kTauNone, ck = 0, epoch = 0, m_in_epoch = 0;
-    uint64_t next_ckpt = n_ckpt ? P->ckpt[0] : 0;
-    float cw = 0.0f;   // w_t = cw S for t >= 1
+    uint32_t next_ckpt = n_ckpt ? static_cast<uint32_t>(P->ckpt[0]) : 0;
+    const bool narrow = T <= kMaxNarrowT;              // S stays below 2^32
+    float cw_lane = 0.0f;                              // lane i: the scale of w_t = cw S at t = 64 floor(t / 64) + i
     // f(w) at w = c S, FP64 (Eq. (3), diagonal Sigma), summed over the assets' lanes
     auto objective = [&](double c) {
         const double w = (static_cast<double>(S) + (hib ? 4294967296.0 : 0.0)) * c;
@@ -516,10 +535,10 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
         return fma(lambda, quad, -lin);
     };
 
-    // the normals of epoch e into buffer e mod 2, blocks b = first, first + stride, ...
-    auto draw = [&](uint32_t e, uint32_t first, uint32_t stride) {
+    // the normals of epoch e into its buffer (e mod 3), blocks b = first, first + stride, ...
+    float *const buf[3] = {zs, zs + stage, zs + 2 * stage};
+    auto draw = [&](uint32_t e, float *dst, uint32_t first, uint32_t stride) {
         const PhiloxRow row = philox_row(e, r, k0);
-        float *dst = zs + (e & 1u) * kStageFloats;
         for (uint32_t b = first; b < nb; b += stride) {
             const Block4<float> q = normals_block_row(row, b, dom, k0, k1);
             dst[4 * b + 0] = q.z[0];
@@ -528,59 +547,101 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
             dst[4 * b + 3] = q.z[3];
         }
     };
-    draw(0u, threadIdx.x, 2 * kWave);
+    float *z_now = buf[0], *z_next = buf[1], *z_draw = buf[2];      // epoch, epoch + 1, epoch + 2
+    draw(0u, z_now, threadIdx.x, blockDim.x);
+    if (M < T) draw(1u, z_next, threadIdx.x, blockDim.x);
     __syncthreads();
 
-    for (uint64_t t = 0; t < T; ++t) {
+    // sample min(lane, N - 1)'s row, which past d meets zeros of v, and this asset's column, zero past N;
+    // what is read past the sample or the buffer is finite (the kernel clears the LDS)
+    float row[DR ? DR : 1], col[NC ? NC : 1];
+    auto take = [&](const float *zc) {
+        const float *zr = zc + min(lane, N - 1) * d, *za = zc + jc;
+#pragma unroll
+        for (int j = 0; j < DR; ++j) row[j] = zr[j];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) col[i] = za[i * d];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) col[i] = static_cast<uint32_t>(i) < N ? col[i] : 0.0f;
+    };
+    auto scalar = [](float x, int from) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), from)); };
+    if (!drawer) take(z_now);
+
+    for (uint32_t t = 0; t < T; ++t) {
+        const bool ends = m_in_epoch + 1 == M;          // the epoch's last iteration
         if (drawer) {
-            // epoch + 1 goes to the buffer the iteration does not read; it was last read before the
-            // previous barrier
-            if (m_in_epoch + 1 == M && t + 1 < T) draw(epoch + 1, lane, kWave);
+            // epoch + 2 goes to the buffer that was last read before the previous barrier
+            if (ends && (static_cast<uint64_t>(epoch) + 2) * M < T)
+                draw(epoch + 2, z_draw, threadIdx.x - kWave, blockDim.x - kWave);
         } else {
-            const float *zc = zs + (epoch & 1u) * kStageFloats;
-            const float w = (t == 0) ? w0 : (static_cast<float>(S) + (hib ? 4294967296.0f : 0.0f)) * cw;
+            // the scale 2/(t (t+1)): an FP64 division every 64 iterations instead of one in each one's chain
+            const uint32_t tl = t % kWave;
+            if (tl == 0) {
+                const uint32_t u = t + lane;
+                cw_lane = u == 0 ? 0.0f : static_cast<float>(2.0 / (static_cast<double>(u) * (static_cast<double>(u) + 1.0)));
+            }
+            const float cw = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cw_lane), tl));
+            const float w = (t == 0) ? w0
+                            : narrow ? static_cast<float>(S) * cw
+                                     : (static_cast<float>(S) + (hib ? 4294967296.0f : 0.0f)) * cw;
             const float v = sz * w;
-            if (lane < 32) vs[lane] = v;
-            wave_lds_order();
-            for (uint32_t i = lane; i < N; i += kWave) {
-                float dot = 0.0f;
-#pragma unroll 8
-                for (uint32_t j = 0; j < d; ++j) dot = fmaf(zc[i * d + j], vs[j], dot);
-                dots[i] = dot;
-            }
-            wave_lds_order();
             float s1 = 0.0f, s2 = 0.0f;
-            if (in) {
+            if constexpr (DR > 0) {
+                float dot = 0.0f;
+#pragma unroll
+                for (int j = 0; j < DR; j += 8)
+                    if (j == 0 || static_cast<uint32_t>(j) < d) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) dot = fmaf(row[j + e], scalar(v, j + e), dot);
+                    }
+#pragma unroll
+                for (int i = 0; i < NC; i += 8)
+                    if (i == 0 || static_cast<uint32_t>(i) < N) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            s1 += col[i + e];
+                            s2 = fmaf(col[i + e], scalar(dot, i + e), s2);
+                        }
+                    }
+                if (!in) s1 = s2 = 0.0f;
+                if (ends && t + 1 < T) take(z_next);
+            } else {
+                if (lane < 32) vs[lane] = v;
+                wave_lds_order();
+                for (uint32_t i = lane; i < N; i += kWave) {
+                    float dot = 0.0f;
 #pragma unroll 8
-                for (uint32_t i = 0; i < N; ++i) {
-                    const float z = zc[i * d + lane];
-                    s1 += z;
-                    s2 = fmaf(z, dots[i], s2);
+                    for (uint32_t j = 0; j < d; ++j) dot = fmaf(z_now[i * d + j], vs[j], dot);
+                    dots[i] = dot;
                 }
+                wave_lds_order();
+                if (in) {
+#pragma unroll 8
+                    for (uint32_t i = 0; i < N; ++i) {
+                        const float z = z_now[i * d + lane];
+                        s1 += z;
+                        s2 = fmaf(z, dots[i], s2);
+                    }
+                }
+                wave_lds_order();                           // vs and dots are rewritten next iteration
             }
-            wave_lds_order();                               // vs and dots are rewritten next iteration
-            // the next iteration's scale 2/((t+1)(t+2)), its FP64 division beside the reductions
-            // rather than at the head of the next iteration's chain
-            const float cw_next =
-                static_cast<float>(2.0 / (static_cast<double>(t + 1) * static_cast<double>(t + 2)));
             const float qn = half_sum32(s1 * v) * inv_n;
             float g = INFINITY;
             uint32_t jg = 0xFFFFFFFFu;
-            if (in) {
-                g = fmaf(-c1, s1, fmaf(c2, fmaf(-s1, qn, s2), -mu));
-                jg = lane;
-            }
-            const float gw = half_sum32(in ? g * w : 0.0f);
-            half_argmin32(g, jg);
+            if (in) g = fmaf(-c1, s1, fmaf(c2, fmaf(-s1, qn, s2), -mu));
+            const float g_lane = in ? g * w : 0.0f;
+            first_argmin32(g, jg);
             const uint32_t a = (g < 0.0f) ? jg + 1 : 0u;
-            const float gap = gw - (g < 0.0f ? g : 0.0f);
-            if (tau == kTauNone && gap <= gap_eps) tau = static_cast<uint32_t>(t);
-            if (logged) B.dlog[log_at + t * log_count] = static_cast<uint8_t>(a);
+            if (__builtin_amdgcn_readfirstlane(tau) == kTauNone) {
+                const float gap = half_sum32(g_lane) - (g < 0.0f ? g : 0.0f);
+                if (gap <= gap_eps) tau = t;
+            }
+            if (logged) B.dlog[log_at + static_cast<uint64_t>(t) * log_count] = static_cast<uint8_t>(a);
             // step 2/(t+2): the signature absorbs the update
             cnt0 += (a == 0u) ? 1u : 0u;
             if (a == lane + 1) {
-                const uint32_t now = S + static_cast<uint32_t>(t + 1);
-                if (now < S) hib = 1u;
+                const uint32_t now = S + t + 1;
+                if (!narrow && now < S) hib = 1u;
                 S = now;
                 cnt += 1u;
             }
@@ -588,12 +649,16 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
                 const double f = objective(2.0 / (static_cast<double>(t + 1) * static_cast<double>(t + 2)));
                 if (lane == 0) B.fck[static_cast<uint64_t>(ck) * B.total_R + P->path_base + r] = f;
                 ++ck;
-                next_ckpt = ck < n_ckpt ? P->ckpt[ck] : 0;
+                next_ckpt = ck < n_ckpt ? static_cast<uint32_t>(P->ckpt[ck]) : 0;
             }
-            cw = cw_next;
         }
-        __syncthreads();   // both wavefronts: the drawn buffer is complete and the read one is free
-        if (++m_in_epoch == M) {
+        ++m_in_epoch;
+        if (ends) {
+            __syncthreads();   // all wavefronts: the drawn buffer is complete and the oldest is free
+            float *const z = z_now;
+            z_now = z_next;
+            z_next = z_draw;
+            z_draw = z;
             m_in_epoch = 0;
             ++epoch;
         }
@@ -667,15 +732,25 @@ __global__ __launch_bounds__(kWave) void fw_tile_kernel(BatchBuffers B)
     else run_tile<1, 2>(B, tile, stage, coef);
 }
 
-// One replication per workgroup of two wavefronts (the iteration, the next epoch's normals), every
-// tile of a batch that qualifies (BatchBuffers.wave_mode).
-__global__ __launch_bounds__(2 * kWave) void fw_wave_kernel(BatchBuffers B)
+// Floats of its LDS: `dots` for every sample, or what a lane reads past the last buffer.
+__host__ __device__ inline uint32_t wave_lds(uint32_t stage) { return 3 * stage + 32 + (stage > 32 * 33 ? stage : 32 * 33); }
+
+// One replication per workgroup (a wavefront for the iteration, the others for the next epochs'
+// normals), every tile of a batch that qualifies (BatchBuffers.wave_mode).
+__global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_kernel(BatchBuffers B)
 {
-    __shared__ float zs[2 * kStageFloats];
-    __shared__ float vs[32];
-    __shared__ float dots[kStageFloats];
+    HIP_DYNAMIC_SHARED(float, zs)                      // three buffers of the largest N d, vs, dots (wave_lds)
+    const uint32_t stage = B.wave_stage ? B.wave_stage : static_cast<uint32_t>(kStageFloats);
+    float *vs = zs + 3 * stage, *dots = vs + 32;
+    for (uint32_t i = threadIdx.x; i < wave_lds(stage); i += blockDim.x) zs[i] = 0.0f;
+    __syncthreads();
     const Tile tile = B.tiles[blockIdx.x];
-    run_wave(B, tile, zs, vs, dots);
+    const uint32_t d = B.inst[tile.inst].d, N = B.inst[tile.inst].N;
+    if (d <= 16 && N <= 16) run_wave<16, 16>(B, tile, zs, stage, vs, dots);
+    else if (d <= 16 && N <= 32) run_wave<16, 32>(B, tile, zs, stage, vs, dots);
+    else if (N <= 16) run_wave<32, 16>(B, tile, zs, stage, vs, dots);
+    else if (N <= 32) run_wave<32, 32>(B, tile, zs, stage, vs, dots);
+    else run_wave<0, 0>(B, tile, zs, stage, vs, dots);
 }
 
 // One workgroup per instance: its tile slots in order.
@@ -734,7 +809,12 @@ __global__ __launch_bounds__(kBlock) void fw_batch_reduce(BatchBuffers B)
 int launch_fw_batch(const BatchBuffers &B, hipStream_t stream)
 {
     if (B.n_tiles) {
-        if (B.wave_mode) hipLaunchKernelGGL(fw_wave_kernel, dim3(B.n_tiles), dim3(2 * kWave), 0, stream, B);
+        if (B.wave_mode) {
+            // a drawing wavefront draws 256 normals a pass: more of them from the second pass on, where the
+            // device still holds every workgroup at once
+            const uint32_t threads = B.wave_stage > 256 && B.n_tiles <= kWaveManyDrawers ? kWaveMaxThreads : 2 * kWave;
+            hipLaunchKernelGGL(fw_wave_kernel, dim3(B.n_tiles), dim3(threads), sizeof(float) * wave_lds(B.wave_stage), stream, B);
+        }
         else hipLaunchKernelGGL(fw_tile_kernel, dim3(B.n_tiles), dim3(kWave), 0, stream, B);
     }
     hipLaunchKernelGGL(fw_batch_reduce, dim3(B.n_inst), dim3(kBlock), 0, stream, B);

@@ -110,6 +110,18 @@ __device__ __forceinline__ uint32_t dpp_min64(uint32_t x)
     return min(w[0], w[1]);
 }
 
+// A value as an unsigned key in the order of the values (negative ones below positive).
+__device__ __forceinline__ uint32_t value_key(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    return b ^ (static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u);
+}
+
+__device__ __forceinline__ float key_value(uint32_t k)
+{
+    return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k);
+}
+
 __device__ __forceinline__ void argmin_take(float &g, uint32_t &j, float og, uint32_t oj)
 {
     if (og < g || (og == g && oj < j)) {

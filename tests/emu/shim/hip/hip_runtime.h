@@ -100,6 +100,9 @@ inline uint64_t __builtin_amdgcn_ballot_w64(bool p)
     return m;
 }
 inline int __builtin_amdgcn_sbfe(int x, uint32_t at, uint32_t bits) { return static_cast<int>(static_cast<uint32_t>(x) << (32 - at - bits)) >> (32 - bits); }
+#ifndef HIP_DYNAMIC_SHARED
+#define HIP_DYNAMIC_SHARED(type, var) static type var[1 << 14];
+#endif
 inline void __builtin_amdgcn_sched_barrier(int) {}
 inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return emu_exchange(v, threadIdx.x / 64 * 64); }
 inline uint32_t __builtin_amdgcn_readlane(uint32_t v, int lane) { return emu_exchange(v, threadIdx.x / 64 * 64 + lane); }

@@ -75,3 +75,19 @@ def test_tile_widths(ctx, split, N, noise):
             parity.check_rep(op, g, r, 70, oracle.U32, decisions=g["decisions"][:, r])
         assert list(st.decision_total)[:len(p.mu) + 1] == g["cnt"].sum(axis=1).tolist()
         assert st.mean == pytest.approx(g["y"].mean(), rel=1e-12) and st.R == 3
+
+
+@pytest.mark.parametrize("d,N,M", [(1, 2, 1), (16, 16, 1), (16, 17, 2), (17, 16, 1), (3, 32, 1), (32, 32, 3), (32, 33, 1), (8, 32, 1),
+                                   (9, 29, 1), (5, 100, 2), (4, 527, 1)])
+def test_one_replication_per_wavefront(ctx, d, N, M):
+    # the edges of the register forms, one and three drawing wavefronts, epochs of several iterations
+    mu, sigma = workloads.diag_instance(14, d, d)
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, checkpoints=(5, 70), gap_eps=0.05, w0=np.full(d, 0.5 / d), instance_id=d,
+                    log_reps=(0, 3))
+    print(f"[widths] wavefront d={d} N={N} M={M}", flush=True)
+    ctx.run_batch([p], [3], [70], 9, lanes_per_rep=[64], keep_paths=True)
+    st, g = ctx.batch_stats(0), ctx.batch_paths(0)
+    op = parity.oracle_problem(p, 9)
+    for r in range(3):
+        parity.check_rep(op, g, r, 70, oracle.U32, decisions=g["decisions"][:, r])
+    assert list(st.decision_total)[:d + 1] == g["cnt"].sum(axis=1).tolist()
