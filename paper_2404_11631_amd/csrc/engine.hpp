@@ -13,6 +13,8 @@
 #include "sim_types.hpp"
 
 namespace fw {
+// Whether a run should give launch_fw_paths records (RunBuffers.rec_y): with them it takes the split form.
+bool paths_split_applies(const InstanceDesc &desc, bool fp64, bool sched, int device);
 int launch_fw_paths(const InstanceDesc &host_desc, const InstanceDesc *dev_desc, const RunBuffers &B,
                     bool fp64, hipStream_t stream, int *kernel_width);
 int launch_fw_batch(const BatchBuffers &B, hipStream_t stream);
@@ -133,6 +135,7 @@ struct sim_ctx {
     DevBuf y, fck, cnt, wsum, tau, dlog, part_f, part_i, done, final_f, final_i;
     DevBuf dense;                         // dense-L operands: Ag, Av (FP32), L (FP64)
     DevBuf feat;                          // control-variate features [(d+2)][R]
+    DevBuf recs;                          // per-path records of a run that keeps none (spare)
     DevBuf sched;                         // per-epoch sample-size table (sim_params.n_schedule)
     std::vector<unsigned char> sched_host; // its host copy, kept until the next run
     void *dense_host = nullptr;           // pinned staging of the same

@@ -95,32 +95,32 @@ constexpr int gcd_const(int a, int b) { return b == 0 ? a : gcd_const(b, a % b);
 // each of S and the counts -- 50 of the 250 VALU instructions an iteration spends outside its
 // samples at d = 10, and 2 d + 1 registers. Feature runs (whose LDS holds the category sums) and 64-bit
 // signatures keep registers.
-template <int D, typename WS, bool LDS>
+template <int D, typename WS, bool LDS, int STRIDE = kBlock>
 struct PathRec;
 
-template <int D, typename WS>
-struct PathRec<D, WS, true> {
+template <int D, typename WS, int STRIDE>
+struct PathRec<D, WS, true, STRIDE> {
     WS *s;             // this thread's signature column
     uint32_t *c;       // and its count column
     __device__ __forceinline__ void clear()
     {
 #pragma unroll
         for (int j = 0; j <= D; ++j) {
-            s[j * kBlock] = 0;
-            c[j * kBlock] = 0;
+            s[j * STRIDE] = 0;
+            c[j * STRIDE] = 0;
         }
     }
-    __device__ __forceinline__ WS sig(int j) const { return s[(j + 1) * kBlock]; }
-    __device__ __forceinline__ uint32_t count(int j) const { return c[j * kBlock]; }
+    __device__ __forceinline__ WS sig(int j) const { return s[(j + 1) * STRIDE]; }
+    __device__ __forceinline__ uint32_t count(int j) const { return c[j * STRIDE]; }
     __device__ __forceinline__ void step(int a, WS tp1)
     {
-        __hip_atomic_fetch_add(s + a * kBlock, tp1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(c + a * kBlock, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(s + a * STRIDE, tp1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(c + a * STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
 
-template <int D, typename WS>
-struct PathRec<D, WS, false> {
+template <int D, typename WS, int STRIDE>
+struct PathRec<D, WS, false, STRIDE> {
     WS s[D];
     uint32_t c[D + 1];
     __device__ __forceinline__ void clear()
@@ -187,11 +187,17 @@ __device__ __forceinline__ double lane_value(double x, uint32_t lane)
     return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
+// The source of a replication's normals: its own lane draws them (fw_paths_split.hpp has another).
+struct OwnDraws {
+    static constexpr bool kFed = false;
+    static constexpr int kStride = kBlock;             // lanes of an LDS record row
+};
+
 // One replication of Algorithm 1; returns Y and tau, leaves signature and counts in rec. Every lane of
 // the wavefront takes part (lanes past R repeat the last replication and store nothing).
-template <int D, bool EXACT, typename Real, int NOISE, typename WS, bool FEAT, bool SCHED, class Rec>
+template <int D, bool EXACT, typename Real, int NOISE, typename WS, bool FEAT, bool SCHED, class Rec, class Feed = OwnDraws>
 __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, const RunBuffers &B,
-                                         uint32_t r, bool active, Rec &rec, LaneResult &res, uint64_t *feat_cnt)
+                                         uint32_t r, bool active, Rec &rec, LaneResult &res, uint64_t *feat_cnt, Feed feed = Feed{})
 {
     const Coef<Real> C{P};
     const int d = EXACT ? D : static_cast<int>(P->d);
@@ -231,12 +237,12 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
     uint32_t epoch = 0, m_in_epoch = 0;   // t = epoch * M + m_in_epoch
     // control-variate summaries: per category (0 origin, j+1 vertex e_j) the integer sum of (t+1)^2
     // over iterations whose epoch's reference decision is that category, in this thread's column
-    // of LDS (feat_cnt[c * kBlock]); the (t+1)-weighted count of the most probable category
+    // of LDS (feat_cnt[c * Feed::kStride]); the (t+1)-weighted count of the most probable category
     uint64_t fcnt1 = 0;
     const uint32_t ftop = FEAT ? P->cv_top : 0u;
     if constexpr (FEAT) {
 #pragma unroll
-        for (int c = 0; c <= D; ++c) feat_cnt[c * kBlock] = 0;
+        for (int c = 0; c <= D; ++c) feat_cnt[c * Feed::kStride] = 0;
     }
 
     Real cw_lane = Real(0);
@@ -297,7 +303,9 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
             return C.tscale() * Coef<Real>::rsqrt(ss);
         };
 
-        if constexpr (EXACT) {
+        if constexpr (Feed::kFed) {
+            feed.samples(N, v, s1, s2);
+        } else if constexpr (EXACT) {
             // groups of G samples hold a whole number of Philox blocks: static packing. Blocks are
             // drawn as the samples reach them, so a wide instance holds one sample and a part.
             // Narrow binary32 instances take several groups at a time, for enough independent
@@ -386,7 +394,7 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
                         }
                     }
                 }
-                feat_cnt[pick * kBlock] += w2;
+                feat_cnt[pick * Feed::kStride] += w2;
                 fcnt1 += (pick == ftop) ? w1 : 0u;
             }
         }
@@ -454,13 +462,134 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
                 if (c <= d) {
                     const uint64_t row = (c == 0) ? static_cast<uint64_t>(d) : static_cast<uint64_t>(c - 1);
                     B.feat[row * R + r] =
-                        static_cast<float>((static_cast<double>(feat_cnt[c * kBlock]) - P->cv_mean[c]) * P->cv_inv[c]);
+                        static_cast<float>((static_cast<double>(feat_cnt[c * Feed::kStride]) - P->cv_mean[c]) * P->cv_inv[c]);
                 }
             }
             B.feat[static_cast<uint64_t>(d + 1) * R + r] =
                 static_cast<float>((static_cast<double>(fcnt1) - P->cv_mean1) * P->cv_inv1);
         }
     }
+}
+
+// The workgroup's partials and, in the last workgroup to finish, the run's statistics, from replication
+// r's outcome, hitting time and decision counts (256 threads, LDS sm_f [2 kBlock / 64], sm_i
+// [kBlock / 64], sm_last).
+template <class Count>
+__device__ __forceinline__ void reduce_paths(const InstanceDesc *__restrict__ P, const RunBuffers &B, uint64_t r, bool active, int d,
+                                             double y, uint32_t tau, Count count, double *sm_f, uint64_t *sm_i, uint32_t *sm_last)
+{
+    const uint64_t R = P->R;
+    // per-workgroup partials: streams Y, f(w_c), RSE_c
+    const uint32_t nb = B.nblocks;
+    const uint32_t n_ckpt = P->n_ckpt;
+    const uint32_t n_streams = 1 + 2 * n_ckpt;
+    for (uint32_t s = 0; s < n_streams; ++s) {
+        double x = 0.0;
+        bool valid = active;
+        if (active) {
+            if (s == 0) {
+                x = y;
+            } else if (s <= n_ckpt) {
+                x = B.fck[static_cast<uint64_t>(s - 1) * R + r];
+            } else {
+                const double f = B.fck[static_cast<uint64_t>(s - 1 - n_ckpt) * R + r];
+                valid = (f != 0.0);
+                const double e = valid ? (f - y) / f : 0.0;
+                x = e * e;
+            }
+        }
+        if (!valid) x = 0.0;
+        double h = x, l = 0.0;
+        block_sum_dd(h, l, sm_f);
+        double qh = x * x, ql = fma(x, x, -(x * x));
+        block_sum_dd(qh, ql, sm_f);
+        double ch = valid ? 1.0 : 0.0, cl = 0.0;
+        block_sum_dd(ch, cl, sm_f);
+        if (threadIdx.x == 0) {
+            double *base = B.part_f + static_cast<uint64_t>(s) * kStreamFields * nb + blockIdx.x;
+            store_agent(base + 0 * nb, h);
+            store_agent(base + 1 * nb, l);
+            store_agent(base + 2 * nb, qh);
+            store_agent(base + 3 * nb, ql);
+            store_agent(base + 4 * nb, ch);
+        }
+    }
+    {
+        const double ymin = block_extreme<false>(active ? y : INFINITY, sm_f);
+        const double ymax = block_extreme<true>(active ? y : -INFINITY, sm_f);
+        if (threadIdx.x == 0) {
+            double *base = B.part_f + static_cast<uint64_t>(n_streams) * kStreamFields * nb + blockIdx.x;
+            store_agent(base, ymin);
+            store_agent(base + nb, ymax);
+        }
+    }
+    for (int j = 0; j <= d; ++j) {
+        const uint32_t cj = active ? count(j) : 0u;
+        const uint64_t tot = block_sum_u64(cj, sm_i);
+        if (threadIdx.x == 0) store_agent(B.part_i + static_cast<uint64_t>(j) * nb + blockIdx.x, tot);
+    }
+    {
+        const bool hit = active && tau != kTauNone;
+        const uint64_t tc = block_sum_u64(hit ? 1u : 0u, sm_i);
+        const uint64_t ts = block_sum_u64(hit ? tau : 0u, sm_i);
+        if (threadIdx.x == 0) {
+            store_agent(B.part_i + static_cast<uint64_t>(d + 1) * nb + blockIdx.x, tc);
+            store_agent(B.part_i + static_cast<uint64_t>(d + 2) * nb + blockIdx.x, ts);
+        }
+    }
+
+    // the last workgroup to finish reduces every partial in a fixed order
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t prev = __hip_atomic_fetch_add(B.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        *sm_last = (prev == nb - 1) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!*sm_last) return;
+    __threadfence();
+
+    for (uint32_t s = 0; s < n_streams; ++s) {
+        const double *base = B.part_f + static_cast<uint64_t>(s) * kStreamFields * nb;
+        double h = 0.0, l = 0.0, qh = 0.0, ql = 0.0, ch = 0.0, cl = 0.0;
+        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) {
+            dd_add(h, l, load_agent(base + 0 * nb + b), load_agent(base + 1 * nb + b));
+            dd_add(qh, ql, load_agent(base + 2 * nb + b), load_agent(base + 3 * nb + b));
+            dd_add(ch, cl, load_agent(base + 4 * nb + b), 0.0);
+        }
+        block_sum_dd(h, l, sm_f);
+        block_sum_dd(qh, ql, sm_f);
+        block_sum_dd(ch, cl, sm_f);
+        if (threadIdx.x == 0) {
+            double *o = B.final_f + static_cast<uint64_t>(s) * kStreamFields;
+            o[0] = h;
+            o[1] = l;
+            o[2] = qh;
+            o[3] = ql;
+            o[4] = ch + cl;
+        }
+    }
+    {
+        const double *base = B.part_f + static_cast<uint64_t>(n_streams) * kStreamFields * nb;
+        double mn = INFINITY, mx = -INFINITY;
+        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) {
+            mn = fmin(mn, load_agent(base + b));
+            mx = fmax(mx, load_agent(base + nb + b));
+        }
+        mn = block_extreme<false>(mn, sm_f);
+        mx = block_extreme<true>(mx, sm_f);
+        if (threadIdx.x == 0) {
+            B.final_f[n_streams * kStreamFields] = mn;
+            B.final_f[n_streams * kStreamFields + 1] = mx;
+        }
+    }
+    for (int j = 0; j < d + 3; ++j) {
+        uint64_t x = 0;
+        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) x += load_agent(B.part_i + static_cast<uint64_t>(j) * nb + b);
+        x = block_sum_u64(x, sm_i);
+        if (threadIdx.x == 0) B.final_i[j] = x;
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(B.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -513,117 +642,7 @@ __global__ __launch_bounds__(kBlock) void fw_paths_kernel(const InstanceDesc *__
         }
     }
 
-    // per-workgroup partials: streams Y, f(w_c), RSE_c
-    const uint32_t nb = B.nblocks;
-    const uint32_t n_ckpt = P->n_ckpt;
-    const uint32_t n_streams = 1 + 2 * n_ckpt;
-    for (uint32_t s = 0; s < n_streams; ++s) {
-        double x = 0.0;
-        bool valid = active;
-        if (active) {
-            if (s == 0) {
-                x = res.y;
-            } else if (s <= n_ckpt) {
-                x = B.fck[static_cast<uint64_t>(s - 1) * R + r];
-            } else {
-                const double f = B.fck[static_cast<uint64_t>(s - 1 - n_ckpt) * R + r];
-                valid = (f != 0.0);
-                const double e = valid ? (f - res.y) / f : 0.0;
-                x = e * e;
-            }
-        }
-        if (!valid) x = 0.0;
-        double h = x, l = 0.0;
-        block_sum_dd(h, l, sm_f);
-        double qh = x * x, ql = fma(x, x, -(x * x));
-        block_sum_dd(qh, ql, sm_f);
-        double ch = valid ? 1.0 : 0.0, cl = 0.0;
-        block_sum_dd(ch, cl, sm_f);
-        if (threadIdx.x == 0) {
-            double *base = B.part_f + static_cast<uint64_t>(s) * kStreamFields * nb + blockIdx.x;
-            store_agent(base + 0 * nb, h);
-            store_agent(base + 1 * nb, l);
-            store_agent(base + 2 * nb, qh);
-            store_agent(base + 3 * nb, ql);
-            store_agent(base + 4 * nb, ch);
-        }
-    }
-    {
-        const double ymin = block_extreme<false>(active ? res.y : INFINITY, sm_f);
-        const double ymax = block_extreme<true>(active ? res.y : -INFINITY, sm_f);
-        if (threadIdx.x == 0) {
-            double *base = B.part_f + static_cast<uint64_t>(n_streams) * kStreamFields * nb + blockIdx.x;
-            store_agent(base, ymin);
-            store_agent(base + nb, ymax);
-        }
-    }
-    for (int j = 0; j <= d; ++j) {
-        const uint32_t cj = active ? rec.count(j) : 0u;
-        const uint64_t tot = block_sum_u64(cj, sm_i);
-        if (threadIdx.x == 0) store_agent(B.part_i + static_cast<uint64_t>(j) * nb + blockIdx.x, tot);
-    }
-    {
-        const bool hit = active && res.tau != kTauNone;
-        const uint64_t tc = block_sum_u64(hit ? 1u : 0u, sm_i);
-        const uint64_t ts = block_sum_u64(hit ? res.tau : 0u, sm_i);
-        if (threadIdx.x == 0) {
-            store_agent(B.part_i + static_cast<uint64_t>(d + 1) * nb + blockIdx.x, tc);
-            store_agent(B.part_i + static_cast<uint64_t>(d + 2) * nb + blockIdx.x, ts);
-        }
-    }
-
-    // the last workgroup to finish reduces every partial in a fixed order
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t prev = __hip_atomic_fetch_add(B.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        sm_last = (prev == nb - 1) ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!sm_last) return;
-    __threadfence();
-
-    for (uint32_t s = 0; s < n_streams; ++s) {
-        const double *base = B.part_f + static_cast<uint64_t>(s) * kStreamFields * nb;
-        double h = 0.0, l = 0.0, qh = 0.0, ql = 0.0, ch = 0.0, cl = 0.0;
-        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) {
-            dd_add(h, l, load_agent(base + 0 * nb + b), load_agent(base + 1 * nb + b));
-            dd_add(qh, ql, load_agent(base + 2 * nb + b), load_agent(base + 3 * nb + b));
-            dd_add(ch, cl, load_agent(base + 4 * nb + b), 0.0);
-        }
-        block_sum_dd(h, l, sm_f);
-        block_sum_dd(qh, ql, sm_f);
-        block_sum_dd(ch, cl, sm_f);
-        if (threadIdx.x == 0) {
-            double *o = B.final_f + static_cast<uint64_t>(s) * kStreamFields;
-            o[0] = h;
-            o[1] = l;
-            o[2] = qh;
-            o[3] = ql;
-            o[4] = ch + cl;
-        }
-    }
-    {
-        const double *base = B.part_f + static_cast<uint64_t>(n_streams) * kStreamFields * nb;
-        double mn = INFINITY, mx = -INFINITY;
-        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) {
-            mn = fmin(mn, load_agent(base + b));
-            mx = fmax(mx, load_agent(base + nb + b));
-        }
-        mn = block_extreme<false>(mn, sm_f);
-        mx = block_extreme<true>(mx, sm_f);
-        if (threadIdx.x == 0) {
-            B.final_f[n_streams * kStreamFields] = mn;
-            B.final_f[n_streams * kStreamFields + 1] = mx;
-        }
-    }
-    for (int j = 0; j < d + 3; ++j) {
-        uint64_t x = 0;
-        for (uint32_t b = threadIdx.x; b < nb; b += kBlock) x += load_agent(B.part_i + static_cast<uint64_t>(j) * nb + b);
-        x = block_sum_u64(x, sm_i);
-        if (threadIdx.x == 0) B.final_i[j] = x;
-    }
-    if (threadIdx.x == 0) __hip_atomic_store(B.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    reduce_paths(P, B, r, active, d, res.y, res.tau, [&](int j) { return rec.count(j); }, sm_f, sm_i, &sm_last);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,0 +1,8 @@
+// fw_paths_split_features.hip -- the same with control-variate features (fw_paths_split.hpp).
+#include "fw_paths_split.hpp"
+
+namespace fw {
+
+KernelFn paths_split_features(uint32_t d) { return choose_split<1, 32, true>(d); }
+
+}  // namespace fw

@@ -30,7 +30,7 @@ namespace {
 // Gives back the buffers a run can do without (hipFree waits for the launches that use them).
 void release_spare(sim_ctx *ctx)
 {
-    for (DevBuf *b : {&ctx->wide.words, &ctx->nv.words, &ctx->nvlp.words, &ctx->sqn.words}) {
+    for (DevBuf *b : {&ctx->recs, &ctx->wide.words, &ctx->nv.words, &ctx->nvlp.words, &ctx->sqn.words}) {
         ctx->ws_used -= b->bytes;
         free_buf(*b);
     }
@@ -225,7 +225,7 @@ void sim_destroy(sim_ctx *ctx)
     else (void)hipDeviceSynchronize();
     for (DevBuf *b : {&ctx->y, &ctx->fck, &ctx->cnt, &ctx->wsum, &ctx->tau, &ctx->dlog, &ctx->part_f,
                       &ctx->part_i, &ctx->done, &ctx->final_f, &ctx->final_i, &ctx->dense,
-                      &ctx->feat, &ctx->sched})
+                      &ctx->feat, &ctx->sched, &ctx->recs})
         free_buf(*b);
     if (ctx->dense_host) (void)hipHostFree(ctx->dense_host);
     if (ctx->desc_dev) (void)hipFree(ctx->desc_dev);
@@ -380,6 +380,17 @@ int run_impl(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint64_t
         rc = fw::launch_fw_dense(*ctx->desc_host, ctx->desc_dev, B, ctx->stream);
         width = 2;
     } else {
+        // the records of the two-launch form; without room for them the paths reduce themselves
+        B.rec_y = nullptr;
+        const bool fp64 = p->state_precision == SIM_FP64;
+        if (fw::paths_split_applies(*ctx->desc_host, fp64, p->n_schedule != 0, ctx->device) &&
+            (keep || ensure_spare(ctx, ctx->recs, R * (sizeof(double) + sizeof(uint32_t) * (d + 2))))) {
+            double *const y = static_cast<double *>(ctx->recs.ptr);
+            uint32_t *const tau = reinterpret_cast<uint32_t *>(y + R);
+            B.rec_y = want_y ? B.y : y;
+            B.rec_tau = keep ? B.tau : tau;
+            B.rec_cnt = keep ? B.cnt : tau + R;
+        }
         rc = fw::launch_fw_paths(*ctx->desc_host, ctx->desc_dev, B, p->state_precision == SIM_FP64, ctx->stream, &width);
     }
     if (rc == -5) return set_err(ctx, SIM_EUNSUPPORTED, "no kernel for d=%u with this precision and noise", d);

@@ -101,6 +101,15 @@ constexpr uint32_t kBatchStageFloats = 2112;
 // 8 outcomes Y only (set by the library for its own control-variate runs).
 constexpr uint32_t kFlagYOnly = 8u;
 
+// Replications up to which other wavefronts draw a path's normals (fw_paths_split.hpp), where the device
+// also holds every workgroup at once. Speed against a lane per replication, at 1,000, 32,768, 49,152 and
+// 65,536 replications: d = 3 1.6, 1.3, 1.1, 0.9; d = 10 1.8, 1.3, 1.1, 0.9; d = 24 2.3, 1.6, 1.3, 0.9 (past
+// three workgroups per compute unit the lanes fill the issue slots by themselves); d = 2 1.2, 1.05, 0.9, 0.8;
+// d = 1 is slower throughout (its path is as long as its draws). d = 32 holds two workgroups per compute
+// unit, with features one: 1.4 at 32,768 and 0.9 at 49,152.
+constexpr uint64_t kSplitReps = 49152;
+constexpr uint64_t kSplitRepsTwo = 32768;      // d = 2
+
 // Per-run device buffers. Structure of arrays, replication index fastest.
 struct RunBuffers {
     double *y;            // [R]              (KEEP_PATHS or outcomes only)
@@ -128,6 +137,10 @@ struct RunBuffers {
     const double *sched_inv_d;
     const float *sched_c_f;
     const double *sched_c_d;
+    // records the paths leave for the reduction launch, laid out as y, tau and cnt (NULL: one launch)
+    double *rec_y;
+    uint32_t *rec_tau;
+    uint32_t *rec_cnt;
 };
 
 }  // namespace fw

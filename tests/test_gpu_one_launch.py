@@ -14,11 +14,11 @@ def both(run, records):
     """The records of `run` on an uncapped context and on one without room for the exchange."""
     out, used = [], 0
     for cap in (0, 1):
-        ctx = sim.Sim(0, workspace_bytes=used - 32 if cap else 0)
+        ctx = sim.Sim(0, workspace_bytes=used - 8 if cap else 0)
         try:
             run(ctx)
             out.append(records(ctx))
-            assert not cap or ctx.workspace_bytes() < used - 32      # the slots were not allocated
+            assert not cap or ctx.workspace_bytes() < used - 8      # the slots were not allocated
             used = ctx.workspace_bytes()
         finally:
             ctx.close()
@@ -141,3 +141,33 @@ def test_sqn_split(n, rows, b, bH, M, L, R, K, fp32, ckpt):
     a, b2 = both(run, records)
     same(a, b2)
     assert a["pairs"].tolist() == [max(K // L - 1, 0)] * R
+
+
+@pytest.mark.parametrize("d,N,M,R,T,ckpt,features", [
+    (2, 2, 1, 1, 1, (), False), (3, 5, 1, 64, 40, (1, 40), False), (4, 9, 3, 65, 37, (7,), False), (5, 3, 1, 300, 25, (), True),
+    (7, 6, 1, 257, 30, (30,), False), (10, 11, 2, 130, 33, (2, 33), False), (10, 10, 1, 100, 200, (), True), (13, 2, 1, 70, 40, (), False),
+    (15, 7, 1, 64, 30, (3,), False), (17, 5, 2, 100, 31, (), False), (21, 6, 1, 90, 20, (), True), (27, 31, 1, 65, 20, (20,), False),
+    (30, 3, 1, 63, 20, (), False), (31, 8, 1, 129, 20, (), False), (32, 4, 1, 300, 20, (5,), False), (12, 3, 1, 49_000, 12, (), False)])
+def test_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt, features):
+    # against a lane per replication, which a context without room for the records takes: odd groups, halves
+    # of long groups, partial units, chunks across iterations, features
+    print(f"[one launch] paths d={d} N={N} M={M} R={R} T={T} features={features}", flush=True)
+    mu, sigma = workloads.diag_instance(15, d, d)
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, checkpoints=ckpt, gap_eps=0.05, cv_features=features,
+                    cv_ref=-mu if features else None, w0=np.full(d, 0.5 / d) if R == 300 else None, instance_id=d,
+                    log_reps=(0, min(R, 8)))
+
+    def run(ctx):
+        ctx.run(p, R, T, 5)
+
+    def records(ctx):
+        st, g = ctx.stats(), ctx.paths()
+        out = {f: getattr(st, f) for f in ("mean", "var", "min", "max", "tau_count", "tau_mean")}
+        out.update(total=list(st.decision_total), sd=list(st.f_sd)[:len(ckpt)], rse=list(st.rse_mean)[:len(ckpt)],
+                   decisions=g["decisions"], f=g.get("f_ckpt", 0))
+        if features:
+            out["x"] = g["x"]
+        return out
+
+    a, b = both(run, records)
+    same(a, b)
