@@ -15,9 +15,18 @@ __global__ __launch_bounds__(kBlock) void fw_paths_reduce_kernel(const InstanceD
                  [&](int j) { return B.rec_cnt[static_cast<uint64_t>(j) * R + r]; }, sm_f, sm_i, &sm_last);
 }
 
+// drawing wavefronts of a workgroup
+static int split_draw(const InstanceDesc &desc)
+{
+    return !(desc.flags & 4u) && desc.d >= kSplitSevenFrom && desc.R <= kSplitRepsSeven ? 7 : 3;
+}
+
 static KernelFn split_kernel(const InstanceDesc &desc)
 {
-    return desc.flags & 4u ? paths_split_features(desc.d) : desc.d <= 16 ? paths_split_narrow(desc.d) : paths_split_broad(desc.d);
+    const int draw = split_draw(desc);
+    return desc.flags & 4u ? paths_split_features(desc.d)
+           : desc.d <= 16  ? paths_split_narrow(desc.d, draw)
+                           : paths_split_broad(desc.d, draw);
 }
 
 static uint32_t split_grid(const InstanceDesc &desc) { return static_cast<uint32_t>((desc.R + 63) / 64); }
@@ -29,7 +38,8 @@ bool paths_split_applies(const InstanceDesc &desc, bool fp64, bool sched, int de
         return false;
     int cus = 0, per_cu = 0;
     return hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
-           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(split_kernel(desc)), kBlock, 0) ==
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(split_kernel(desc)),
+                                                        64 * (split_draw(desc) + 1), 0) ==
                hipSuccess &&
            static_cast<uint64_t>(cus) * static_cast<uint64_t>(per_cu) >= split_grid(desc);
 }
@@ -45,7 +55,7 @@ int launch_fw_paths(const InstanceDesc &host_desc, const InstanceDesc *dev_desc,
     KernelChoice kc{nullptr, 0, false};
     if (B.rec_y) {
         if (kernel_width) *kernel_width = static_cast<int>(d);
-        hipLaunchKernelGGL(split_kernel(host_desc), dim3(split_grid(host_desc)), dim3(kBlock), 0, stream, dev_desc, B);
+        hipLaunchKernelGGL(split_kernel(host_desc), dim3(split_grid(host_desc)), dim3(64 * (split_draw(host_desc) + 1)), 0, stream, dev_desc, B);
         hipLaunchKernelGGL(fw_paths_reduce_kernel, dim3(B.nblocks), dim3(kBlock), 0, stream, dev_desc, B);
         return hipGetLastError() == hipSuccess ? 0 : -3;
     }

@@ -4,10 +4,16 @@
 // fw_paths.hpp gives a replication one lane that draws and uses its normals; 64 replications are one
 // wavefront, and a run of up to ~65,000 leaves most of the device's issue slots empty. Here a
 // workgroup is 64 replications: one wavefront runs their paths as fw_paths.hpp does (a lane each), the
-// other three draw their normals, chunk by chunk, into the other of two LDS buffers. The draws are
-// about four fifths of a replication's instructions, so they set the pace of three wavefronts about
-// as the path does that of one. Which wavefront runs the paths rotates with the workgroup, so that the
-// SIMDs of a compute unit share them.
+// other three (or seven) draw their normals, chunk by chunk, into the other of two LDS buffers. The draws
+// are about four fifths of a replication's instructions, so they set the pace of three wavefronts about
+// as the path does that of one; seven hide the latency of one another's chains where a SIMD has no other
+// wavefront. Which wavefront runs the paths rotates with the workgroup, so that the SIMDs of a compute
+// unit share them.
+//
+// What bounds it: the draws' issue and latency, then the path wavefront (its reads of the buffers are a
+// tenth of its time). ms, a lane per replication -> split, 16,000 replications: d = N = 10, 1,000 iterations
+// 4.7 -> 2.4; d = 16, N = 18, 500 5.7 -> 2.9; d = 20, N = 20, 400 6.6 -> 3.1; d = 27, N = 31, 200
+// 7.7 -> 2.3 (seven drawing wavefronts from d = 7; three take 3.1).
 //
 // A chunk is a fixed number of units in stream order, across iterations. A unit is a group of samples
 // that holds whole Philox blocks, or half of one where a group is long (D odd from 15 on: the block
@@ -22,7 +28,7 @@
 
 namespace fw {
 
-template <int D>
+template <int D, int DRAW>
 struct SplitShape {
     static constexpr int kGroup = 4 / gcd_const(D, 4);                  // samples of whole blocks
     static constexpr int kGroupBlocks = kGroup * D / 4;
@@ -33,18 +39,19 @@ struct SplitShape {
     static constexpr int kBlocks = kHalves == 1 ? blocks(0) : (blocks(0) > blocks(1) ? blocks(0) : blocks(1));
     static constexpr bool kFused = kFuseSum<D>;
     static constexpr int kFloats = kFused ? 6 : 4;                      // floats of a block
-    static constexpr int kTarget = kFused ? 10 : 12;                    // blocks of a chunk, about
+    static constexpr int kTarget = DRAW > 3 ? 14 : kFused ? 10 : 12;    // blocks of a chunk, about
     static constexpr int kUnits = kBlocks > kTarget ? 1 : kTarget / kBlocks;   // units of a chunk
     static constexpr int kSlots = kUnits * kBlocks;
+    static constexpr int kEach = (kSlots + DRAW - 1) / DRAW;            // slots of a drawing wavefront
     static constexpr int kBuffer = kSlots * kFloats * 64;               // floats of a chunk
 };
 
 // The path wavefront's side of the buffers. One barrier before each chunk.
-template <int D>
+template <int D, int DRAW>
 struct FedDraws {
     static constexpr bool kFed = true;
     static constexpr int kStride = 64;
-    using Shape = SplitShape<D>;
+    using Shape = SplitShape<D, DRAW>;
     const float *lane0;        // this lane's column of buffer 0
     int buf, pos;              // the current chunk's buffer and unit
 
@@ -101,14 +108,13 @@ struct FedDraws {
     }
 };
 
-// Drawing wavefront W's side: its third of every chunk's slots, all their Philox chains side by side.
-template <int D, int W>
-__device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, uint32_t r, float *lane0)
+// Drawing wavefront w's side: its share of every chunk's slots, all their Philox chains side by side
+// (w: a number, or an integral constant, which places the slots at compile time).
+template <int D, int DRAW, class Wave>
+__device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, uint32_t r, Wave w, float *lane0)
 {
-    using Shape = SplitShape<D>;
-    constexpr int kEach = (Shape::kSlots + 2) / 3, kFrom = W * kEach;
-    constexpr int kMine = kFrom >= Shape::kSlots ? 0 : (Shape::kSlots - kFrom < kEach ? Shape::kSlots - kFrom : kEach);
-    constexpr int kHeld = kMine ? kMine : 1;
+    using Shape = SplitShape<D, DRAW>;
+    constexpr int kEach = Shape::kEach;
     const uint32_t N = P->N, M = P->M, T = static_cast<uint32_t>(P->T);
     const uint32_t k0 = static_cast<uint32_t>(P->seed), k1 = static_cast<uint32_t>(P->seed >> 32);
     const uint32_t dom = P->instance & 0xFFFFFFu;
@@ -116,36 +122,43 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
     const uint32_t n_last = N - (units - 1) * Shape::kUnit;             // samples of its last one
     const uint64_t chunks = (static_cast<uint64_t>(T) * units + Shape::kUnits - 1) / Shape::kUnits;
     uint32_t t0 = 0, u0 = 0;                                            // the chunk's first unit
+    // this wavefront's slots: unit and block within it
+    uint32_t in_unit[kEach], in_block[kEach];
+    bool mine[kEach];
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) {
+        const uint32_t slot = w * kEach + i;
+        mine[i] = slot < static_cast<uint32_t>(Shape::kSlots);
+        in_unit[i] = mine[i] ? slot / Shape::kBlocks : i ? in_unit[i ? i - 1 : 0] : 0u;
+        in_block[i] = slot % Shape::kBlocks;
+    }
     float *dst = lane0;
     for (uint64_t k = 0; k < chunks; ++k) {
         // each slot's block of the stream, its epoch, and whether a sample uses it
-        uint32_t epoch[kHeld], block[kHeld];
-        bool used[kHeld], all = true;
-        uint32_t t = t0, u = u0;
-        int at = 0;                                     // the unit of (t, u)
+        uint32_t epoch[kEach], block[kEach];
+        bool used[kEach], all = true;
+        uint32_t t = t0, u = u0, at = 0;                // (t, u): the chunk's unit `at`
 #pragma unroll
-        for (int i = 0; i < kMine; ++i) {
-            constexpr int kB = Shape::kBlocks;
-            const int j = (kFrom + i) / kB, b = (kFrom + i) % kB;
-            if (j != at) {
-                u += static_cast<uint32_t>(j - at);
-                at = j;
+        for (int i = 0; i < kEach; ++i) {
+            if (in_unit[i] != at) {
+                u += in_unit[i] - at;
+                at = in_unit[i];
                 while (u >= units) {
                     u -= units;
                     ++t;
                 }
             }
             const bool odd = Shape::kHalves == 2 && (u & 1u);
-            const int first = odd ? Shape::first(Shape::kHalves - 1) : 0;
-            int need = odd ? Shape::blocks(Shape::kHalves - 1) : Shape::blocks(0);
-            if (u + 1 == units) need = static_cast<int>((((odd ? Shape::kUnit : 0) + n_last) * D + 3) / 4) - first;
+            const uint32_t first = odd ? Shape::first(Shape::kHalves - 1) : 0;
+            uint32_t need = odd ? Shape::blocks(Shape::kHalves - 1) : Shape::blocks(0);
+            if (u + 1 == units) need = (((odd ? Shape::kUnit : 0) + n_last) * D + 3) / 4 - first;
             epoch[i] = M == 1 ? t : t / M;
-            block[i] = u / Shape::kHalves * Shape::kGroupBlocks + static_cast<uint32_t>(first + b);
-            used[i] = t < T && b < need;
+            block[i] = u / Shape::kHalves * Shape::kGroupBlocks + first + in_block[i];
+            used[i] = mine[i] && t < T && in_block[i] < need;
             all = all && used[i];
         }
-        PhiloxRow row[Shape::kUnits > 1 ? kHeld : 1];
-        float q[kHeld][6];
+        PhiloxRow row[Shape::kUnits > 1 ? kEach : 1];
+        float q[kEach][6];
         auto draw = [&](int i) {
             const Words4 x = philox_block(row[Shape::kUnits > 1 ? i : 0], block[i], dom, k0, k1);
             const uint32_t xs[4] = {x.x0, x.x1, x.x2, x.x3};
@@ -158,7 +171,7 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
             }
         };
         auto put = [&](int i) {
-            float *o = dst + (kFrom + i) * (Shape::kFloats * 64);
+            float *o = dst + (w * kEach + i) * (Shape::kFloats * 64);
             if constexpr (Shape::kFused) {
 #pragma unroll
                 for (int e = 0; e < 6; ++e) o[e * 64] = q[i][e];
@@ -170,16 +183,16 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
             }
         };
 #pragma unroll
-        for (int i = 0; i < kMine; ++i)
+        for (int i = 0; i < kEach; ++i)
             if (Shape::kUnits > 1 || i == 0) row[Shape::kUnits > 1 ? i : 0] = philox_row(epoch[i], r, k0);
         if (all) {
 #pragma unroll
-            for (int i = 0; i < kMine; ++i) draw(i);
+            for (int i = 0; i < kEach; ++i) draw(i);
 #pragma unroll
-            for (int i = 0; i < kMine; ++i) put(i);
+            for (int i = 0; i < kEach; ++i) put(i);
         } else {
 #pragma unroll
-            for (int i = 0; i < kMine; ++i)
+            for (int i = 0; i < kEach; ++i)
                 if (used[i]) {
                     draw(i);
                     put(i);
@@ -195,25 +208,30 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
     }
 }
 
-// 64 replications per workgroup: a path wavefront and three drawing ones.
-template <int D, bool FEAT>
-__global__ __launch_bounds__(kBlock) void fw_paths_split_kernel(const InstanceDesc *__restrict__ P, RunBuffers B)
+// 64 replications per workgroup: a path wavefront and DRAW drawing ones.
+template <int D, bool FEAT, int DRAW>
+__global__ __launch_bounds__(64 * (DRAW + 1)) void fw_paths_split_kernel(const InstanceDesc *__restrict__ P, RunBuffers B)
 {
     constexpr bool kLds = !FEAT && D >= 7;
-    __shared__ float sm_z[2 * SplitShape<D>::kBuffer];
+    using Shape = SplitShape<D, DRAW>;
+    __shared__ float sm_z[2 * Shape::kBuffer];
     __shared__ uint64_t sm_feat[FEAT ? (D + 1) * 64 : 1];
     __shared__ uint32_t sm_sig[kLds ? (D + 1) * 64 : 1];
     __shared__ uint32_t sm_cnt[kLds ? (D + 1) * 64 : 1];
     const uint64_t R = P->R;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t role = __builtin_amdgcn_readfirstlane((threadIdx.x / 64 + blockIdx.x) & 3u);
+    const uint32_t role = __builtin_amdgcn_readfirstlane((threadIdx.x / 64 + blockIdx.x) & static_cast<uint32_t>(DRAW));
     const uint64_t r = static_cast<uint64_t>(blockIdx.x) * 64 + lane;
     const bool active = r < R;
     const uint32_t rc = static_cast<uint32_t>(active ? r : R - 1);
     if (role != 0) {
-        if (role == 1) draw_chunks<D, 0>(P, rc, sm_z + lane);
-        else if (role == 2) draw_chunks<D, 1>(P, rc, sm_z + lane);
-        else draw_chunks<D, 2>(P, rc, sm_z + lane);
+        if constexpr (DRAW == 3) {
+            if (role == 1) draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 0>{}, sm_z + lane);
+            else if (role == 2) draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 1>{}, sm_z + lane);
+            else draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 2>{}, sm_z + lane);
+        } else {
+            draw_chunks<D, DRAW>(P, rc, role - 1, sm_z + lane);
+        }
         return;
     }
     PathRec<D, uint32_t, kLds, 64> rec;
@@ -223,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void fw_paths_split_kernel(const InstanceDe
     }
     LaneResult res{0.0, kTauNone};
     run_path<D, true, float, 0, uint32_t, FEAT, false>(P, B, rc, active, rec, res, sm_feat + lane,
-                                                       FedDraws<D>{sm_z + lane, 1, SplitShape<D>::kUnits});
+                                                       FedDraws<D, DRAW>{sm_z + lane, 1, Shape::kUnits});
     if (!active) return;
     B.rec_y[r] = res.y;
     B.rec_tau[r] = res.tau;
@@ -236,19 +254,20 @@ __global__ __launch_bounds__(kBlock) void fw_paths_split_kernel(const InstanceDe
 }
 
 // The kernel of width d among LO .. HI.
-template <int LO, int HI, bool FEAT>
+template <int LO, int HI, bool FEAT, int DRAW>
 inline KernelFn choose_split(uint32_t d)
 {
     if constexpr (LO > HI) {
         return nullptr;
     } else {
-        if (d == static_cast<uint32_t>(LO)) return &fw_paths_split_kernel<LO, FEAT>;
-        return choose_split<LO + 1, HI, FEAT>(d);
+        if (d == static_cast<uint32_t>(LO)) return &fw_paths_split_kernel<LO, FEAT, DRAW>;
+        return choose_split<LO + 1, HI, FEAT, DRAW>(d);
     }
 }
 
-KernelFn paths_split_narrow(uint32_t d);       // d <= 16
-KernelFn paths_split_broad(uint32_t d);        // 17 <= d <= 32
-KernelFn paths_split_features(uint32_t d);     // with features, d <= 32
+// with 3 or 7 drawing wavefronts
+KernelFn paths_split_narrow(uint32_t d, int draw);       // d <= 16
+KernelFn paths_split_broad(uint32_t d, int draw);        // 17 <= d <= 32
+KernelFn paths_split_features(uint32_t d);               // with features, d <= 32; 3
 
 }  // namespace fw

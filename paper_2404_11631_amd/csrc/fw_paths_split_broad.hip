@@ -3,6 +3,6 @@
 
 namespace fw {
 
-KernelFn paths_split_broad(uint32_t d) { return choose_split<17, 32, false>(d); }
+KernelFn paths_split_broad(uint32_t d, int draw) { return draw > 3 ? choose_split<17, 32, false, 7>(d) : choose_split<17, 32, false, 3>(d); }
 
 }  // namespace fw

@@ -3,6 +3,6 @@
 
 namespace fw {
 
-KernelFn paths_split_features(uint32_t d) { return choose_split<1, 32, true>(d); }
+KernelFn paths_split_features(uint32_t d) { return choose_split<2, 32, true, 3>(d); }
 
 }  // namespace fw

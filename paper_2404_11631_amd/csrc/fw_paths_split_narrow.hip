@@ -3,6 +3,6 @@
 
 namespace fw {
 
-KernelFn paths_split_narrow(uint32_t d) { return choose_split<1, 16, false>(d); }
+KernelFn paths_split_narrow(uint32_t d, int draw) { return draw > 3 ? choose_split<kSplitSevenFrom, 16, false, 7>(d) : choose_split<2, 16, false, 3>(d); }
 
 }  // namespace fw

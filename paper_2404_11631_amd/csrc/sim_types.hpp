@@ -109,6 +109,11 @@ constexpr uint32_t kFlagYOnly = 8u;
 // unit, with features one: 1.4 at 32,768 and 0.9 at 49,152.
 constexpr uint64_t kSplitReps = 49152;
 constexpr uint64_t kSplitRepsTwo = 32768;      // d = 2
+// Seven drawing wavefronts instead of three up to a workgroup per compute unit: at 1,000 replications d = 8
+// 1.15, d = 14 1.6, d = 22 1.2, d = 28 1.4 times as fast; d = 5 0.9 and with features 1.0 (the path sets
+// the pace). At two workgroups per compute unit d = 24 is at 0.6 (one is resident).
+constexpr uint64_t kSplitRepsSeven = 16384;
+constexpr uint32_t kSplitSevenFrom = 7;
 
 // Per-run device buffers. Structure of arrays, replication index fastest.
 struct RunBuffers {
