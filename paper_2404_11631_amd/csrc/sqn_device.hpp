@@ -28,6 +28,38 @@ __device__ __forceinline__ void draw_rows(const SqnArgs &A, uint32_t rep, uint64
     }
 }
 
+// x where mask is all ones, 0.0 where it is 0
+__device__ __forceinline__ double masked(double x, uint32_t mask)
+{
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
+    const uint32_t lo = static_cast<uint32_t>(b) & mask, hi = static_cast<uint32_t>(b >> 32) & mask;
+    return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+// a[e] += coef[i] where bit sh + e of bits[i pitch] is set, the rows i < count in order, eight rows' loads
+// together; a row past the end and a clear bit add 0.0, which changes no sum.
+__device__ __forceinline__ void add_bits(const uint32_t *bits, uint32_t pitch, uint32_t sh, const double *coef, uint32_t count,
+                                         double (&a)[4])
+{
+    for (uint32_t i = 0; i < count; i += 8) {
+        uint32_t x[8];
+        double r[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t row = min(i + j, count - 1);
+            x[j] = bits[row * pitch];
+            r[j] = coef[row];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t w = i + j < count ? x[j] >> sh : 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] += masked(r[j], static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(w), e, 1)));
+        }
+    }
+}
+
 // v summed over the set bits of a 32-feature word starting at feature j0, lowest bit first.
 __device__ __forceinline__ double word_dot(uint32_t bits, const double *v, uint32_t j0)
 {

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "sqn.hpp"
+#include "sqn_device.hpp"
 #include "sqn_split.hpp"
 
 namespace fw {
@@ -43,14 +44,6 @@ __device__ __forceinline__ void stage_slice(const Slice &c, const double (&v)[4]
     }
 }
 
-// x where mask is all ones, 0.0 where it is 0
-__device__ __forceinline__ double masked(double x, uint32_t mask)
-{
-    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
-    const uint32_t lo = static_cast<uint32_t>(b) & mask, hi = static_cast<uint32_t>(b >> 32) & mask;
-    return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
-}
-
 // The sum over the rows of coef[i] times the quad's four bits: each wavefront sums a contiguous
 // quarter of the rows in order, then every thread adds the four quarters in order (part: LDS
 // [kSplitWaves][64][4]). Every thread of the workgroup must call it; it synchronises.
@@ -61,24 +54,7 @@ __device__ __forceinline__ void slice_bit_sum(const Slice &c, const uint32_t *bi
     const uint32_t i0 = min(count, c.wv * per), i1 = min(count, i0 + per);
     const uint32_t wq = c.ql >> 3, sh = 4 * (c.ql & 7);
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    // eight rows' loads together; a row past the end and a clear bit add 0.0, which changes no sum
-    for (uint32_t i = i0; i < i1; i += 8) {
-        uint32_t x[8];
-        double r[8];
-#pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) {
-            const uint32_t row = min(i + j, i1 - 1);
-            x[j] = bits[row * kSliceWords + wq];
-            r[j] = coef[row];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) {
-            const uint32_t w = i + j < i1 ? x[j] >> sh : 0u;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] += masked(r[j], static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(w), e, 1)));
-        }
-    }
+    if (i0 < i1) add_bits(bits + i0 * kSliceWords + wq, kSliceWords, sh, coef + i0, i1 - i0, a);
 #pragma unroll
     for (int e = 0; e < 4; ++e) part[c.wv][c.ql][e] = a[e];
     __syncthreads();

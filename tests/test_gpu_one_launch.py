@@ -171,3 +171,29 @@ def test_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt, features):
 
     a, b = both(run, records)
     same(a, b)
+
+
+@pytest.mark.parametrize("n,M,b,bH,R", [(1, 1, 1, 1, 2), (60, 32, 1024, 300, 3), (1000, 25, 50, 300, 300), (1024, 4, 33, 1024, 2),
+                                        (1028, 4, 9, 20, 257), (2048, 3, 5, 7, 260), (2600, 25, 50, 90, 2), (4100, 2, 40, 65, 2)])
+def test_sqn_replications_do_not_depend_on_their_number(n, M, b, bH, R):
+    # the threads of a workgroup and the rows staged at a time follow from the sizes and from R: a
+    # replication alone and among R others is the same bits
+    print(f"[one launch] sqn n={n} M={M} b={b} bH={bH} R={R}", flush=True)
+    rng = np.random.default_rng(4)
+    X = (rng.random((500, n)) < min(0.5, 25.0 / n)).astype(np.uint8)
+    z = rng.integers(0, 2, 500).astype(np.uint8)
+    ctx = sim.Sim(0)
+    try:
+        ctx.sqn_load(X, z)
+        ctx.run_sqn(R, 30, 5, L=3, M=M, b=b, bH=bH, checkpoints=(7, 30))
+        a, st = ctx.sqn_paths(), ctx.sqn_stats()
+        ctx.run_sqn(1, 30, 5, L=3, M=M, b=b, bH=bH, checkpoints=(7, 30))
+        c = ctx.sqn_paths()
+    finally:
+        ctx.close()
+    for f in ("w", "S", "Y", "pairs"):
+        assert np.array_equal(np.asarray(a[f][0]), np.asarray(c[f][0]), equal_nan=True), f
+    assert np.array_equal(a["w_ckpt"][:, 0], c["w_ckpt"][:, 0], equal_nan=True)
+    if np.isfinite(a["F"]).all():           # a pair without curvature (one feature, one row) divides by 0
+        assert st.min == a["F"].min() and st.max == a["F"].max()
+        assert st.f_mean[0] == pytest.approx(a["F_ckpt"][0].mean(), rel=1e-13)
