@@ -124,7 +124,7 @@ __device__ __forceinline__ void vec_dots(const SqnArgs &A, uint32_t count, VecOf
 
 // The run kernel's LDS, sized by the run. A replication's iteration is a chain of short steps (88 % of its
 // wavefronts' cycles wait), so two workgroups per compute unit run in little more than the time of one:
-// the staged rows are cut to fit two where they can (n up to ~2,600 at M = 25). n = 1,000, 512
+// the staged rows are cut to fit two where a workgroup has 512 threads. n = 1,000, 512
 // replications, us per iteration: 57.2 with the arrays at their largest, 33.9 so (n = 100: 34.2, 17.8).
 constexpr uint32_t kPitch = kSqnMaxM + 1;                    // of the small matrices: a column's entries in different banks
 constexpr uint32_t kStageWords = 32 * (kSqnMaxN / 32);      // staged rows at most: 32 KB, 32 rows at the largest n
@@ -143,6 +143,15 @@ struct RunLds {
     size_t bytes;
 };
 
+// 512 threads where they own every quad and another replication can use the other half of the compute unit
+// (the registers hold 1,024 threads of it); no sum depends on their number. us per iteration at 512 and
+// 1,024 threads: n = 1,000, 256 replications 28.4, 28.0, 512 33.9, 55.6; n = 2,000, 256 36.2, 33.6, 512
+// 52.6, 66.1.
+__host__ __device__ inline bool half_block(const SqnArgs &A)
+{
+    return A.nq <= kRunBlock / 4 || (A.nq <= kRunBlock / 2 && A.R > kSqnComputeUnits);
+}
+
 __host__ __device__ inline RunLds run_lds(char *base, const SqnArgs &A)
 {
     RunLds l;
@@ -152,17 +161,17 @@ __host__ __device__ inline RunLds run_lds(char *base, const SqnArgs &A)
         at += sizeof(double) * ((n + 1) / 2 * 2);
         return p;
     };
-    const uint32_t rows = A.b > A.bH ? A.b : A.bH, mat = A.M * kPitch, each = rows > mat ? rows : mat;
+    const uint32_t M = A.M, rows = A.b > A.bH ? A.b : A.bH, mat = M * kPitch, each = rows > mat ? rows : mat;
     l.stage = doubles(A.ld);
     l.v = doubles(each);
     l.coef = doubles(each);
-    l.dots = doubles(3 * A.M);
+    l.dots = doubles(3 * M);
     l.SY = doubles(mat);
     l.YY = doubles(mat);
     l.Ri = doubles(mat);
     l.C = doubles(mat);
-    l.cs = doubles(A.M);
-    l.cy = doubles(A.M);
+    l.cs = doubles(M);
+    l.cy = doubles(M);
     l.idx = reinterpret_cast<uint32_t *>(doubles((rows + 1) / 2));
     l.rows = reinterpret_cast<uint32_t *>(base + at);
     const size_t row = sizeof(uint32_t) * A.xw, limit = at + 8 * row <= kLdsOfTwo ? kLdsOfTwo : kSqnLdsPerCu;
@@ -176,15 +185,23 @@ __host__ __device__ inline RunLds run_lds(char *base, const SqnArgs &A)
 }  // namespace
 
 // PT: the storage type of the pairs (double, or float when they are kept in binary32)
-template <int EQ, typename PT>
-__global__ __launch_bounds__(kRunBlock) void sqn_run_kernel(SqnArgs A)
+// TWO: the form that shares a compute unit (half_block)
+template <int EQ, typename PT, bool TWO>
+__global__ __launch_bounds__(TWO ? kRunBlock / 2 : kRunBlock, TWO ? 4 : 1) void sqn_run_kernel(SqnArgs A)
 {
+    // alone, the arrays stand at their largest: arrays of their own, which the compiler knows not to overlap
+    // (cut from one they cost an iteration 5 % at n = 5,000)
+    constexpr uint32_t kMat = TWO ? 1 : kSqnMaxM * kPitch, kEach = TWO ? 1 : kMat > kSqnMaxB ? kMat : kSqnMaxB;
+    __shared__ double m_stage[TWO ? 1 : kSqnMaxN], m_v[kEach], m_coef[kEach], m_dots[TWO ? 1 : 3 * kSqnMaxM];
+    __shared__ double m_SY[kMat], m_YY[kMat], m_Ri[kMat], m_C[kMat], m_cs[kSqnMaxM], m_cy[kSqnMaxM];
+    __shared__ uint32_t m_idx[TWO ? 1 : kSqnMaxB], m_rows[TWO ? 1 : kStageWords];
     HIP_DYNAMIC_SHARED(double, lds)
     const RunLds l = run_lds(reinterpret_cast<char *>(lds), A);
-    double *s_stage = l.stage, *s_v = l.v, *s_coef = l.coef, *s_dots = l.dots;
-    double *s_SY = l.SY, *s_YY = l.YY, *s_Ri = l.Ri, *s_C = l.C, *s_cs = l.cs, *s_cy = l.cy;
-    uint32_t *s_idx = l.idx, *s_rows = l.rows;
-    const uint32_t chunk = l.chunk;
+    double *s_stage = TWO ? l.stage : m_stage, *s_v = TWO ? l.v : m_v, *s_coef = TWO ? l.coef : m_coef;
+    double *s_dots = TWO ? l.dots : m_dots, *s_SY = TWO ? l.SY : m_SY, *s_YY = TWO ? l.YY : m_YY;
+    double *s_Ri = TWO ? l.Ri : m_Ri, *s_C = TWO ? l.C : m_C, *s_cs = TWO ? l.cs : m_cs, *s_cy = TWO ? l.cy : m_cy;
+    uint32_t *s_idx = TWO ? l.idx : m_idx, *s_rows = TWO ? l.rows : m_rows;
+    const uint32_t chunk = TWO ? l.chunk : kStageWords / A.xw;
 
     const uint32_t rep = blockIdx.x;
     const uint32_t tid = threadIdx.x, T = blockDim.x;
@@ -241,7 +258,17 @@ __global__ __launch_bounds__(kRunBlock) void sqn_run_kernel(SqnArgs A)
             for (int e = 0; e < EQ; ++e) {
                 if (!own[e]) continue;
                 const uint32_t wq = q[e] >> 3, sh = 4 * (q[e] & 7);
-                add_bits(s_rows + wq, xw, sh, s_coef + i0, cnt, g[e]);
+                if constexpr (EQ == 1) {
+                    add_bits(s_rows + wq, xw, sh, s_coef + i0, cnt, g[e]);
+                    continue;
+                }
+                for (uint32_t i = 0; i < cnt; ++i) {       // most rows have no bit in a wavefront's quads and are passed over
+                    const uint32_t x = (s_rows[i * xw + wq] >> sh) & 0xFu;
+                    const double r = s_coef[i0 + i];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if ((x >> c) & 1u) g[e][c] += r;
+                }
             }
         }
 #pragma unroll
@@ -365,7 +392,17 @@ __global__ __launch_bounds__(kRunBlock) void sqn_run_kernel(SqnArgs A)
                     for (int e = 0; e < EQ; ++e) {
                         if (!own[e]) continue;
                         const uint32_t wq = q[e] >> 3, sh = 4 * (q[e] & 7);
-                        add_bits(s_rows + wq, xw, sh, s_coef + i0, cnt, y[e]);
+                        if constexpr (EQ == 1) {
+                            add_bits(s_rows + wq, xw, sh, s_coef + i0, cnt, y[e]);
+                            continue;
+                        }
+                        for (uint32_t i = 0; i < cnt; ++i) {       // most rows have no bit in a wavefront's quads and are passed over
+                            const uint32_t x = (s_rows[i * xw + wq] >> sh) & 0xFu;
+                            const double r = s_coef[i0 + i];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if ((x >> c) & 1u) y[e][c] += r;
+                        }
                     }
                 }
 #pragma unroll
@@ -872,19 +909,18 @@ __global__ void sqn_stats_kernel(SqnArgs A)
 
 int launch_sqn_run(const SqnArgs &A, hipStream_t s)
 {
-    const bool one = A.nq <= static_cast<uint32_t>(kRunBlock);
-    void (*fn)(SqnArgs) = A.pairs_fp32 ? (one ? &sqn_run_kernel<1, float> : &sqn_run_kernel<2, float>)
-                                       : (one ? &sqn_run_kernel<1, double> : &sqn_run_kernel<2, double>);
-    const size_t lds = run_lds(nullptr, A).bytes;
+    const bool one = A.nq <= static_cast<uint32_t>(kRunBlock), two = half_block(A);
+    void (*fn)(SqnArgs) = A.pairs_fp32 ? (two   ? &sqn_run_kernel<1, float, true>
+                                          : one ? &sqn_run_kernel<1, float, false>
+                                                : &sqn_run_kernel<2, float, false>)
+                                       : (two   ? &sqn_run_kernel<1, double, true>
+                                          : one ? &sqn_run_kernel<1, double, false>
+                                                : &sqn_run_kernel<2, double, false>);
+    const size_t lds = two ? run_lds(nullptr, A).bytes : 0;
     if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            static_cast<int>(lds)) != hipSuccess)
         return -1;
-    // 512 threads where they own every quad and another replication can use the other half of the compute
-    // unit (the registers hold 1,024 threads of it); no sum depends on their number. us per iteration at
-    // 512 and 1,024 threads: n = 1,000, 256 replications 28.4, 28.0, 512 33.9, 55.6; n = 2,000, 256
-    // 36.2, 33.6, 512 52.6, 66.1
-    const bool half = A.nq <= kRunBlock / 4 || (A.nq <= kRunBlock / 2 && A.R > kSqnComputeUnits);
-    const uint32_t threads = half ? kRunBlock / 2 : kRunBlock;
+    const uint32_t threads = two ? kRunBlock / 2 : kRunBlock;
     hipLaunchKernelGGL(fn, dim3(A.R), dim3(threads), lds, s, A);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
