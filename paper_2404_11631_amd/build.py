@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsim.so")
 SOURCES = ["csrc/fw_paths_gauss_broad.hip", "csrc/fw_paths_t_broad.hip", "csrc/fw_paths_gauss_narrow.hip", "csrc/fw_paths_t_narrow.hip",
            "csrc/fw_paths_features.hip", "csrc/fw_paths_fp64.hip", "csrc/fw_paths_sched.hip", "csrc/fw_paths_long.hip", "csrc/fw_paths.hip",
-           "csrc/fw_paths_split_narrow.hip", "csrc/fw_paths_split_broad.hip", "csrc/fw_paths_split_features.hip",
+           "csrc/fw_paths_split_narrow.hip", "csrc/fw_paths_split_broad.hip", "csrc/fw_paths_split_features.hip", "csrc/fw_paths_split_fp64.hip",
            "csrc/fw_batch.hip", "csrc/fw_dense.hip", "csrc/mlp.hip", "csrc/sim_api.hip", "csrc/sim_batch.hip", "csrc/sim_noalloc.hip", "csrc/cv_api.hip", "csrc/fw_wide.hip", "csrc/fw_wide_run.hip", "csrc/wide_api.hip", "csrc/fw_newsvendor.hip", "csrc/fw_newsvendor_run.hip", "csrc/fw_newsvendor_lp_run.hip", "csrc/nv_api.hip",
            "csrc/fw_sqn.hip", "csrc/fw_sqn_split.hip", "csrc/fw_sqn_split_run.hip", "csrc/sqn_api.hip",
            "csrc/host_core.cpp"]

@@ -16,14 +16,15 @@ __global__ __launch_bounds__(kBlock) void fw_paths_reduce_kernel(const InstanceD
 }
 
 // drawing wavefronts of a workgroup
-static int split_draw(const InstanceDesc &desc)
+static int split_draw(const InstanceDesc &desc, bool fp64)
 {
-    return !(desc.flags & 4u) && desc.d >= kSplitSevenFrom && desc.R <= kSplitRepsSeven ? 7 : 3;
+    return !fp64 && !(desc.flags & 4u) && desc.d >= kSplitSevenFrom && desc.R <= kSplitRepsSeven ? 7 : 3;
 }
 
-static KernelFn split_kernel(const InstanceDesc &desc)
+static KernelFn split_kernel(const InstanceDesc &desc, bool fp64)
 {
-    const int draw = split_draw(desc);
+    if (fp64) return paths_split_fp64(desc.d);
+    const int draw = split_draw(desc, false);
     return desc.flags & 4u ? paths_split_features(desc.d)
            : desc.d <= 16  ? paths_split_narrow(desc.d, draw)
                            : paths_split_broad(desc.d, draw);
@@ -33,13 +34,15 @@ static uint32_t split_grid(const InstanceDesc &desc) { return static_cast<uint32
 
 bool paths_split_applies(const InstanceDesc &desc, bool fp64, bool sched, int device)
 {
-    if (fp64 || sched || desc.noise != 0 || desc.d < 2 || desc.d > 32 || desc.T > kMaxNarrowT ||
-        desc.R > (desc.d == 2 ? kSplitRepsTwo : kSplitReps))
-        return false;
+    if (sched || desc.noise != 0 || desc.d > (fp64 ? 16u : 32u) || desc.T > kMaxNarrowT) return false;
+    const bool own_kernel = desc.d <= 6 || desc.d == 8 || desc.d == 10 || desc.d == 12 || desc.d == 16;    // in binary64
+    const uint64_t most = fp64 ? (!own_kernel ? kSplitReps64Generic : desc.d <= 8 ? kSplitReps64 : kSplitReps64Wide)
+                               : (desc.d == 2 ? kSplitRepsTwo : kSplitReps);
+    if (desc.R > most || (fp64 ? (desc.flags & 4u) != 0 : desc.d < 2)) return false;
     int cus = 0, per_cu = 0;
     return hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
-           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(split_kernel(desc)),
-                                                        64 * (split_draw(desc) + 1), 0) ==
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(split_kernel(desc, fp64)),
+                                                        64 * (split_draw(desc, fp64) + 1), 0) ==
                hipSuccess &&
            static_cast<uint64_t>(cus) * static_cast<uint64_t>(per_cu) >= split_grid(desc);
 }
@@ -55,7 +58,7 @@ int launch_fw_paths(const InstanceDesc &host_desc, const InstanceDesc *dev_desc,
     KernelChoice kc{nullptr, 0, false};
     if (B.rec_y) {
         if (kernel_width) *kernel_width = static_cast<int>(d);
-        hipLaunchKernelGGL(split_kernel(host_desc), dim3(split_grid(host_desc)), dim3(64 * (split_draw(host_desc) + 1)), 0, stream, dev_desc, B);
+        hipLaunchKernelGGL(split_kernel(host_desc, fp64), dim3(split_grid(host_desc)), dim3(64 * (split_draw(host_desc, fp64) + 1)), 0, stream, dev_desc, B);
         hipLaunchKernelGGL(fw_paths_reduce_kernel, dim3(B.nblocks), dim3(kBlock), 0, stream, dev_desc, B);
         return hipGetLastError() == hipSuccess ? 0 : -3;
     }

@@ -13,7 +13,8 @@
 // What bounds it: the draws' issue and latency, then the path wavefront (its reads of the buffers are a
 // tenth of its time). ms, a lane per replication -> split, 16,000 replications: d = N = 10, 1,000 iterations
 // 4.7 -> 2.4; d = 16, N = 18, 500 5.7 -> 2.9; d = 20, N = 20, 400 6.6 -> 3.1; d = 27, N = 31, 200
-// 7.7 -> 2.3 (seven drawing wavefronts from d = 7; three take 3.1).
+// 7.7 -> 2.3 (seven drawing wavefronts from d = 7; three take 3.1). Binary64, 1,000 replications, 100
+// iterations of d = N = 2: 0.15 -> 0.06.
 //
 // A chunk is a fixed number of units in stream order, across iterations. A unit is a group of samples
 // that holds whole Philox blocks, or half of one where a group is long (D odd from 15 on: the block
@@ -28,31 +29,31 @@
 
 namespace fw {
 
-template <int D, int DRAW>
+template <int D, int DRAW, typename Real>
 struct SplitShape {
     static constexpr int kGroup = 4 / gcd_const(D, 4);                  // samples of whole blocks
     static constexpr int kGroupBlocks = kGroup * D / 4;
-    static constexpr int kHalves = kGroup == 4 && kGroupBlocks > 13 ? 2 : 1;
+    static constexpr int kHalves = kGroup == 4 && kGroupBlocks > (sizeof(Real) == 8 ? 8 : 13) ? 2 : 1;
     static constexpr int kUnit = kGroup / kHalves;                      // samples of a unit
     static constexpr int first(int h) { return h * kUnit * D / 4; }     // its first block in the group
     static constexpr int blocks(int h) { return ((h + 1) * kUnit * D + 3) / 4 - first(h); }
     static constexpr int kBlocks = kHalves == 1 ? blocks(0) : (blocks(0) > blocks(1) ? blocks(0) : blocks(1));
     static constexpr bool kFused = kFuseSum<D>;
-    static constexpr int kFloats = kFused ? 6 : 4;                      // floats of a block
-    static constexpr int kTarget = DRAW > 3 ? 14 : kFused ? 10 : 12;    // blocks of a chunk, about
+    static constexpr int kReals = kFused ? 6 : 4;                       // values of a block
+    static constexpr int kTarget = sizeof(Real) == 8 ? 6 : DRAW > 3 ? 14 : kFused ? 10 : 12;   // blocks of a chunk, about
     static constexpr int kUnits = kBlocks > kTarget ? 1 : kTarget / kBlocks;   // units of a chunk
     static constexpr int kSlots = kUnits * kBlocks;
     static constexpr int kEach = (kSlots + DRAW - 1) / DRAW;            // slots of a drawing wavefront
-    static constexpr int kBuffer = kSlots * kFloats * 64;               // floats of a chunk
+    static constexpr int kBuffer = kSlots * kReals * 64;               // values of a chunk
 };
 
 // The path wavefront's side of the buffers. One barrier before each chunk.
-template <int D, int DRAW>
+template <int D, int DRAW, typename Real>
 struct FedDraws {
     static constexpr bool kFed = true;
     static constexpr int kStride = 64;
-    using Shape = SplitShape<D, DRAW>;
-    const float *lane0;        // this lane's column of buffer 0
+    using Shape = SplitShape<D, DRAW, Real>;
+    const Real *lane0;        // this lane's column of buffer 0
     int buf, pos;              // the current chunk's buffer and unit
 
     template <int H, class V>
@@ -63,12 +64,12 @@ struct FedDraws {
             pos = 0;
             buf ^= 1;
         }
-        const float *u = lane0 + buf * Shape::kBuffer + pos * (Shape::kBlocks * Shape::kFloats * 64);
+        const Real *u = lane0 + buf * Shape::kBuffer + pos * (Shape::kBlocks * Shape::kReals * 64);
         ++pos;
 #pragma unroll
         for (int s = 0; s < Shape::kUnit; ++s) {
             if (s > 0 && static_cast<uint32_t>(s) >= n) break;
-            float z[D], rad[D], cs[D];
+            Real z[D], rad[D], cs[D];
 #pragma unroll
             for (int j = 0; j < D; ++j) {
                 constexpr int kFirst = 4 * Shape::first(H);
@@ -81,15 +82,15 @@ struct FedDraws {
                     z[j] = u[(b * 4 + c) * 64];
                 }
             }
-            float dot = 0.0f;
+            Real dot = Real(0);
 #pragma unroll
-            for (int j = 0; j < D; ++j) dot = fmaf(z[j], v[j], dot);
+            for (int j = 0; j < D; ++j) dot = fma(z[j], v[j], dot);
 #pragma unroll
             for (int j = 0; j < D; ++j) {
 #pragma clang fp contract(off)
-                if (Shape::kFused && n == static_cast<uint32_t>(Shape::kUnit)) s1[j] = fmaf(rad[j], cs[j], s1[j]);
+                if (Shape::kFused && n == static_cast<uint32_t>(Shape::kUnit)) s1[j] = fma(rad[j], cs[j], s1[j]);
                 else s1[j] += z[j];
-                s2[j] = fmaf(z[j], dot, s2[j]);
+                s2[j] = fma(z[j], dot, s2[j]);
             }
         }
     }
@@ -110,10 +111,10 @@ struct FedDraws {
 
 // Drawing wavefront w's side: its share of every chunk's slots, all their Philox chains side by side
 // (w: a number, or an integral constant, which places the slots at compile time).
-template <int D, int DRAW, class Wave>
-__device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, uint32_t r, Wave w, float *lane0)
+template <int D, int DRAW, typename Real, class Wave>
+__device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, uint32_t r, Wave w, Real *lane0)
 {
-    using Shape = SplitShape<D, DRAW>;
+    using Shape = SplitShape<D, DRAW, Real>;
     constexpr int kEach = Shape::kEach;
     const uint32_t N = P->N, M = P->M, T = static_cast<uint32_t>(P->T);
     const uint32_t k0 = static_cast<uint32_t>(P->seed), k1 = static_cast<uint32_t>(P->seed >> 32);
@@ -132,7 +133,7 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
         in_unit[i] = mine[i] ? slot / Shape::kBlocks : i ? in_unit[i ? i - 1 : 0] : 0u;
         in_block[i] = slot % Shape::kBlocks;
     }
-    float *dst = lane0;
+    Real *dst = lane0;
     for (uint64_t k = 0; k < chunks; ++k) {
         // each slot's block of the stream, its epoch, and whether a sample uses it
         uint32_t epoch[kEach], block[kEach];
@@ -158,20 +159,25 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
             all = all && used[i];
         }
         PhiloxRow row[Shape::kUnits > 1 ? kEach : 1];
-        float q[kEach][6];
+        Real q[kEach][6];
         auto draw = [&](int i) {
             const Words4 x = philox_block(row[Shape::kUnits > 1 ? i : 0], block[i], dom, k0, k1);
             const uint32_t xs[4] = {x.x0, x.x1, x.x2, x.x3};
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const float u1 = uniform_open01(xs[2 * e]), u2 = uniform_open01(xs[2 * e + 1]);
-                q[i][3 * e] = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
-                q[i][3 * e + 1] = __builtin_amdgcn_cosf(u2);
-                q[i][3 * e + 2] = __builtin_amdgcn_sinf(u2);
+                if constexpr (sizeof(Real) == 8) {
+                    q[i][3 * e] = sqrt(-2.0 * log(static_cast<double>(u1)));
+                    sincospi(2.0 * static_cast<double>(u2), &q[i][3 * e + 2], &q[i][3 * e + 1]);
+                } else {
+                    q[i][3 * e] = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
+                    q[i][3 * e + 1] = __builtin_amdgcn_cosf(u2);
+                    q[i][3 * e + 2] = __builtin_amdgcn_sinf(u2);
+                }
             }
         };
         auto put = [&](int i) {
-            float *o = dst + (w * kEach + i) * (Shape::kFloats * 64);
+            Real *o = dst + (w * kEach + i) * (Shape::kReals * 64);
             if constexpr (Shape::kFused) {
 #pragma unroll
                 for (int e = 0; e < 6; ++e) o[e * 64] = q[i][e];
@@ -209,12 +215,12 @@ __device__ __forceinline__ void draw_chunks(const InstanceDesc *__restrict__ P, 
 }
 
 // 64 replications per workgroup: a path wavefront and DRAW drawing ones.
-template <int D, bool FEAT, int DRAW>
+template <int D, bool FEAT, int DRAW, typename Real>
 __global__ __launch_bounds__(64 * (DRAW + 1)) void fw_paths_split_kernel(const InstanceDesc *__restrict__ P, RunBuffers B)
 {
     constexpr bool kLds = !FEAT && D >= 7;
-    using Shape = SplitShape<D, DRAW>;
-    __shared__ float sm_z[2 * Shape::kBuffer];
+    using Shape = SplitShape<D, DRAW, Real>;
+    __shared__ Real sm_z[2 * Shape::kBuffer];
     __shared__ uint64_t sm_feat[FEAT ? (D + 1) * 64 : 1];
     __shared__ uint32_t sm_sig[kLds ? (D + 1) * 64 : 1];
     __shared__ uint32_t sm_cnt[kLds ? (D + 1) * 64 : 1];
@@ -226,11 +232,11 @@ __global__ __launch_bounds__(64 * (DRAW + 1)) void fw_paths_split_kernel(const I
     const uint32_t rc = static_cast<uint32_t>(active ? r : R - 1);
     if (role != 0) {
         if constexpr (DRAW == 3) {
-            if (role == 1) draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 0>{}, sm_z + lane);
-            else if (role == 2) draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 1>{}, sm_z + lane);
-            else draw_chunks<D, DRAW>(P, rc, std::integral_constant<uint32_t, 2>{}, sm_z + lane);
+            if (role == 1) draw_chunks<D, DRAW, Real>(P, rc, std::integral_constant<uint32_t, 0>{}, sm_z + lane);
+            else if (role == 2) draw_chunks<D, DRAW, Real>(P, rc, std::integral_constant<uint32_t, 1>{}, sm_z + lane);
+            else draw_chunks<D, DRAW, Real>(P, rc, std::integral_constant<uint32_t, 2>{}, sm_z + lane);
         } else {
-            draw_chunks<D, DRAW>(P, rc, role - 1, sm_z + lane);
+            draw_chunks<D, DRAW, Real>(P, rc, role - 1, sm_z + lane);
         }
         return;
     }
@@ -240,8 +246,8 @@ __global__ __launch_bounds__(64 * (DRAW + 1)) void fw_paths_split_kernel(const I
         rec.c = sm_cnt + lane;
     }
     LaneResult res{0.0, kTauNone};
-    run_path<D, true, float, 0, uint32_t, FEAT, false>(P, B, rc, active, rec, res, sm_feat + lane,
-                                                       FedDraws<D, DRAW>{sm_z + lane, 1, Shape::kUnits});
+    run_path<D, true, Real, 0, uint32_t, FEAT, false>(P, B, rc, active, rec, res, sm_feat + lane,
+                                                       FedDraws<D, DRAW, Real>{sm_z + lane, 1, Shape::kUnits});
     if (!active) return;
     B.rec_y[r] = res.y;
     B.rec_tau[r] = res.tau;
@@ -254,14 +260,14 @@ __global__ __launch_bounds__(64 * (DRAW + 1)) void fw_paths_split_kernel(const I
 }
 
 // The kernel of width d among LO .. HI.
-template <int LO, int HI, bool FEAT, int DRAW>
+template <int LO, int HI, bool FEAT, int DRAW, typename Real = float>
 inline KernelFn choose_split(uint32_t d)
 {
     if constexpr (LO > HI) {
         return nullptr;
     } else {
-        if (d == static_cast<uint32_t>(LO)) return &fw_paths_split_kernel<LO, FEAT, DRAW>;
-        return choose_split<LO + 1, HI, FEAT, DRAW>(d);
+        if (d == static_cast<uint32_t>(LO)) return &fw_paths_split_kernel<LO, FEAT, DRAW, Real>;
+        return choose_split<LO + 1, HI, FEAT, DRAW, Real>(d);
     }
 }
 
@@ -269,5 +275,6 @@ inline KernelFn choose_split(uint32_t d)
 KernelFn paths_split_narrow(uint32_t d, int draw);       // d <= 16
 KernelFn paths_split_broad(uint32_t d, int draw);        // 17 <= d <= 32
 KernelFn paths_split_features(uint32_t d);               // with features, d <= 32; 3
+KernelFn paths_split_fp64(uint32_t d);                   // binary64, d <= 16; 3
 
 }  // namespace fw

@@ -143,19 +143,12 @@ def test_sqn_split(n, rows, b, bH, M, L, R, K, fp32, ckpt):
     assert a["pairs"].tolist() == [max(K // L - 1, 0)] * R
 
 
-@pytest.mark.parametrize("d,N,M,R,T,ckpt,features", [
-    (2, 2, 1, 1, 1, (), False), (3, 5, 1, 64, 40, (1, 40), False), (4, 9, 3, 65, 37, (7,), False), (5, 3, 1, 300, 25, (), True),
-    (7, 6, 1, 257, 30, (30,), False), (10, 11, 2, 130, 33, (2, 33), False), (10, 10, 1, 100, 200, (), True), (13, 2, 1, 70, 40, (), False),
-    (15, 7, 1, 64, 30, (3,), False), (17, 5, 2, 100, 31, (), False), (21, 6, 1, 90, 20, (), True), (27, 31, 1, 65, 20, (20,), False),
-    (30, 3, 1, 63, 20, (), False), (31, 8, 1, 129, 20, (), False), (32, 4, 1, 300, 20, (5,), False), (12, 3, 1, 49_000, 12, (), False)])
-def test_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt, features):
-    # against a lane per replication, which a context without room for the records takes: odd groups, halves
-    # of long groups, partial units, chunks across iterations, features
-    print(f"[one launch] paths d={d} N={N} M={M} R={R} T={T} features={features}", flush=True)
+def compare_split(d, N, M, R, T, ckpt, features=False, precision=sim.FP32):
+    print(f"[one launch] paths d={d} N={N} M={M} R={R} T={T} features={features} precision={precision}", flush=True)
     mu, sigma = workloads.diag_instance(15, d, d)
     p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, checkpoints=ckpt, gap_eps=0.05, cv_features=features,
                     cv_ref=-mu if features else None, w0=np.full(d, 0.5 / d) if R == 300 else None, instance_id=d,
-                    log_reps=(0, min(R, 8)))
+                    log_reps=(0, min(R, 8)), precision=precision)
 
     def run(ctx):
         ctx.run(p, R, T, 5)
@@ -171,6 +164,24 @@ def test_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt, features):
 
     a, b = both(run, records)
     same(a, b)
+
+
+@pytest.mark.parametrize("d,N,M,R,T,ckpt,features", [
+    (2, 2, 1, 1, 1, (), False), (3, 5, 1, 64, 40, (1, 40), False), (4, 9, 3, 65, 37, (7,), False), (5, 3, 1, 300, 25, (), True),
+    (7, 6, 1, 257, 30, (30,), False), (10, 11, 2, 130, 33, (2, 33), False), (10, 10, 1, 100, 200, (), True), (13, 2, 1, 70, 40, (), False),
+    (15, 7, 1, 64, 30, (3,), False), (17, 5, 2, 100, 31, (), False), (21, 6, 1, 90, 20, (), True), (27, 31, 1, 65, 20, (20,), False),
+    (30, 3, 1, 63, 20, (), False), (31, 8, 1, 129, 20, (), False), (32, 4, 1, 300, 20, (5,), False), (12, 3, 1, 49_000, 12, (), False)])
+def test_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt, features):
+    # against a lane per replication, which a context without room for the records takes: odd groups, halves
+    # of long groups, partial units, chunks across iterations, features
+    compare_split(d, N, M, R, T, ckpt, features)
+
+
+@pytest.mark.parametrize("d,N,M,R,T,ckpt", [
+    (1, 2, 1, 1, 1, ()), (1, 9, 2, 65, 37, (3, 37)), (2, 2, 1, 1000, 100, (100,)), (5, 7, 1, 64, 30, ()), (7, 6, 3, 300, 25, (25,)),
+    (9, 5, 1, 130, 20, ()), (10, 3, 1, 63, 40, (1,)), (13, 4, 1, 100, 20, ()), (15, 7, 2, 70, 20, (20,)), (16, 5, 1, 129, 20, ())])
+def test_binary64_paths_drawn_by_other_wavefronts(d, N, M, R, T, ckpt):
+    compare_split(d, N, M, R, T, ckpt, precision=sim.FP64)
 
 
 @pytest.mark.parametrize("n,M,b,bH,R", [(1, 1, 1, 1, 2), (60, 32, 1024, 300, 3), (1000, 25, 50, 300, 300), (1024, 4, 33, 1024, 2),
