@@ -556,7 +556,7 @@ int sim_run_sqn(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_t K, u
  * over many workgroups: every workgroup owns a 256-feature slice of w, of the gradient and of the
  * stored pairs, and the dot products that need the whole vector (the sampled rows' x_i'w, S'g and
  * Y'g, the new pair's products) are summed over the slices, in slice order. Where the device holds
- * the run's workgroups at once, a cooperative launch runs up to 4,096 iterations; otherwise there are
+ * the run's workgroups at once, a cooperative launch runs up to 4,096 iterations; otherwise, and under capture, there are
  * one to two launches per iteration and three more at the end of a window, with the same results bit
  * for bit. sim_run_sqn keeps one
  * workgroup per replication, which streams the stored pairs through a single compute unit; this

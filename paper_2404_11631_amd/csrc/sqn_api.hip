@@ -238,9 +238,13 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
     P.small = static_cast<double *>(q.ssmall.ptr);
     hipStream_t st = ctx->stream;
     HIP_TRY(ctx, hipEventRecord(q.ev0, st));
-    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots
+    // the cooperative form when it fits and the workspace limit leaves room for its exchange slots; under
+    // capture the launches, since a replay needs the slots cleared by a node of the graph and the host's
+    // check of the wait, which is made once, when the results are first read
+    hipStreamCaptureStatus captured = hipStreamCaptureStatusNone;
+    const bool eager = hipStreamIsCapturing(st, &captured) == hipSuccess && captured == hipStreamCaptureStatusNone;
     const size_t words = fw::sqn_split_run_bytes(A, P.W);
-    const bool one_launch = fw::sqn_split_run_fits(P, ctx->device) && ensure_spare(ctx, q.words, words);
+    const bool one_launch = eager && fw::sqn_split_run_fits(P, ctx->device) && ensure_spare(ctx, q.words, words);
     if (one_launch) {
         HIP_TRY(ctx, hipMemsetAsync(q.words.ptr, 0, words, st));
         fw::SqnSplitRun Q{};

@@ -2,6 +2,8 @@
 exchanging tagged words) against their launch-by-launch forms, record for record. The second is
 reached with a context whose memory cap leaves no room for the exchange slots, which a run
 allocates last."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -141,6 +143,44 @@ def test_sqn_split(n, rows, b, bH, M, L, R, K, fp32, ckpt):
     a, b2 = both(run, records)
     same(a, b2)
     assert a["pairs"].tolist() == [max(K // L - 1, 0)] * R
+
+
+def test_sqn_split_captured():
+    # a captured run is replayed with eager runs in between: every replay leaves the eager run's iterates
+    rng = np.random.default_rng(6)
+    X, z = (rng.random((400, 300)) < 0.1).astype(np.uint8), rng.integers(0, 2, 400).astype(np.uint8)
+    ctx, vp = sim.Sim(0), ctypes.c_void_p
+    stream, graph, replay = vp(), vp(), vp()
+
+    def hip(name, *args):                     # the runtime that the library is linked with
+        assert getattr(ctx.L, name)(*args) == 0, name
+
+    def run(seed):
+        ctx.run_sqn(2, 40, seed, L=4, M=5, b=20, bH=40, checkpoints=(), split=True)
+
+    try:
+        hip("hipStreamCreate", ctypes.byref(stream))
+        ctx.set_stream(stream.value)
+        ctx.sqn_load(X, z)
+        run(6)
+        want, view = ctx.sqn_paths()["w"], sim.SimSqnView()
+        ctx._check(ctx.L.sim_sqn_paths(ctx.h, ctypes.byref(view)))
+        hip("hipStreamBeginCapture", stream, 1)
+        run(6)
+        hip("hipStreamEndCapture", stream, ctypes.byref(graph))
+        hip("hipGraphInstantiate", ctypes.byref(replay), graph, None, None, ctypes.c_size_t(0))
+        for k in range(3):
+            print(f"[one launch] sqn graph replay {k}", flush=True)
+            run(7 + k)
+            assert not np.array_equal(ctx.sqn_paths()["w"], want)
+            hip("hipGraphLaunch", replay, stream)
+            hip("hipStreamSynchronize", stream)
+            w = ctx._copy(view.w, np.float64, 2 * view.ld).reshape(2, view.ld)[:, :300]
+            assert np.array_equal(w, want)
+        hip("hipGraphExecDestroy", replay)
+        hip("hipGraphDestroy", graph)
+    finally:
+        ctx.close()
 
 
 def compare_split(d, N, M, R, T, ckpt, features=False, precision=sim.FP32):
