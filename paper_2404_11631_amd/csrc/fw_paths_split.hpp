@@ -88,7 +88,7 @@ struct FedDraws {
 #pragma unroll
             for (int j = 0; j < D; ++j) {
 #pragma clang fp contract(off)
-                if (Shape::kFused && n == static_cast<uint32_t>(Shape::kUnit)) s1[j] = fma(rad[j], cs[j], s1[j]);
+                if (Shape::kFused && (kFuseRest<D> || n == static_cast<uint32_t>(Shape::kUnit))) s1[j] = fma(rad[j], cs[j], s1[j]);
                 else s1[j] += z[j];
                 s2[j] = fma(z[j], dot, s2[j]);
             }

@@ -91,3 +91,18 @@ def test_one_replication_per_wavefront(ctx, d, N, M):
     for r in range(3):
         parity.check_rep(op, g, r, 70, oracle.U32, decisions=g["decisions"][:, r])
     assert list(st.decision_total)[:d + 1] == g["cnt"].sum(axis=1).tolist()
+
+
+@pytest.mark.parametrize("d,N,R,T,features,mean", [
+    (1, 7, 8192, 3000, False, "0x1.5aa84d8c3f40ep-6"), (2, 3, 60_000, 1500, False, "-0x1.3579d6ece3074p-1"),
+    (2, 3, 60_000, 1500, True, "-0x1.3579d6ece3074p-1"), (10, 5, 8192, 3000, False, "-0x1.cca8b498cd351p-1"),
+    (10, 5, 8192, 3000, True, "-0x1.cca8b498cd351p-1"), (10, 5, 60_000, 1500, False, "-0x1.cca5956864ad8p-1"),
+    (2, 5, 1000, 93_000, False, "-0x1.46fc73d6f19b0p-1"), (10, 3, 1000, 93_000, False, "-0x1.c9ed2be147d08p-1")])
+def test_partial_group_decisions(ctx, d, N, R, T, features, mean):
+    # N past a whole group of Philox blocks, at the widths whose last samples fuse into s1 as the others do:
+    # one rounding more there decides a near tie in ~1e7 iterations the other way, which shows in the mean of
+    # Y. The values are those of the kernels before there was one for every width.
+    print(f"[widths] partial group d={d} N={N} R={R} T={T} features={features}", flush=True)
+    mu, sigma = workloads.diag_instance(1, 0, d)
+    ctx.run(sim.Problem(mu=mu, sigma=sigma, N=N, checkpoints=(T,), cv_features=features, cv_ref=-mu if features else None), R, T, 5)
+    assert ctx.stats().mean.hex() == mean
