@@ -36,7 +36,8 @@ bool paths_split_applies(const InstanceDesc &desc, bool fp64, bool sched, int de
 {
     if (sched || desc.noise != 0 || desc.d > (fp64 ? 16u : 32u) || desc.T > kMaxNarrowT) return false;
     const bool own_kernel = desc.d <= 6 || desc.d == 8 || desc.d == 10 || desc.d == 12 || desc.d == 16;    // in binary64
-    const uint64_t most = fp64 ? (!own_kernel ? kSplitReps64Generic : desc.d <= 8 ? kSplitReps64 : kSplitReps64Wide)
+    const bool odd = desc.d == 5 || (desc.d == 3 && desc.N > 4);
+    const uint64_t most = fp64 ? (!own_kernel ? kSplitReps64Generic : desc.d <= 8 && !odd ? kSplitReps64 : kSplitReps64Wide)
                                : (desc.d == 2 ? kSplitRepsTwo : kSplitReps);
     if (desc.R > most || (fp64 ? (desc.flags & 4u) != 0 : desc.d < 2)) return false;
     int cus = 0, per_cu = 0;

@@ -80,16 +80,54 @@ __device__ __forceinline__ Block4<Real> block_of_row(const PhiloxRow &row, uint3
 
 constexpr int gcd_const(int a, int b) { return b == 0 ? a : gcd_const(b, a % b); }
 
+// The widths of the named workloads, and the small ones.
+template <int D>
+constexpr bool kWorkloadWidth = D <= 6 || D == 8 || D == 10 || D == 12 || D == 16;
+
 // Whether a sample's term of s1 fuses with the product that forms it (radius times cosine or sine). It
-// does in the whole groups of the widths that always had an exact kernel, at 1, 2, 6 and 10 assets in the
+// does in the whole groups of the named workloads' widths, at 1, 2, 6 and 10 assets in the
 // samples of a last, partial group too, and under t noise with the product by the scale; elsewhere the
 // product is rounded first, as the generic kernels' cursor does. A width thus keeps its decisions,
 // whichever kernel runs it (a rounding more or less in s1 decides a near tie the other way: of 1e6
 // replications of d = 10, N = 5, 600 iterations, the variance moved by 4e-7 of itself).
 template <int D>
-constexpr bool kFuseSum = D <= 6 || D == 8 || D == 10 || D == 12 || D == 16;
+constexpr bool kFuseSum = kWorkloadWidth<D>;
 template <int D>
 constexpr bool kFuseRest = kFuseSum<D> && (D == 1 || 4 / gcd_const(D, 4) == 2);
+
+// How an exact-width Gaussian kernel runs its samples. One table for all widths costs some of them up to
+// 15 %, by registers (wavefronts per SIMD) and, with a wavefront per SIMD, by where the sample loop's code
+// lies: its instructions are 8 bytes for the most part, a few of 4, and the loop is 3 to 10 % slower where
+// the 8-byte ones straddle 8-byte boundaries. ms at 65,000 replications, N = 60, with the code before the
+// loop padded to 0 | 4 bytes past a multiple of 8: binary32 d = 2 3.78 | 4.08, d = 8 3.53 | 3.83, d = 16
+// 3.83 | 3.48; binary64 d = 5 2.75 | 2.71; 64-bit signature, d = 4, N = 12, 1,000 replications 220 | 207.
+// Drawn at once, a group holds more normals and has its Philox chains side by side: binary64 d = 10,
+// N = 9, 65,000 replications 2.76 against 2.93 ms; binary32 d = 3, N = 9, 5.02 against 4.84.
+struct PathForm {
+    bool at_once;    // a group's blocks are drawn before its first sample (or each as the samples reach it)
+    bool several;    // binary32: several short groups at a time
+    int start;       // the code before the sample loop is padded to this many bytes past a multiple of 8, or -1
+};
+
+template <int D, typename Real, typename WS, int NOISE, bool FEAT>
+constexpr PathForm path_form()
+{
+    if (NOISE != 0) return {false, !FEAT, -1};
+    if (FEAT) return {false, false, D <= 2 ? 0 : -1};
+    if (sizeof(Real) == 8 && sizeof(WS) == 8) return {false, false, -1};
+    if (sizeof(Real) == 8)
+        return {D == 2 || D == 3 || D == 5 || D >= 10, false, D == 3 || D == 5 || D == 6 || D == 8 ? 4 : 0};
+    if (sizeof(WS) == 8) return {D == 10, D == 8, D == 4 || D == 5 || D == 10 || D == 16 ? 4 : 0};
+    if (!kWorkloadWidth<D>) return {false, true, -1};
+    return {D == 1 || D == 6, D == 4 || D == 8, D == 10 || D == 16 ? 4 : 0};
+}
+
+template <int START>
+__device__ __forceinline__ void code_start()
+{
+    if constexpr (START == 0) asm volatile(".p2align 3");
+    if constexpr (START == 4) asm volatile(".p2align 3\n\ts_nop 0");
+}
 
 // The per-replication records a run accumulates: signature S_j and decision counts. With a 32-bit
 // signature they live in LDS, [category][thread], each thread its own column (category 0 the origin,
@@ -309,29 +347,40 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
         if constexpr (Feed::kFed) {
             feed.samples(N, v, s1, s2);
         } else if constexpr (EXACT) {
-            // groups of G samples hold a whole number of Philox blocks: static packing. Blocks are
-            // drawn as the samples reach them, so a wide instance holds one sample and a part.
-            // Narrow binary32 instances take several groups at a time, for enough independent
-            // Philox chains (4 to 6 blocks) to cover a chain's latency at few wavefronts per SIMD.
+            // groups of G samples hold a whole number of Philox blocks: static packing. Drawn as the
+            // samples reach them, blocks leave a wide instance to hold one sample and a part. Several
+            // groups at a time have enough independent Philox chains (4 to 6 blocks) to cover a
+            // chain's latency at few wavefronts per SIMD.
             constexpr int G = 4 / gcd_const(D, 4);
             constexpr int NB = G * D / 4;
-            constexpr int MUL = sizeof(Real) == 4 && !FEAT ? (NB == 1 ? 4 : NB <= 3 ? 2 : 1) : 1;
+            constexpr PathForm F = path_form<D, Real, WS, NOISE, FEAT>();
+            constexpr int MUL = F.several && sizeof(Real) == 4 ? (NB == 1 ? 4 : NB <= 3 ? 2 : 1) : 1;
             PhiloxRow row{};
             if constexpr (std::is_same<Real, float>::value) row = philox_row(epoch, r, k0);
             // the next samples from block b0 on: all GS of them, or with GS = 0 the first n of a group
             auto group = [&](uint32_t b0, uint32_t n, auto size) {
                 constexpr int GS = decltype(size)::value ? decltype(size)::value : G;
                 Real z[GS * D];
+                auto block = [&](int b) {
+                    const Block4<Real> q = block_of_row<Real>(row, b0 + b, epoch, r, dom, k0, k1);
+                    z[4 * b + 0] = q.z[0];
+                    z[4 * b + 1] = q.z[1];
+                    z[4 * b + 2] = q.z[2];
+                    z[4 * b + 3] = q.z[3];
+                };
+                if constexpr (F.at_once) {
+#pragma unroll
+                    for (int b = 0; b < GS * D / 4; ++b) {
+                        if (decltype(size)::value || static_cast<uint32_t>(b) < (n * D + 3) / 4) block(b);
+                        else z[4 * b + 0] = z[4 * b + 1] = z[4 * b + 2] = z[4 * b + 3] = Real(0);
+                    }
+                }
 #pragma unroll
                 for (int s = 0; s < GS; ++s) {
                     if (decltype(size)::value || static_cast<uint32_t>(s) < n) {
+                        if constexpr (!F.at_once) {
 #pragma unroll
-                        for (int b = (s * D + 3) / 4; b < ((s + 1) * D + 3) / 4; ++b) {
-                            const Block4<Real> q = block_of_row<Real>(row, b0 + b, epoch, r, dom, k0, k1);
-                            z[4 * b + 0] = q.z[0];
-                            z[4 * b + 1] = q.z[1];
-                            z[4 * b + 2] = q.z[2];
-                            z[4 * b + 3] = q.z[3];
+                            for (int b = (s * D + 3) / 4; b < ((s + 1) * D + 3) / 4; ++b) block(b);
                         }
                         if constexpr (FEAT && NOISE == 1) {
 #pragma unroll
@@ -351,8 +400,11 @@ __device__ __forceinline__ void run_path(const InstanceDesc *__restrict__ P, con
             };
             const uint32_t full = N / G, rem = N % G;
             uint32_t gi = 0;
-            if constexpr (MUL > 1)
+            if constexpr (MUL > 1) {
+                code_start<F.start>();
                 for (; gi + MUL <= full; gi += MUL) group(gi * NB, 0, std::integral_constant<int, MUL * G>{});
+            }
+            code_start<F.start>();
             for (; gi < full; ++gi) group(gi * NB, 0, std::integral_constant<int, G>{});
             if (rem) group(full * NB, rem, std::integral_constant<int, 0>{});
         } else {

@@ -111,8 +111,10 @@ constexpr uint64_t kSplitReps = 49152;
 constexpr uint64_t kSplitRepsTwo = 32768;      // d = 2
 // Binary64 (the draws are a larger share): at 1,000, 32,768, 49,152 and 65,536 replications d = 2 2.6, 1.6,
 // 1.1, 0.9; d = 8 2.8, 1.6, 1.2, 1.0; d = 10 2.2, 1.3, 1.0; against the generic kernel, d = 9 3.5, 2.1, 1.6, 1.2.
+// At 3 and 5 assets a group is four samples, the blocks of which don't divide among three wavefronts: at 40,000
+// d = 3, N = 3 1.1, N = 5 0.87, N = 13 0.95; d = 5, N = 3 0.90, N = 60 0.93; at 32,768 1.0 and more.
 constexpr uint64_t kSplitReps64 = 49152;       // widths up to 8 with a kernel of their own
-constexpr uint64_t kSplitReps64Wide = 32768;   // the same from 10 on
+constexpr uint64_t kSplitReps64Wide = 32768;   // the same from 10 on, 5, and 3 with more than one group
 constexpr uint64_t kSplitReps64Generic = 65536;
 // Seven drawing wavefronts instead of three up to a workgroup per compute unit: at 1,000 replications d = 8
 // 1.15, d = 14 1.6, d = 22 1.2, d = 28 1.4 times as fast; d = 5 0.9 and with features 1.0 (the path sets
