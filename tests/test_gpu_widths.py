@@ -106,3 +106,57 @@ def test_partial_group_decisions(ctx, d, N, R, T, features, mean):
     mu, sigma = workloads.diag_instance(1, 0, d)
     ctx.run(sim.Problem(mu=mu, sigma=sigma, N=N, checkpoints=(T,), cv_features=features, cv_ref=-mu if features else None), R, T, 5)
     assert ctx.stats().mean.hex() == mean
+
+
+@pytest.mark.parametrize("d,limit,precision", [(2, 32_768, sim.FP32), (3, 49_152, sim.FP32), (10, 49_152, sim.FP32),
+                                               (3, 32_768, sim.FP64), (4, 49_152, sim.FP64), (10, 32_768, sim.FP64)])
+def test_split_form_ends(d, limit, precision):
+    # the split form leaves records, which a run that keeps none has a buffer for: up to `limit` replications,
+    # so the tests past it reach the kernels of one lane per replication
+    mu, sigma = workloads.diag_instance(16, d, d)
+    used = []
+    for R in (limit, limit + 1):
+        print(f"[widths] form d={d} R={R} precision={precision}", flush=True)
+        s = sim.Sim(0)
+        try:
+            s.run(sim.Problem(mu=mu, sigma=sigma, N=5, precision=precision), R, 2, 1)
+            used.append(s.workspace_bytes())
+        finally:
+            s.close()
+    assert used[0] - used[1] > limit * (8 + 4 * (d + 2)) - 65_536
+
+
+@pytest.mark.parametrize("features", [False, True])
+@pytest.mark.parametrize("d,N,M", [(1, 6, 1), (2, 5, 2), (6, 3, 1), (7, 6, 2), (10, 5, 1), (13, 7, 1), (16, 3, 2), (27, 7, 1), (31, 3, 1),
+                                   (32, 5, 2)])
+def test_one_lane_per_replication(ctx, d, N, M, features):
+    # past the split form: the last replications (the last alone in its workgroup) against the oracle, and
+    # the records of all against the statistics
+    R, T = 49_153, 24
+    print(f"[widths] one lane d={d} N={N} M={M} features={features}", flush=True)
+    mu, sigma = workloads.diag_instance(16, d, d)
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, checkpoints=(5, T), gap_eps=0.05, w0=np.full(d, 0.5 / d), instance_id=d,
+                    keep_paths=True, log_reps=(R - 4, 4), cv_features=features, cv_ref=-mu if features else None)
+    ctx.run(p, R, T, 21 + d)
+    st, g = ctx.stats(), ctx.paths()
+    P = parity.oracle_problem(p, 21 + d)
+    for r in range(R - 4, R):
+        parity.check_rep(P, g, r, T, oracle.U32, decisions=g["decisions"][:, r - (R - 4)])
+    assert (g["cnt"].sum(axis=0) == T).all()
+    assert list(st.decision_total)[:d + 1] == g["cnt"].sum(axis=1, dtype=np.uint64).tolist()
+    hit = g["tau"] != oracle.TAU_NONE
+    assert st.tau_count == hit.sum() and st.min == g["y"].min() and st.max == g["y"].max()
+    # a plain sum of R values is within R roundings of the exact one
+    assert st.mean == pytest.approx(g["y"].mean(), rel=R * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("d,N", [(2, 5), (7, 6), (10, 10), (13, 5), (27, 7), (32, 3)])
+def test_one_lane_features_same_paths(ctx, d, N):
+    mu, sigma = workloads.diag_instance(12, d, d)
+    kw = dict(mu=mu, sigma=sigma, N=N, checkpoints=(30,), keep_paths=True)
+    ctx.run(sim.Problem(**kw), 49_153, 30, 5)
+    a = ctx.paths()
+    ctx.run(sim.Problem(cv_features=True, cv_ref=-mu, **kw), 49_153, 30, 5)
+    b = ctx.paths()
+    for f in ("y", "f_ckpt", "cnt", "wsum", "tau"):
+        assert np.array_equal(a[f], b[f]), f
