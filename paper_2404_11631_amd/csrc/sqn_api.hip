@@ -189,7 +189,8 @@ static int sqn_split_sequenced(sim_ctx *ctx, const fw::SqnSplit &P)
     return lrc ? set_err(ctx, SIM_EDEVICE, "SQN split launch failed: %s", hipGetErrorString(hipGetLastError())) : SIM_OK;
 }
 
-// Waits for the last run. One in one launch whose wait gave up is run again launch by launch.
+// Waits for the last run. One in one launch whose wait gave up is run again launch by launch; until that
+// has been enqueued whole, its statistics keep their mark and the run stays unsettled.
 static int sqn_settle(sim_ctx *ctx)
 {
     SqnState &q = ctx->sqn;
@@ -197,14 +198,17 @@ static int sqn_settle(sim_ctx *ctx)
     if (!q.unsettled) return SIM_OK;
     double count = 0.0;
     HIP_TRY(ctx, hipMemcpy(&count, static_cast<const double *>(q.stats.ptr) + 4, sizeof(count), hipMemcpyDeviceToHost));
-    q.unsettled = false;
-    if (count >= 0.0) return SIM_OK;
+    if (count >= 0.0) {
+        q.unsettled = false;
+        return SIM_OK;
+    }
     q.split.A.fail = nullptr;
     HIP_TRY(ctx, hipEventRecord(q.ev0, ctx->stream));
     if (int rc = sqn_split_sequenced(ctx, q.split)) return rc;
     const sim_sqn_params p = q.params;
     if (int rc = sqn_finish(ctx, &p, q.split.A, q.R, q.K)) return rc;
     HIP_TRY(ctx, hipEventSynchronize(q.ev2));
+    q.unsettled = false;
     return SIM_OK;
 }
 

@@ -189,3 +189,24 @@ def test_wait_gives_up_in_a_launch(emu, kind, missing):
     got, cooperative, launches = run(lib, kind, missing=missing)
     same(got, want)
     assert cooperative and launches > by_launch
+
+
+@pytest.mark.parametrize("at", [0, 2])
+@pytest.mark.parametrize("kind", KINDS)
+def test_repeat_fails(emu, kind, at):
+    # the repeat of a run that gave up fails (its ordinary launch `at`): no result of the abandoned run is
+    # handed out, then or later, and once launches work again the results are right or still an error
+    lib = emu()
+    want, _ = wanted(lib, kind)
+    set_faults(lib, kind, failed=0)
+    ctx = sim.Sim(0)
+    try:
+        start(kind, ctx)
+        lib.emu_faults()[0].fail_launch = lib.emu_faults()[0].launches + at
+        for read in (stats, paths, stats):
+            with pytest.raises(sim.SimError):
+                read(kind, ctx)
+        lib.emu_faults()[0].fail_launch = -1
+        same(records(kind, ctx), want)
+    finally:
+        ctx.close()
