@@ -25,6 +25,15 @@
 
 namespace fw {
 
+// A cooperative launch of kernel fn: 0, or kRunRefused. The occupancy that the fit rules ask for is the
+// whole device's; the stream may hold less of it.
+static inline int launch_cooperative(const void *fn, dim3 grid, int threads, void **args, size_t lds, hipStream_t s)
+{
+    if (hipLaunchCooperativeKernel(fn, grid, dim3(threads), args, static_cast<unsigned>(lds), s) == hipSuccess) return 0;
+    (void)hipGetLastError();                            // or the next launch's check would report it
+    return kRunRefused;
+}
+
 #ifndef FW_POLL_LIMIT
 #define FW_POLL_LIMIT (1u << 20)
 #endif

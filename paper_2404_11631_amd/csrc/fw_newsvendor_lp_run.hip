@@ -461,9 +461,7 @@ int launch_nv_lp_run(const NvLpArgs &A, const NvLpRunArgs &Q, hipStream_t s)
     void *args[] = {&a, &q};
     bool alds;
     const size_t lds = lp_run_lds(A.n, A.M, alds);
-    if (hipLaunchCooperativeKernel(lp_run_fn<1>(A.M, alds), dim3(A.nwg + 1, A.R), dim3(kNvBlock), args,
-                                   static_cast<unsigned>(lds), s) != hipSuccess)
-        return -1;
+    if (int rc = launch_cooperative(lp_run_fn<1>(A.M, alds), dim3(A.nwg + 1, A.R), kNvBlock, args, lds, s)) return rc;
     hipLaunchKernelGGL(nv_lp_log_kernel, dim3(static_cast<uint32_t>(Q.t1 - Q.t0), A.R), dim3(64), 0, s, A, Q);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -213,9 +213,7 @@ int launch_nv_run(const NvArgs &A, const NvRunArgs &Q, hipStream_t s)
     NvArgs a = A;
     NvRunArgs q = Q;
     void *args[] = {&a, &q};
-    if (hipLaunchCooperativeKernel(nv_run_fn((A.S + A.P - 1) / A.P), dim3(A.nwg, A.R), dim3(kNvBlock), args, 0, s) !=
-        hipSuccess)
-        return -1;
+    if (int rc = launch_cooperative(nv_run_fn((A.S + A.P - 1) / A.P), dim3(A.nwg, A.R), kNvBlock, args, 0, s)) return rc;
     const RunLog L{Q.gx_log, Q.best_log, A.nwg, A.R, A.n, A.C, A.gap_eps, Q.t0, A.T, Q.fail, A.dec, A.tau, A.cnt};
     return launch_run_log(L, Q.t1 - Q.t0, s);
 }

@@ -761,10 +761,7 @@ int launch_sqn_split_run(const SqnSplit &P, const SqnSplitRun &Q, hipStream_t s)
     SqnSplit p = P;
     SqnSplitRun q = Q;
     void *args[] = {&p, &q};
-    return hipLaunchCooperativeKernel(run_fn(P), dim3(P.W, P.A.R), dim3(kSplitThreads), args,
-                                      static_cast<unsigned>(run_lds(P)), s) == hipSuccess
-               ? 0
-               : -1;
+    return launch_cooperative(run_fn(P), dim3(P.W, P.A.R), kSplitThreads, args, run_lds(P), s);
 }
 
 }  // namespace fw

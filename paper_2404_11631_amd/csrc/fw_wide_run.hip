@@ -362,8 +362,7 @@ int launch_wide_run(const WideArgs &A, const WideRunArgs &Q, hipStream_t s)
     WideArgs a = A;
     WideRunArgs q = Q;
     void *args[] = {&a, &q};
-    if (hipLaunchCooperativeKernel(wide_run_fn(A.N, A.nwg), dim3(A.nwg, A.R), dim3(kWideBlock), args, 0, s) != hipSuccess)
-        return -1;
+    if (int rc = launch_cooperative(wide_run_fn(A.N, A.nwg), dim3(A.nwg, A.R), kWideBlock, args, 0, s)) return rc;
     const RunLog L{Q.gw_log, Q.best_log, A.nwg, A.R, A.d, 1.0f, A.gap_eps, Q.t0, A.T, Q.fail, A.dec, A.tau, A.cnt};
     return launch_run_log(L, Q.t1 - Q.t0, s);
 }

@@ -90,7 +90,7 @@ inline size_t nv_run_bytes(uint64_t R, uint32_t nwg, uint64_t T)
 }
 
 bool nv_run_fits(uint32_t nwg, uint32_t R, uint32_t S, uint32_t P, int device);
-int launch_nv_run(const NvArgs &A, const NvRunArgs &Q, hipStream_t s);
+int launch_nv_run(const NvArgs &A, const NvRunArgs &Q, hipStream_t s);         // kRunRefused: the runtime would not
 
 // ---- Algorithm 2 over X = {A x <= C, x >= 0} with M resource rows (Eq. (7)) --------------------
 // threads of the subproblem workgroup (one per replication): few products leave a pricing pass
@@ -184,7 +184,7 @@ int nv_lp_sequence(uint64_t M, uint64_t T, uint32_t n_ckpt, const uint64_t *chec
 }
 
 bool nv_lp_run_fits(const NvLpArgs &A, int device);
-int launch_nv_lp_run(const NvLpArgs &A, const NvLpRunArgs &Q, hipStream_t s);
+int launch_nv_lp_run(const NvLpArgs &A, const NvLpRunArgs &Q, hipStream_t s);  // kRunRefused: the runtime would not
 // Iteration t's gradient at x_t; with fold_prev it first moves x to x_t = x_{t-1} + gamma (s - x_{t-1})
 // with the vertex the previous subproblem launch recorded.
 int launch_nv_lp_gradient(const NvLpArgs &A, uint64_t t, uint32_t epoch, bool fold_prev, hipStream_t s);

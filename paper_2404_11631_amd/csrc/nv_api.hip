@@ -90,7 +90,9 @@ int nv_enqueue(sim_ctx *ctx, NvState &w, bool one_launch)
         while (Q.t1 < T) {
             Q.t0 = Q.t1;
             Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kRunSteps);
-            if (fw::launch_nv_run(A, Q, st))
+            const int rc = fw::launch_nv_run(A, Q, st);
+            if (rc == fw::kRunRefused) return nv_enqueue(ctx, w, false);
+            if (rc)
                 return set_err(ctx, SIM_EDEVICE, "newsvendor launch failed at t=%llu", (unsigned long long)Q.t0);
             for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
                 if (fw::launch_nv_cost(A, 2.0 / (static_cast<double>(Q.t1) * static_cast<double>(Q.t1 + 1)), ck, st))
@@ -174,7 +176,9 @@ int nv_lp_enqueue(sim_ctx *ctx, NvLpState &w, bool one_launch)
         while (Q.t1 < T) {
             Q.t0 = Q.t1;
             Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kLpRunSteps);
-            if (fw::launch_nv_lp_run(A, Q, st))
+            const int lrc = fw::launch_nv_lp_run(A, Q, st);
+            if (lrc == fw::kRunRefused) return nv_lp_enqueue(ctx, w, false);
+            if (lrc)
                 return set_err(ctx, SIM_EDEVICE, "newsvendor launch failed at t=%llu", (unsigned long long)Q.t0);
             for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
                 if (int rc = cost(ck)) return rc;

@@ -12,4 +12,8 @@ namespace fw {
 constexpr uint32_t kRunLine = 16;
 constexpr uint32_t kRunSteps = 1024;            // iterations per launch at most (the length of the logs)
 
+// What a launcher of a cooperative run returns when the runtime refuses the launch; the host then takes the
+// launch-by-launch form from the start.
+constexpr int kRunRefused = 1;
+
 }  // namespace fw

@@ -255,15 +255,19 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
         Q.words = static_cast<uint64_t *>(q.words.ptr);
         Q.fail = reinterpret_cast<uint32_t *>(static_cast<char *>(q.words.ptr) + words - sizeof(uint64_t));
         P.A.fail = Q.fail;
-        for (Q.k0 = 1; Q.k0 <= K; Q.k0 = Q.k1) {
+        bool refused = false;
+        for (Q.k0 = 1; Q.k0 <= K && !refused; Q.k0 = Q.k1) {
             Q.k1 = std::min(K + 1, Q.k0 + fw::kSqnRunSteps);
-            if (fw::launch_sqn_split_run(P, Q, st))
-                return set_err(ctx, SIM_EDEVICE, "SQN split launch failed: %s", hipGetErrorString(hipGetLastError()));
+            refused = fw::launch_sqn_split_run(P, Q, st) != 0;
         }
-        if (int rc2 = sqn_finish(ctx, p, P.A, R, K)) return rc2;
-        q.split = P;
-        q.unsettled = true;
-        return SIM_OK;
+        if (!refused) {
+            if (int rc2 = sqn_finish(ctx, p, P.A, R, K)) return rc2;
+            q.split = P;
+            q.unsettled = true;
+            return SIM_OK;
+        }
+        P.A.fail = nullptr;
+        HIP_TRY(ctx, hipEventRecord(q.ev0, st));
     }
     if (int rc2 = sqn_split_sequenced(ctx, P)) return rc2;
     return sqn_finish(ctx, p, A, R, K);

@@ -151,6 +151,6 @@ inline size_t sqn_split_run_bytes(const SqnArgs &A, uint32_t W)
 }
 
 bool sqn_split_run_fits(const SqnSplit &P, int device);
-int launch_sqn_split_run(const SqnSplit &P, const SqnSplitRun &Q, hipStream_t s);
+int launch_sqn_split_run(const SqnSplit &P, const SqnSplitRun &Q, hipStream_t s);   // kRunRefused: the runtime would not
 
 }  // namespace fw

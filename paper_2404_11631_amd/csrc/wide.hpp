@@ -136,7 +136,7 @@ int launch_wide_step(const WideArgs &A, uint64_t t, hipStream_t s);
 // f(w) at w = c S into fval[slot][r].
 int launch_wide_objective(const WideArgs &A, double c, uint32_t slot, hipStream_t s);
 bool wide_run_fits(uint32_t nwg, uint32_t R, uint32_t N, int device);
-int launch_wide_run(const WideArgs &A, const WideRunArgs &Q, hipStream_t s);
+int launch_wide_run(const WideArgs &A, const WideRunArgs &Q, hipStream_t s);   // kRunRefused: the runtime would not
 // Cross-replication statistics of Y and of the n_ckpt checkpoints into stats.
 int launch_wide_finalize(const WideArgs &A, uint32_t n_ckpt, hipStream_t s);
 

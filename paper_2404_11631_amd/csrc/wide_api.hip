@@ -114,7 +114,9 @@ int wide_enqueue(sim_ctx *ctx, WideState &w, const uint32_t *n_schedule, uint32_
         while (Q.t1 < T) {
             Q.t0 = Q.t1;
             Q.t1 = std::min(ck < nc ? p.checkpoints[ck] : T, Q.t0 + fw::kRunSteps);
-            if (fw::launch_wide_run(A, Q, st))
+            const int lrc = fw::launch_wide_run(A, Q, st);
+            if (lrc == fw::kRunRefused) return wide_enqueue(ctx, w, n_schedule, Nmax, false);
+            if (lrc)
                 return set_err(ctx, SIM_EDEVICE, "wide launch failed at t=%llu", (unsigned long long)Q.t0);
             for (; ck < nc && p.checkpoints[ck] == Q.t1; ++ck)
                 if (int rc = objective(2.0 / (static_cast<double>(Q.t1) * static_cast<double>(Q.t1 + 1)), ck)) return rc;

@@ -210,3 +210,13 @@ def test_repeat_fails(emu, kind, at):
         same(records(kind, ctx), want)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("kind,refuse", LAUNCHES)
+def test_launch_refused(emu, kind, refuse):
+    # a cooperative launch that the runtime refuses, the first or a later one: the launch-by-launch form
+    lib = emu()
+    want, by_launch = wanted(lib, kind)
+    got, cooperative, launches = run(lib, kind, refuse=refuse)
+    same(got, want)
+    assert cooperative == refuse + 1 and launches >= by_launch
