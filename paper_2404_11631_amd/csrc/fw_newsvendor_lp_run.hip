@@ -447,7 +447,8 @@ bool nv_lp_run_fits(const NvLpArgs &A, int device)
     bool alds;
     const size_t lds = lp_run_lds(A.n, A.M, alds);
     const void *fn = lp_run_fn<1>(A.M, alds);
-    if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess) {
+    // the form's largest size, not this run's: the attribute is the function's, for every context and thread
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLpRunLds)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }

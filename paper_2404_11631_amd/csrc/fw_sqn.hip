@@ -916,9 +916,11 @@ int launch_sqn_run(const SqnArgs &A, hipStream_t s)
                                        : (two   ? &sqn_run_kernel<1, double, true>
                                           : one ? &sqn_run_kernel<1, double, false>
                                                 : &sqn_run_kernel<2, double, false>);
+    // at most kLdsOfTwo (74,496 bytes and the rows that fit, at the largest n, b and M); the attribute is set to
+    // that, not to this run's bytes: it is the function's, for every context and thread
     const size_t lds = two ? run_lds(nullptr, A).bytes : 0;
-    if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           static_cast<int>(lds)) != hipSuccess)
+    if (two && hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   static_cast<int>(kLdsOfTwo)) != hipSuccess)
         return -1;
     const uint32_t threads = two ? kRunBlock / 2 : kRunBlock;
     hipLaunchKernelGGL(fn, dim3(A.R), dim3(threads), lds, s, A);

@@ -749,7 +749,8 @@ bool sqn_split_run_fits(const SqnSplit &P, int device)
         return false;
     const size_t lds = run_lds(P);
     if (lds > kSqnLdsPerCu) return false;
-    if (hipFuncSetAttribute(run_fn(P), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess) {
+    // the form's largest size, not this run's: the attribute is the function's, for every context and thread
+    if (hipFuncSetAttribute(run_fn(P), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kSqnLdsPerCu)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }

@@ -110,7 +110,7 @@ def start(kind, ctx, R=1, big=False):
         rng = np.random.default_rng(3)
         n = 520 if big else 300
         ctx.sqn_load((rng.random((60, n)) < 0.1).astype(np.uint8), rng.integers(0, 2, 60).astype(np.uint8))
-        ctx.run_sqn(R, 12, 5, L=2, M=3, b=5, bH=7, checkpoints=(3, 8), split=True)
+        ctx.run_sqn(R, 12, 5, L=2, M=3, b=20 if big else 5, bH=7, checkpoints=(3, 8), split=True)
 
 
 def stats(kind, ctx):
@@ -220,3 +220,31 @@ def test_launch_refused(emu, kind, refuse):
     got, cooperative, launches = run(lib, kind, refuse=refuse)
     same(got, want)
     assert cooperative == refuse + 1 and launches >= by_launch
+
+
+@pytest.mark.parametrize("kind", [CONSTRAINTS, SQN])
+def test_function_attribute_does_not_follow_the_run(emu, kind):
+    # the LDS that a kernel may take is set for the function, which every context and thread shares: a smaller
+    # run must not lower it between a larger one's check and its launch
+    lib = emu()
+    set_faults(lib, kind, refuse=0)
+    ctx = sim.Sim(0)
+    try:
+        for big in (True, False):
+            if kind == CONSTRAINTS:
+                n = 5120 if big else 4096
+                A, C = workloads.newsvendor_constraints(3, 0, n, 2)
+                ctx.run_newsvendor_lp(workloads.newsvendor_instance(3, 0, n), A, C, 1, 1, 5, S=2)
+            else:
+                start(SQN, ctx, big=big)
+            lib.emu_faults()[0].refuse = 1
+    finally:
+        ctx.close()
+    values = {}
+    for line in lib.emu_log().decode().split("\n"):
+        if line.startswith("attribute"):
+            _, fn, value = line.split()
+            values.setdefault(fn, []).append(value)
+    assert values
+    for fn, v in values.items():
+        assert len(set(v)) == 1, v
