@@ -374,24 +374,25 @@ int run_impl(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint64_t
     B.sched_c_f = p->n_schedule ? reinterpret_cast<const float *>(sb + sl.off_c_f) : nullptr;
     B.sched_c_d = p->n_schedule ? reinterpret_cast<const double *>(sb + sl.off_c_d) : nullptr;
 
+    // the records of the two-launch form; without room for them the paths reduce themselves
+    B.rec_y = nullptr;
+    const bool fp64 = p->state_precision == SIM_FP64;
+    if (!dense && fw::paths_split_applies(*ctx->desc_host, fp64, p->n_schedule != 0, ctx->device) &&
+        (keep || ensure_spare(ctx, ctx->recs, R * (sizeof(double) + sizeof(uint32_t) * (d + 2))))) {
+        double *const y = static_cast<double *>(ctx->recs.ptr);
+        uint32_t *const tau = reinterpret_cast<uint32_t *>(y + R);
+        B.rec_y = want_y ? B.y : y;
+        B.rec_tau = keep ? B.tau : tau;
+        B.rec_cnt = keep ? B.cnt : tau + R;
+    }
+
     HIP_TRY(ctx, hipEventRecord(ctx->ev_start, ctx->stream));
     int width = 0;
     if (dense) {
         rc = fw::launch_fw_dense(*ctx->desc_host, ctx->desc_dev, B, ctx->stream);
         width = 2;
     } else {
-        // the records of the two-launch form; without room for them the paths reduce themselves
-        B.rec_y = nullptr;
-        const bool fp64 = p->state_precision == SIM_FP64;
-        if (fw::paths_split_applies(*ctx->desc_host, fp64, p->n_schedule != 0, ctx->device) &&
-            (keep || ensure_spare(ctx, ctx->recs, R * (sizeof(double) + sizeof(uint32_t) * (d + 2))))) {
-            double *const y = static_cast<double *>(ctx->recs.ptr);
-            uint32_t *const tau = reinterpret_cast<uint32_t *>(y + R);
-            B.rec_y = want_y ? B.y : y;
-            B.rec_tau = keep ? B.tau : tau;
-            B.rec_cnt = keep ? B.cnt : tau + R;
-        }
-        rc = fw::launch_fw_paths(*ctx->desc_host, ctx->desc_dev, B, p->state_precision == SIM_FP64, ctx->stream, &width);
+        rc = fw::launch_fw_paths(*ctx->desc_host, ctx->desc_dev, B, fp64, ctx->stream, &width);
     }
     if (rc == -5) return set_err(ctx, SIM_EUNSUPPORTED, "no kernel for d=%u with this precision and noise", d);
     if (rc) return set_err(ctx, SIM_EDEVICE, "kernel launch failed: %s", hipGetErrorString(hipGetLastError()));

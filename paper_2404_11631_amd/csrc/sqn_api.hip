@@ -241,7 +241,6 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
     P.ypart = static_cast<double *>(q.sypart.ptr);
     P.small = static_cast<double *>(q.ssmall.ptr);
     hipStream_t st = ctx->stream;
-    HIP_TRY(ctx, hipEventRecord(q.ev0, st));
     // the cooperative form when it fits and the workspace limit leaves room for its exchange slots; under
     // capture the launches, since a replay needs the slots cleared by a node of the graph and the host's
     // check of the wait, which is made once, when the results are first read
@@ -255,6 +254,7 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
         Q.words = static_cast<uint64_t *>(q.words.ptr);
         Q.fail = reinterpret_cast<uint32_t *>(static_cast<char *>(q.words.ptr) + words - sizeof(uint64_t));
         P.A.fail = Q.fail;
+        HIP_TRY(ctx, hipEventRecord(q.ev0, st));
         bool refused = false;
         for (Q.k0 = 1; Q.k0 <= K && !refused; Q.k0 = Q.k1) {
             Q.k1 = std::min(K + 1, Q.k0 + fw::kSqnRunSteps);
@@ -267,8 +267,8 @@ int sim_run_sqn_split(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_
             return SIM_OK;
         }
         P.A.fail = nullptr;
-        HIP_TRY(ctx, hipEventRecord(q.ev0, st));
     }
+    HIP_TRY(ctx, hipEventRecord(q.ev0, st));
     if (int rc2 = sqn_split_sequenced(ctx, P)) return rc2;
     return sqn_finish(ctx, p, A, R, K);
 }

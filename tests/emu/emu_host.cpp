@@ -21,8 +21,8 @@ thread_local Dim3emu blockIdx;
 EmuBlock *g_block = nullptr;
 
 namespace fw {
-bool paths_split_applies(const InstanceDesc &, bool, bool, int) { return false; }
-int launch_fw_paths(const InstanceDesc &, const InstanceDesc *, const RunBuffers &, bool, hipStream_t, int *) { return -3; }
+bool paths_split_applies(const InstanceDesc &, bool, bool, int) { return true; }
+int launch_fw_paths(const InstanceDesc &, const InstanceDesc *, const RunBuffers &, bool, hipStream_t, int *) { return 0; }
 int launch_fw_dense(const InstanceDesc &, const InstanceDesc *, const RunBuffers &, hipStream_t) { return -3; }
 int launch_sqn_run(const SqnArgs &, hipStream_t) { return -1; }
 int launch_sqn_hessian(const SqnArgs &, uint32_t, uint32_t, uint32_t, double *, double *, uint32_t, hipStream_t) { return -1; }

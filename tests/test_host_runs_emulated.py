@@ -248,3 +248,22 @@ def test_function_attribute_does_not_follow_the_run(emu, kind):
     assert values
     for fn, v in values.items():
         assert len(set(v)) == 1, v
+
+
+@pytest.mark.parametrize("kind", [0, *KINDS])
+def test_timed_interval_holds_no_allocation(emu, kind):
+    # a first run's device time (between two events) does not include the allocation of its scratch
+    lib = emu()
+    set_faults(lib, kind)
+    ctx = sim.Sim(0)
+    try:
+        if kind:
+            start(kind, ctx)
+        else:
+            ctx.run(sim.Problem(mu=np.ones(3), sigma=np.ones(3), N=5), 100, 5, 1)
+    finally:
+        log = lib.emu_log().decode().split("\n")
+        ctx.close()
+    events = [i for i, line in enumerate(log) if line == "event"]
+    assert len(events) >= 2 and "malloc" in log[:events[0]]
+    assert not {"malloc", "free"} & set(log[events[0]:events[-1]])
