@@ -740,7 +740,7 @@ __host__ __device__ inline uint32_t wave_lds(uint32_t stage) { return 3 * stage 
 __global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_kernel(BatchBuffers B)
 {
     HIP_DYNAMIC_SHARED(float, zs)                      // three buffers of the largest N d, vs, dots (wave_lds)
-    const uint32_t stage = B.wave_stage ? B.wave_stage : static_cast<uint32_t>(kStageFloats);
+    const uint32_t stage = B.wave_stage;
     float *vs = zs + 3 * stage, *dots = vs + 32;
     for (uint32_t i = threadIdx.x; i < wave_lds(stage); i += blockDim.x) zs[i] = 0.0f;
     __syncthreads();
@@ -805,15 +805,20 @@ __global__ __launch_bounds__(kBlock) void fw_batch_reduce(BatchBuffers B)
     }
 }
 
+// A drawing wavefront draws 256 normals a pass: more of them from the second pass on, where the device
+// still holds every workgroup at once.
+inline uint32_t wave_threads(const BatchBuffers &B)
+{
+    return B.wave_stage > 256 && B.n_tiles <= kWaveManyDrawers ? kWaveMaxThreads : 2 * kWave;
+}
+
 // the tile kernel over every tile, then the per-instance reduction, in stream order
 int launch_fw_batch(const BatchBuffers &B, hipStream_t stream)
 {
     if (B.n_tiles) {
         if (B.wave_mode) {
-            // a drawing wavefront draws 256 normals a pass: more of them from the second pass on, where the
-            // device still holds every workgroup at once
-            const uint32_t threads = B.wave_stage > 256 && B.n_tiles <= kWaveManyDrawers ? kWaveMaxThreads : 2 * kWave;
-            hipLaunchKernelGGL(fw_wave_kernel, dim3(B.n_tiles), dim3(threads), sizeof(float) * wave_lds(B.wave_stage), stream, B);
+            hipLaunchKernelGGL(fw_wave_kernel, dim3(B.n_tiles), dim3(wave_threads(B)), sizeof(float) * wave_lds(B.wave_stage),
+                               stream, B);
         }
         else hipLaunchKernelGGL(fw_tile_kernel, dim3(B.n_tiles), dim3(kWave), 0, stream, B);
     }

@@ -104,8 +104,7 @@ int sim_run_batch(sim_ctx *ctx, uint32_t n_inst, const sim_params *p, const uint
     B.dlog = P.dlog_total ? (uint8_t *)b.dlog.ptr : nullptr;
     B.final_stats = (fw::TilePartial *)b.final_stats.ptr;
     B.wave_mode = P.wave_mode ? 1u : 0u;
-    for (uint32_t i = 0; B.wave_mode && i < n_inst; ++i)
-        B.wave_stage = std::max(B.wave_stage, (p[i].n_samples * p[i].d + 3) / 4 * 4);
+    B.wave_stage = P.wave_stage;
 
     HIP_TRY(ctx, hipMemcpyAsync(b.inst.ptr, b.inst_host, sizeof(InstanceDesc) * n_inst, hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.tiles.ptr, b.tiles_host, sizeof(fw::Tile) * n_tiles, hipMemcpyHostToDevice, ctx->stream));

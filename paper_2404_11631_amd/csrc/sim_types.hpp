@@ -90,7 +90,7 @@ struct BatchBuffers {
     uint8_t *dlog;            // DECISION_LOG: concatenated [T_i][log_count_i]
     TilePartial *final_stats; // [n_inst] reduced per instance
     uint32_t wave_mode;       // 1: every tile is one replication on a wavefront (fw_wave_kernel)
-    uint32_t wave_stage;      // then: floats of its buffers, the largest N d in whole blocks (0: kBatchStageFloats)
+    uint32_t wave_stage;      // then: floats of one of its buffers, the largest N d in whole blocks
 };
 
 // LDS staging of a batched tile's normals (floats per wavefront). A replication qualifies for the

@@ -24,6 +24,9 @@ static std::vector<uint8_t> g_dlog;
 static std::vector<sim_params> g_params;
 static std::vector<uint64_t> g_R, g_T;
 static char g_err[512];
+static uint32_t g_wave_stage, g_wave_threads;         // of the last run
+extern "C" uint32_t emu_wave_stage() { return g_wave_stage; }
+extern "C" uint32_t emu_wave_threads() { return g_wave_threads; }
 
 extern "C" int emu_run_batch(uint32_t n_inst, const sim_params *p, const uint64_t *R, const uint64_t *T,
                              uint64_t seed, const sim_batch_config *cfg, int keep)
@@ -59,8 +62,11 @@ extern "C" int emu_run_batch(uint32_t n_inst, const sim_params *p, const uint64_
     B.dlog = P.dlog_total ? g_dlog.data() : nullptr;
     B.final_stats = g_final.data();
     B.wave_mode = P.wave_mode ? 1u : 0u;
+    B.wave_stage = P.wave_stage;
+    g_wave_stage = B.wave_stage;
+    g_wave_threads = B.wave_mode ? wave_threads(B) : 0;
     for (uint32_t t = 0; t < P.n_tiles; ++t)
-        emu_run_block(B.wave_mode ? 128 : 64, t, [&] { if (B.wave_mode) fw_wave_kernel(B); else fw_tile_kernel(B); });
+        emu_run_block(B.wave_mode ? wave_threads(B) : 64, t, [&] { if (B.wave_mode) fw_wave_kernel(B); else fw_tile_kernel(B); });
     for (uint32_t i = 0; i < n_inst; ++i) emu_run_block(256, i, [&] { fw_batch_reduce(B); });
     return 0;
 }

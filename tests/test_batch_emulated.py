@@ -188,3 +188,22 @@ def test_wave_kernel_matches_oracle(emu):
         for r in range(R[i]):
             outs[r] = parity.check_rep(op, g, r, T[i], oracle.U32, decisions=g["decisions"][:, r])
         parity.check_stats(st, op.reduce(outs, T[i]), len(p.checkpoints), len(p.mu), g["tau"])
+
+
+@pytest.mark.parametrize("d,N,T,M", [(3, 5, 12, 2), (16, 16, 6, 1), (31, 12, 6, 1), (2, 129, 6, 1)])
+def test_wave_kernel_buffers(emu, d, N, T, M):
+    """Alone in its batch an instance's three buffers lie N d (in whole blocks) apart, so that a lane reads past
+    its sample into the next one's; past N d = 256 three wavefronts draw."""
+    mu, sigma = workloads.diag_instance(79, d, d)
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, M=M, checkpoints=(5, T), gap_eps=0.05, instance_id=d, log_reps=(0, 2))
+    n, a, Ra, Ta, cfg, keep = sim._batch_args([p], [2], [T], lanes_per_rep=[64], keep_paths=True)
+    assert emu.emu_run_batch(n, a, Ra, Ta, 43, ctypes.byref(cfg), 1) == 0
+    assert (emu.emu_wave_stage(), emu.emu_wave_threads()) == ((N * d + 3) // 4 * 4, 256 if N * d > 256 else 128)
+    st = sim.SimStats()
+    emu.emu_batch_stats(0, ctypes.byref(st))
+    g = _paths(emu, 0)
+    op = parity.oracle_problem(p, 43)
+    outs = (oracle.PathOut * 2)()
+    for r in range(2):
+        outs[r] = parity.check_rep(op, g, r, T, oracle.U32, decisions=g["decisions"][:, r])
+    parity.check_stats(st, op.reduce(outs, T), 2, d, g["tau"])
