@@ -402,8 +402,9 @@ int sim_cv_law(const sim_params *p, uint64_t T, double *probs, double *S2, doubl
  * noise, FP32 state, 2 <= N <= SIM_WIDE_MAX_N, any M, 1 <= R <= SIM_WIDE_MAX_R, R T <= 2^30; flags
  * may hold SIM_KEEP_PATHS and SIM_DECISION_LOG, and the run keeps every per-path record and
  * decision either way. Asynchronous on the context's stream. Up to d = 65,536 (N <= 63, no
- * schedule, d R / 128 <= 512) a cooperative launch runs all iterations between two checkpoints, with the same
- * results bit for bit; otherwise the host enqueues three launches per iteration before returning. */
+ * schedule, d R / 128 <= 512) a cooperative launch runs the iterations between two checkpoints, at most 1,024 of
+ * them, with the same results bit for bit; otherwise, and where the runtime refuses the cooperative
+ * launch, the host enqueues three launches per iteration before returning. */
 int sim_run_wide(sim_ctx *ctx, const sim_params *p, uint64_t R, uint64_t T, uint64_t seed);
 
 /* Checks a parameter set exactly as sim_run_wide does, without a device. */
@@ -436,8 +437,9 @@ int sim_wide_paths(sim_ctx *ctx, sim_wide_view *out);
  * (replication, epoch) stream in domain 4; Algorithm 2 with the vertex of smallest g_j / c_j when it
  * is negative (else the origin, lowest index among equal values), step 2/(t+2). Y = f(x_T) and the
  * checkpoints f(x_c) in FP64 from Eq. (6) in closed form. The parallelism is inside a replication
- * (a thread per up to four products; up to n = 130,000 one cooperative launch runs all iterations between
- * two checkpoints, beyond that a launch per iteration). */
+ * (a thread per up to four products; up to n = 130,000 one cooperative launch runs the iterations between
+ * two checkpoints, at most 1,024 of them; beyond that, and where the runtime refuses it, a launch per
+ * iteration). */
 typedef struct {
     uint32_t abi_version;       /* SIM_ABI_VERSION */
     uint32_t n;                 /* products, a multiple of 4 in [4, SIM_NV_MAX_N] */
@@ -481,7 +483,8 @@ int sim_nv_paths(sim_ctx *ctx, sim_wide_view *out);
  * updated as x + gamma (s - x) with gamma = 2/(t+2), separately rounded (no fused operations).
  * Y = f(x_T) and the checkpoints f(x_c) come from Eq. (6).
  * Up to n = 15,360 (S <= 128 at most, few enough replications for the device to hold at once) a cooperative
- * launch runs all iterations between two checkpoints, with the same vertices, iterates and pivots.
+ * launch runs the iterations between two checkpoints, at most 256 of them, with the same vertices, iterates
+ * and pivots; otherwise, and where the runtime refuses it, two launches per iteration.
  * The params' c and C are not used (c may be NULL). Requires: 1 <= M <= SIM_NV_MAX_RES, A >= 0
  * with a positive entry in every column (X is then bounded), C > 0, x0 in X, n <= SIM_NV_LP_MAX_N,
  * R T <= 2^24. Asynchronous on the context's stream. Results: sim_nv_lp_stats (f_star NaN;
@@ -557,11 +560,11 @@ int sim_run_sqn(sim_ctx *ctx, const sim_sqn_params *p, uint64_t R, uint64_t K, u
  * over many workgroups: every workgroup owns a 256-feature slice of w, of the gradient and of the
  * stored pairs, and the dot products that need the whole vector (the sampled rows' x_i'w, S'g and
  * Y'g, the new pair's products) are summed over the slices, in slice order. Where the device holds
- * the run's workgroups at once, a cooperative launch runs up to 4,096 iterations; otherwise, and under capture, there are
- * one to two launches per iteration and three more at the end of a window, with the same results bit
- * for bit. sim_run_sqn keeps one
- * workgroup per replication, which streams the stored pairs through a single compute unit; this
- * entry point is for the paper's single runs. Results differ from sim_run_sqn's only in the order
+ * the run's workgroups at once, a cooperative launch runs up to 4,096 iterations; otherwise, under
+ * capture, and where the runtime refuses it, there are one to two launches per iteration and three
+ * more at the end of a window, with the same results bit for bit. sim_run_sqn keeps one workgroup
+ * per replication, which streams the stored pairs through a single compute unit; this entry point
+ * is for the paper's single runs. Results differ from sim_run_sqn's only in the order
  * of those sums (the sampled rows are the same). Same parameters, outputs (sim_sqn_stats,
  * sim_sqn_paths, sim_sqn_hessian) and errors as sim_run_sqn, and 1 <= R <= SIM_SQN_SPLIT_MAX_R
  * (else SIM_EINVAL). Asynchronous on the context's stream; the host issues every launch. */

@@ -6,10 +6,11 @@
 // loaded with relaxed agent-scope atomics: a reader that sees the tag has the value of the same
 // store, so no fence is needed (a release fence writes back the whole L2 of an XCD, which made a
 // counter-based form five times slower than the launches it replaced), and the reader's poll is the
-// only wait. Slots alternate between two buffers by the iteration's parity, each workgroup's on a 64-byte line
-// of its own; a workgroup publishes
-// iteration t + 1 only after it has read every value of iteration t, so a slot is overwritten (at
-// t + 2) only after all have read it.
+// only wait. A slot may be overwritten once every reader is known to be done with it. Where a workgroup
+// publishes iteration t + 1 only after it has read every value of iteration t, two buffers by the iteration's
+// parity do: the vertex words (each workgroup's on a 64-byte line of its own), the wide run's dots, the
+// constraint run's counts and vertex (which share lines) and the SQN run's row sums. The SQN run's other
+// blocks are single; why that is enough stands at SqnSplitSlots.
 //
 // Every wait is bounded: a poll that does not see its tag within kPollLimit rounds (about a second,
 // where a value arrives within microseconds) gives up, the workgroup raises the run's failure word and

@@ -17,8 +17,8 @@
 // The outcome is Y = f(w_T) in FP64 from the exact signature.
 //
 // State: s1, s2, v in registers (binary32 or binary64); the signature S (u32 while T(T+1)/2 < 2^32,
-// else u64) and the decision counts in a per-thread LDS column for the u32 runs, in registers
-// otherwise. No HBM traffic per step except the optional decision log.
+// else u64) and the decision counts in a per-thread LDS column for the u32 runs from 7 assets on, in
+// registers otherwise. No HBM traffic per step except the optional decision log.
 //
 // The kernels are templates over the asset count; each translation unit that includes this header
 // instantiates one family (the selector functions at the end), so they compile side by side.
@@ -741,7 +741,8 @@ inline KernelChoice choose_generic(uint32_t d)
 // (45.1 ms against 10.8 ms of issue time for 2.2e10 normals). Binary32 runs with a 32-bit signature have an exact kernel
 // for every d, features too under Gaussian noise. Elsewhere the widths that the named workloads use are
 // exact. Runs with per-epoch sample sizes (SCHED) use the generic kernels, whose per-sample arithmetic
-// and order are the exact-width kernels' (so a constant schedule reproduces the plain run bit for bit).
+// and order are the exact-width kernels' but for the rounding that kFuseSum names: a constant schedule makes the
+// plain run's decisions, at the widths that fuse except in near ties.
 KernelChoice paths_gauss_narrow(uint32_t d);                            // binary32, u32, d <= 16
 KernelChoice paths_gauss_broad(uint32_t d);                             // binary32, u32, 17 <= d <= 32
 KernelChoice paths_t_narrow(uint32_t d);                                // binary32, u32, t noise, d <= 16

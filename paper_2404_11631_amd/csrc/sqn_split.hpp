@@ -125,7 +125,15 @@ struct SqnSplitRun {
 };
 
 // The exchange slots of a replication, in 64-bit words: a slice's block of n values is 2 pad(n) words,
-// the high halves and the low, on 64-byte lines of its own.
+// the high halves and the low, on 64-byte lines of its own. Row sums x have two buffers by the iteration's
+// parity: x(k + 2) is written after the sums x(k + 1) of all slices are read, and a slice publishes x(k + 1)
+// after it has read x(k). One buffer is enough for
+//   d   S'g, Y'g of iteration k: d(k + 1) is written after all x(k + 1) are read, and a slice publishes x(k + 1)
+//       after it has read d(k) (w_{k+1} follows from it);
+//   cx  the rows' coefficients: the same with cx(k) in the place of d(k), both read before w_{k+1};
+//   h, ch, y  of the window that ends at k >= 2L: those of the next, at k + L, are written after all d(k + 1)
+//       are read (k + 1 > 2L, so there is a d), and a slice publishes d(k + 1) after it is through the
+//       window of k. x(k + 1) would not prove that: it is published before the window's work.
 struct SqnSplitSlots {
     uint32_t bp, dp, hp, yp, cp;                // padded values of a block
     size_t x, d, h, y, cx, ch, total;           // [2][W] rows; [W] S'g, Y'g; [W] Hessian rows; [W] new pair; coefficients

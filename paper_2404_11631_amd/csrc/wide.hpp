@@ -55,8 +55,8 @@ constexpr uint64_t kWideFailed = ~0ull;
 // ---- many iterations in one cooperative launch (fw_wide_run.hip) ---------------------------------
 // A run takes this form with one sample size, its samples in registers (N <= 63), and at most
 // kWideRunMaxUnits workgroups (units) per replication, all of them twice per compute unit.
-// Measured (N = 25, K = 1500, device ms): d = 216 16.9 -> 5.7, 3,000 17.1 -> 6.3, 10,000 16.8 -> 6.5,
-// 50,000 19.8 -> 9.5. Past 512 units the vertex exchange (units^2 words) outgrows the launches it saves.
+// Measured (N = 25, K = 1500, device ms): d = 216 16.9 -> 4.9, 3,000 17.1 -> 6.2, 10,000 16.8 -> 6.7,
+// 50,000 19.8 -> 9.6. Past 512 units the vertex exchange (units^2 words) outgrows the launches it saves.
 constexpr uint32_t kWideDirectUnits = 32;       // d <= 4,096: the dots in one exchange
 constexpr uint32_t kWideRunMaxUnits = 512;      // d <= 65,536
 constexpr uint32_t kWideRunMaxN = 63;
