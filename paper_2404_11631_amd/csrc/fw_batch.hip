@@ -490,22 +490,27 @@ __device__ __forceinline__ double half_sum32(double x)
 // Lane i forms sample i's dot product with v = sz .* w, lane j the sums over the samples of z_ij
 // and z_ij (z_i'v); the gradient, its minimum (lowest index among equal values) and g'w are reduced
 // over the first half wavefront. Same formulas as the tile kernel, summed in a different order.
-// The workgroup's other wavefronts draw the normals two epochs ahead (a Philox block per lane at a time)
-// into the third of three LDS buffers; one workgroup barrier per epoch hands the buffers over. The
-// normals do not depend on the iterate, so the draw leaves the iteration's dependent chain.
+// The workgroup's other wavefronts draw the next epochs' normals into LDS (a Philox block per lane at a time);
+// one workgroup barrier per epoch hands a buffer over. The normals do not depend on the iterate, so the draw
+// leaves the iteration's dependent chain.
 //
-// The chain is what bounds it (1,024 replications are a wavefront per SIMD). With up to DR assets and NC
-// samples a lane takes its sample's row and its asset's column into registers while the previous
-// iteration's reductions run, and v_j and the dot products reach the other lanes as scalars: no LDS round
-// trip is left in the chain. DR = 0: both go through LDS (more than 32 samples). us per iteration at
-// 1,024 replications: d = N = 10 1.15 -> 0.98, d = 17, N = 30 1.62 -> 1.44; at 52, d = 23, N = 15 1.61 ->
-// 1.07. Registers for 64 samples cost more in guards than the LDS they save (d = 8, N = 60 1.9 -> 7.8).
+// The chain is what bounds it (1,024 replications are a wavefront per SIMD). In registers (wave_in_registers) a
+// lane takes its sample's row (up to DR assets) and its asset's column (up to NC samples) while the previous
+// iteration's reductions run, from one of three buffers drawn two epochs ahead, and v_j and the dot products
+// reach the other lanes as scalars: no LDS round trip is left in the chain. DR = 0: rows and columns are read
+// from LDS in the iteration, as are v and the dot products; two buffers, one epoch ahead.
+// Registers are set out for DR and NC, so more instructions and fewer resident wavefronts: past one or two
+// wavefronts per SIMD they lose. us per iteration in registers and from LDS, at 1,024, 2,048 and 3,000
+// replications: d = 10, N = 5 0.98, 1.18; 1.33, 1.46; 2.05, 1.67. d = N = 10 1.13, 1.17; 1.55, 1.49; 2.43, 1.71.
+// d = 17, N = 8 1.06, 1.09; 1.42, 1.41; 2.22, 1.63. d = 24, N = 12 1.27, 1.34; 1.83, 1.82; 2.82, 2.13. With
+// N = 17 to 32 in registers d = 24, N = 24 takes 1.66 at 1,024 and 2.28 at 1,500, from LDS 1.47 and 1.89.
 template <int DR, int NC>
-__device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile, float *zs, uint32_t stage, float *vs, float *dots)
+__device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile, float *lds)
 {
     const InstanceDesc *P = B.inst + tile.inst;
+    constexpr bool kAhead = DR > 0;                    // normals drawn two epochs ahead, else one
     const uint32_t lane = threadIdx.x % kWave;
-    const bool drawer = threadIdx.x >= kWave;          // the other wavefronts: the normals of the next epochs
+    const bool drawer = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) != 0;   // the other wavefronts
     const uint32_t r = tile.rep0;
     const uint32_t d = P->d, N = P->N, M = P->M, nd = N * d, nb = (nd + 3) / 4;
     const uint32_t T = static_cast<uint32_t>(P->T);    // at most kMaxBatchT
@@ -535,8 +540,10 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
         return fma(lambda, quad, -lin);
     };
 
-    // the normals of epoch e into its buffer (e mod 3), blocks b = first, first + stride, ...
-    float *const buf[3] = {zs, zs + stage, zs + 2 * stage};
+    // the normals of epoch e into its buffer (e mod 3, or 2), blocks b = first, first + stride, ...
+    const uint32_t stage = 4 * nb;
+    float *const vs = lds, *const dots = lds + 32, *const zs = DR ? lds : lds + 32 + (N + 3) / 4 * 4;
+    float *const buf[3] = {zs, zs + stage, zs + (kAhead ? 2 * stage : 0)};
     auto draw = [&](uint32_t e, float *dst, uint32_t first, uint32_t stride) {
         const PhiloxRow row = philox_row(e, r, k0);
         for (uint32_t b = first; b < nb; b += stride) {
@@ -547,9 +554,9 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
             dst[4 * b + 3] = q.z[3];
         }
     };
-    float *z_now = buf[0], *z_next = buf[1], *z_draw = buf[2];      // epoch, epoch + 1, epoch + 2
+    float *z_now = buf[0], *z_next = buf[1], *z_draw = buf[2];      // epoch, epoch + 1 and, of three, epoch + 2
     draw(0u, z_now, threadIdx.x, blockDim.x);
-    if (M < T) draw(1u, z_next, threadIdx.x, blockDim.x);
+    if (kAhead && M < T) draw(1u, z_next, threadIdx.x, blockDim.x);
     __syncthreads();
 
     // sample min(lane, N - 1)'s row, which past d meets zeros of v, and this asset's column, zero past N;
@@ -570,9 +577,10 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
     for (uint32_t t = 0; t < T; ++t) {
         const bool ends = m_in_epoch + 1 == M;          // the epoch's last iteration
         if (drawer) {
-            // epoch + 2 goes to the buffer that was last read before the previous barrier
-            if (ends && (static_cast<uint64_t>(epoch) + 2) * M < T)
-                draw(epoch + 2, z_draw, threadIdx.x - kWave, blockDim.x - kWave);
+            // the buffer drawn into was last read before the previous barrier
+            constexpr uint32_t kNext = kAhead ? 2 : 1;
+            if (ends && (static_cast<uint64_t>(epoch) + kNext) * M < T)
+                draw(epoch + kNext, kAhead ? z_draw : z_next, threadIdx.x - kWave, blockDim.x - kWave);
         } else {
             // the scale 2/(t (t+1)): an FP64 division every 64 iterations instead of one in each one's chain
             const uint32_t tl = t % kWave;
@@ -657,7 +665,7 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
             __syncthreads();   // all wavefronts: the drawn buffer is complete and the oldest is free
             float *const z = z_now;
             z_now = z_next;
-            z_next = z_draw;
+            z_next = kAhead ? z_draw : z;
             z_draw = z;
             m_in_epoch = 0;
             ++epoch;
@@ -732,25 +740,34 @@ __global__ __launch_bounds__(kWave) void fw_tile_kernel(BatchBuffers B)
     else run_tile<1, 2>(B, tile, stage, coef);
 }
 
-// Floats of its LDS: `dots` for every sample, or what a lane reads past the last buffer.
-__host__ __device__ inline uint32_t wave_lds(uint32_t stage) { return 3 * stage + 32 + (stage > 32 * 33 ? stage : 32 * 33); }
-
 // One replication per workgroup (a wavefront for the iteration, the others for the next epochs'
-// normals), every tile of a batch that qualifies (BatchBuffers.wave_mode).
-__global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_kernel(BatchBuffers B)
+// normals), every tile of a batch that qualifies (BatchBuffers.wave_mode). A kernel for each mode: in one,
+// the form that reads from LDS has the registers of the other and runs up to 6 % slower.
+template <class Run>
+__device__ __forceinline__ void wave_run(const BatchBuffers &B, float4 *lds4, Run run)
 {
-    HIP_DYNAMIC_SHARED(float, zs)                      // three buffers of the largest N d, vs, dots (wave_lds)
-    const uint32_t stage = B.wave_stage;
-    float *vs = zs + 3 * stage, *dots = vs + 32;
-    for (uint32_t i = threadIdx.x; i < wave_lds(stage); i += blockDim.x) zs[i] = 0.0f;
+    float *const lds = reinterpret_cast<float *>(lds4);
+    for (uint32_t i = threadIdx.x; i < B.wave_lds; i += blockDim.x) lds[i] = 0.0f;
     __syncthreads();
     const Tile tile = B.tiles[blockIdx.x];
-    const uint32_t d = B.inst[tile.inst].d, N = B.inst[tile.inst].N;
-    if (d <= 16 && N <= 16) run_wave<16, 16>(B, tile, zs, stage, vs, dots);
-    else if (d <= 16 && N <= 32) run_wave<16, 32>(B, tile, zs, stage, vs, dots);
-    else if (N <= 16) run_wave<32, 16>(B, tile, zs, stage, vs, dots);
-    else if (N <= 32) run_wave<32, 32>(B, tile, zs, stage, vs, dots);
-    else run_wave<0, 0>(B, tile, zs, stage, vs, dots);
+    run(tile, lds, B.inst[tile.inst].d, B.inst[tile.inst].N);
+}
+
+__global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_kernel(BatchBuffers B)
+{
+    HIP_DYNAMIC_SHARED(float4, lds4)                   // v, dot products, buffers (wave_lds), 16-byte aligned
+    wave_run(B, lds4, [&](const Tile &tile, float *lds, uint32_t, uint32_t) { run_wave<0, 0>(B, tile, lds); });
+}
+
+__global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_registers_kernel(BatchBuffers B)
+{
+    HIP_DYNAMIC_SHARED(float4, lds4)
+    wave_run(B, lds4, [&](const Tile &tile, float *lds, uint32_t d, uint32_t N) {
+        if (d > 16 && N > 8) run_wave<32, 16>(B, tile, lds);
+        else if (d > 16) run_wave<32, 8>(B, tile, lds);
+        else if (N > 8) run_wave<16, 16>(B, tile, lds);
+        else run_wave<16, 8>(B, tile, lds);
+    });
 }
 
 // One workgroup per instance: its tile slots in order.
@@ -817,8 +834,8 @@ int launch_fw_batch(const BatchBuffers &B, hipStream_t stream)
 {
     if (B.n_tiles) {
         if (B.wave_mode) {
-            hipLaunchKernelGGL(fw_wave_kernel, dim3(B.n_tiles), dim3(wave_threads(B)), sizeof(float) * wave_lds(B.wave_stage),
-                               stream, B);
+            const auto kernel = B.wave_mode == kWaveRegisters ? fw_wave_registers_kernel : fw_wave_kernel;
+            hipLaunchKernelGGL(kernel, dim3(B.n_tiles), dim3(wave_threads(B)), sizeof(float) * B.wave_lds, stream, B);
         }
         else hipLaunchKernelGGL(fw_tile_kernel, dim3(B.n_tiles), dim3(kWave), 0, stream, B);
     }

@@ -78,8 +78,9 @@ struct BatchPlan {
     std::vector<double> fstar;
     std::vector<Tile> tiles;             // longest first
     uint32_t n_tiles = 0, max_ckpt = 1;
-    bool wave_mode = false;              // every instance at 64 lanes per replication, Gaussian, N d small
+    uint32_t wave_mode = 0;              // kWave...: every instance at 64 lanes per replication, Gaussian, N d small
     uint32_t wave_stage = 0;             // then: the largest N d, in whole blocks of four
+    uint32_t wave_lds = 0;               // and the most LDS an instance takes (wave_lds)
     uint64_t total_R = 0, total_steps = 0, cnt_total = 0, wsum_total = 0, dlog_total = 0;
 };
 

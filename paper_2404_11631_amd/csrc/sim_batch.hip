@@ -103,8 +103,9 @@ int sim_run_batch(sim_ctx *ctx, uint32_t n_inst, const sim_params *p, const uint
     B.wsum = b.keep ? (uint64_t *)b.wsum.ptr : nullptr;
     B.dlog = P.dlog_total ? (uint8_t *)b.dlog.ptr : nullptr;
     B.final_stats = (fw::TilePartial *)b.final_stats.ptr;
-    B.wave_mode = P.wave_mode ? 1u : 0u;
+    B.wave_mode = P.wave_mode;
     B.wave_stage = P.wave_stage;
+    B.wave_lds = P.wave_lds;
 
     HIP_TRY(ctx, hipMemcpyAsync(b.inst.ptr, b.inst_host, sizeof(InstanceDesc) * n_inst, hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.tiles.ptr, b.tiles_host, sizeof(fw::Tile) * n_tiles, hipMemcpyHostToDevice, ctx->stream));
@@ -115,7 +116,7 @@ int sim_run_batch(sim_ctx *ctx, uint32_t n_inst, const sim_params *p, const uint
                            A.partials == B.partials && A.slot_begin == B.slot_begin && A.fck == B.fck &&
                            A.total_R == B.total_R && A.y == B.y && A.tau == B.tau && A.cnt == B.cnt &&
                            A.wsum == B.wsum && A.dlog == B.dlog && A.final_stats == B.final_stats &&
-                           A.wave_mode == B.wave_mode && A.wave_stage == B.wave_stage;
+                           A.wave_mode == B.wave_mode && A.wave_stage == B.wave_stage && A.wave_lds == B.wave_lds;
     if (graph && (!b.exec || !same_args)) {
         // capture the two kernel launches on the library's own stream (default priority)
         if (b.exec) {

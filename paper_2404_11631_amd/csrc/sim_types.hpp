@@ -89,8 +89,9 @@ struct BatchBuffers {
     uint64_t *wsum;           // KEEP_PATHS: concatenated [d_i][R_i]
     uint8_t *dlog;            // DECISION_LOG: concatenated [T_i][log_count_i]
     TilePartial *final_stats; // [n_inst] reduced per instance
-    uint32_t wave_mode;       // 1: every tile is one replication on a wavefront (fw_wave_kernel)
-    uint32_t wave_stage;      // then: floats of one of its buffers, the largest N d in whole blocks
+    uint32_t wave_mode;       // kWave..., or 0: tiles of several replications
+    uint32_t wave_stage;      // then: the largest N d, in whole Philox blocks
+    uint32_t wave_lds;        // and the floats of its LDS (wave_lds), the most that an instance takes
 };
 
 // LDS staging of a batched tile's normals (floats per wavefront). A replication qualifies for the
@@ -100,6 +101,25 @@ constexpr uint32_t kBatchStageFloats = 2112;
 // Descriptor flag bits: 1 keep per-path records, 2 decision log, 4 control-variate features,
 // 8 outcomes Y only (set by the library for its own control-variate runs).
 constexpr uint32_t kFlagYOnly = 8u;
+
+// BatchBuffers.wave_mode: every tile is one replication on a wavefront (fw_batch.hip), whose lanes read the
+// samples from LDS, or hold their sample's row and their asset's column in registers.
+constexpr uint32_t kWaveLds = 1, kWaveRegisters = 2;
+// Whether an instance's wavefronts are faster in registers (run_wave has both sides' times). Registers are set
+// out for 8 or 16 samples and 16 or 32 assets: with more of either the padding's instructions show at fewer tiles.
+constexpr bool wave_in_registers(uint32_t N, uint32_t d, uint64_t n_tiles)
+{
+    return N <= 8 && d <= 16 ? n_tiles <= 2048 : N <= 16 && n_tiles <= 1024;
+}
+// Floats of LDS: in registers three buffers of N d, in whole Philox blocks, and what a lane reads past the last
+// one (a row of 32 at most, columns of 8 or 16); otherwise v, a dot product per sample and two buffers.
+constexpr uint32_t wave_lds(uint32_t N, uint32_t d, uint32_t mode)
+{
+    const uint32_t stage = (N * d + 3) / 4 * 4;
+    const uint32_t columns = (N > 8 ? 16 : 8) * d;
+    return mode == kWaveRegisters ? 2 * stage + (stage + 32 > columns ? stage + 32 : columns)
+                                  : 32 + (N + 3) / 4 * 4 + 2 * stage;
+}
 
 // Replications up to which other wavefronts draw a path's normals (fw_paths_split.hpp), where the device
 // also holds every workgroup at once. Speed against a lane per replication, at 1,000, 32,768, 49,152 and

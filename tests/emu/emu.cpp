@@ -61,12 +61,17 @@ extern "C" int emu_run_batch(uint32_t n_inst, const sim_params *p, const uint64_
     B.wsum = keep ? g_wsum.data() : nullptr;
     B.dlog = P.dlog_total ? g_dlog.data() : nullptr;
     B.final_stats = g_final.data();
-    B.wave_mode = P.wave_mode ? 1u : 0u;
+    B.wave_mode = P.wave_mode;
     B.wave_stage = P.wave_stage;
+    B.wave_lds = P.wave_lds;
     g_wave_stage = B.wave_stage;
     g_wave_threads = B.wave_mode ? wave_threads(B) : 0;
     for (uint32_t t = 0; t < P.n_tiles; ++t)
-        emu_run_block(B.wave_mode ? wave_threads(B) : 64, t, [&] { if (B.wave_mode) fw_wave_kernel(B); else fw_tile_kernel(B); });
+        emu_run_block(B.wave_mode ? wave_threads(B) : 64, t, [&] {
+            if (B.wave_mode == kWaveRegisters) fw_wave_registers_kernel(B);
+            else if (B.wave_mode) fw_wave_kernel(B);
+            else fw_tile_kernel(B);
+        });
     for (uint32_t i = 0; i < n_inst; ++i) emu_run_block(256, i, [&] { fw_batch_reduce(B); });
     return 0;
 }

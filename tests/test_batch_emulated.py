@@ -207,3 +207,15 @@ def test_wave_kernel_buffers(emu, d, N, T, M):
     for r in range(2):
         outs[r] = parity.check_rep(op, g, r, T, oracle.U32, decisions=g["decisions"][:, r])
     parity.check_stats(st, op.reduce(outs, T), 2, d, g["tau"])
+
+
+@pytest.mark.parametrize("d,N", [(16, 8), (17, 8), (16, 17), (32, 8), (17, 9), (32, 16), (32, 17)])
+def test_wave_forms(emu, d, N):
+    """The widths and sample counts at which a lane's registers take another number of values, or LDS all of them."""
+    T = 6
+    mu, sigma = workloads.diag_instance(80, d, d)
+    p = sim.Problem(mu=mu, sigma=sigma, N=N, checkpoints=(5, T), gap_eps=0.05, instance_id=d, log_reps=(0, 1))
+    n, a, Ra, Ta, cfg, keep = sim._batch_args([p], [1], [T], lanes_per_rep=[64], keep_paths=True)
+    assert emu.emu_run_batch(n, a, Ra, Ta, 44, ctypes.byref(cfg), 1) == 0
+    g = _paths(emu, 0)
+    parity.check_rep(parity.oracle_problem(p, 44), g, 0, T, oracle.U32, decisions=g["decisions"][:, 0])

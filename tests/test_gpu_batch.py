@@ -102,6 +102,27 @@ def test_batch_composition_invariance(ctx):
     assert sa.mean == sb.mean and sa.var == sb.var and list(sa.decision_total) == list(sb.decision_total)
 
 
+@pytest.mark.parametrize("d,N,tiles", [(1, 2, 2048), (10, 5, 2048), (16, 8, 2048), (17, 8, 1024), (32, 3, 1024),
+                                       (11, 9, 1024), (16, 16, 1024), (17, 9, 1024), (32, 16, 1024)])
+def test_wave_forms(ctx, d, N, tiles):
+    """One replication per wavefront: on either side of the number of tiles at which the samples stay in LDS
+    the same bits, the first and last replication against the oracle."""
+    T = 60
+    runs = []
+    for R in (tiles, tiles + 1):
+        p = make(d, d, N, ckpt=(20, T), log=(0, R))
+        ctx.run_batch([p], [R], [T], seed=31, lanes_per_rep=[64], keep_paths=True)
+        g = ctx.batch_paths(0)
+        assert g["lanes_per_rep"] == 64
+        op = parity.oracle_problem(p, 31)
+        for r in (0, R - 1):
+            parity.check_rep(op, g, r, T, oracle.U32, decisions=g["decisions"][:, r])
+        runs.append({k: np.array(g[k]) for k in ("y", "cnt", "wsum", "tau", "f_ckpt", "decisions")})
+    for k, x in runs[0].items():
+        assert np.array_equal(x, runs[1][k][..., :tiles]), k
+    say(f"[batch] d={d} N={N}: the same bits at {tiles} and {tiles + 1} tiles")
+
+
 def test_batch_errors(ctx):
     p = make(0, 40, 4)
     with pytest.raises(sim.SimError) as e:
