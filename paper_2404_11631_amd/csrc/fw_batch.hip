@@ -33,10 +33,11 @@ namespace fw {
 
 constexpr int kWave = 64;
 constexpr int kBatchMaxD = 32;
-// Workgroups up to which fw_wave_kernel has three drawing wavefronts: two of four wavefronts per compute
-// unit. At 1,024 the fourth wavefronts wait for a place (d = 4, N = 250 5.4 -> 10.1 us per iteration).
+// Workgroups up to which the one-wavefront form has three drawing wavefronts: two of four wavefronts per compute
+// unit. us per iteration with one and with three: at 512 d = 10, N = 60 1.92, 1.83, N = 200 4.60, 4.36; at 1,024
+// 1.95, 2.01 and 4.67, 4.76.
 constexpr uint32_t kWaveManyDrawers = 512;
-constexpr uint32_t kWaveMaxThreads = 256;      // fw_wave_kernel: up to three drawing wavefronts
+constexpr uint32_t kWaveMaxThreads = 256;      // up to three drawing wavefronts
 constexpr int kLaneAssets = 8;                 // assets held by one lane
 // LDS staging of one wavefront: a sub-group of Pa lanes draws G d <= 4 d <= 32 Pa normals per
 // round, and a wavefront has 64 / Pa sub-groups. Sub-group areas are 32 Pa + 1 floats apart (131 at
@@ -501,8 +502,8 @@ __device__ __forceinline__ double half_sum32(double x)
 // from LDS in the iteration, as are v and the dot products; two buffers, one epoch ahead.
 // Registers are set out for DR and NC, so more instructions and fewer resident wavefronts: past one or two
 // wavefronts per SIMD they lose. us per iteration in registers and from LDS, at 1,024, 2,048 and 3,000
-// replications: d = 10, N = 5 0.98, 1.18; 1.33, 1.46; 2.05, 1.67. d = N = 10 1.13, 1.17; 1.55, 1.49; 2.43, 1.71.
-// d = 17, N = 8 1.06, 1.09; 1.42, 1.41; 2.22, 1.63. d = 24, N = 12 1.27, 1.34; 1.83, 1.82; 2.82, 2.13. With
+// replications: d = 10, N = 5 0.89, 1.06; 1.15, 1.21; 1.85, 1.45. d = N = 10 0.97, 1.05; 1.32, 1.22; 2.11, 1.49.
+// d = 17, N = 8 0.94, 0.98; 1.23, 1.16; 1.99, 1.41. d = 24, N = 12 1.19, 1.22; 1.68, 1.51; 2.59, 1.91. With
 // N = 17 to 32 in registers d = 24, N = 24 takes 1.66 at 1,024 and 2.28 at 1,500, from LDS 1.47 and 1.89.
 template <int DR, int NC>
 __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile, float *lds)
@@ -510,7 +511,8 @@ __device__ __forceinline__ void run_wave(const BatchBuffers &B, const Tile tile,
     const InstanceDesc *P = B.inst + tile.inst;
     constexpr bool kAhead = DR > 0;                    // normals drawn two epochs ahead, else one
     const uint32_t lane = threadIdx.x % kWave;
-    const bool drawer = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) != 0;   // the other wavefronts
+    // the other wavefronts; as a scalar branch in the form from LDS
+    const bool drawer = DR ? threadIdx.x >= kWave : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) != 0;
     const uint32_t r = tile.rep0;
     const uint32_t d = P->d, N = P->N, M = P->M, nd = N * d, nb = (nd + 3) / 4;
     const uint32_t T = static_cast<uint32_t>(P->T);    // at most kMaxBatchT
@@ -742,7 +744,8 @@ __global__ __launch_bounds__(kWave) void fw_tile_kernel(BatchBuffers B)
 
 // One replication per workgroup (a wavefront for the iteration, the others for the next epochs'
 // normals), every tile of a batch that qualifies (BatchBuffers.wave_mode). A kernel for each mode: in one,
-// the form that reads from LDS has the registers of the other and runs up to 6 % slower.
+// the form that reads from LDS has the registers of the other and runs up to 6 % slower. The forms' order in
+// the second decides how the compiler lays out the chain: d = N = 10 0.96 us per iteration, others 0.95 to 1.01.
 template <class Run>
 __device__ __forceinline__ void wave_run(const BatchBuffers &B, float4 *lds4, Run run)
 {
@@ -763,10 +766,10 @@ __global__ __launch_bounds__(kWaveMaxThreads) void fw_wave_registers_kernel(Batc
 {
     HIP_DYNAMIC_SHARED(float4, lds4)
     wave_run(B, lds4, [&](const Tile &tile, float *lds, uint32_t d, uint32_t N) {
-        if (d > 16 && N > 8) run_wave<32, 16>(B, tile, lds);
-        else if (d > 16) run_wave<32, 8>(B, tile, lds);
-        else if (N > 8) run_wave<16, 16>(B, tile, lds);
-        else run_wave<16, 8>(B, tile, lds);
+        if (d <= 16 && N > 8) run_wave<16, 16>(B, tile, lds);
+        else if (d <= 16) run_wave<16, 8>(B, tile, lds);
+        else if (N > 8) run_wave<32, 16>(B, tile, lds);
+        else run_wave<32, 8>(B, tile, lds);
     });
 }
 
