@@ -228,7 +228,7 @@ typedef struct {
  * heavy instances split across several lanes (assets x sample chunks), then one per-instance
  * reduction in fixed order. When every instance asks for 64 lanes per replication, has Gaussian
  * noise and N d + 3 <= 2112, each replication instead runs on a workgroup of its own: a wavefront
- * with an asset per lane, and a second one that draws the next epoch's normals (the latency form,
+ * with an asset per lane, and one or three that draw the next epochs' normals (the latency form,
  * for few replications); the results follow the same protocol.
  * Each instance uses its instance_id as stream domain and the common noise `seed`.
  * Supported: FP32 state, diagonal Sigma, d <= 32, T <= 131071 (the signature is held in 33 bits),
@@ -394,7 +394,7 @@ int sim_cv_law(const sim_params *p, uint64_t T, double *probs, double *S2, doubl
  * Section 4.1 runs Algorithm 1 on a single replication of an instance with many assets: d from 5e2
  * to 1e5, N = 25 (50 at d = 1e5) samples per gradient, K = 1500 iterations, mu_j ~ U(-1,1),
  * sigma_j ~ U(0, 0.025), Sigma diagonal. The wide path runs that shape with the parallelism inside a
- * replication: each iteration is four launches (samples and their dot products with v = sigma .* w,
+ * replication: each iteration is four steps (samples and their dot products with v = sigma .* w,
  * the cross-workgroup sums, the gradient of Eq. (4)-(5) with the per-workgroup vertex search, and
  * the global vertex with the update), all sums in a fixed order. The noise is the stream of sim_run:
  * standard normal i d + j of (replication, epoch) for sample i and asset j.

@@ -130,7 +130,7 @@ __device__ __forceinline__ void code_start()
 }
 
 // The per-replication records a run accumulates: signature S_j and decision counts. With a 32-bit
-// signature they live in LDS, [category][thread], each thread its own column (category 0 the origin,
+// signature and 7 assets or more they live in LDS, [category][thread], each thread its own column (category 0 the origin,
 // whose signature row only absorbs the additions of steps that choose it): a step is then two LDS
 // additions at a dynamic index, where registers need a compare, a select and an add per asset for
 // each of S and the counts -- 50 of the 250 VALU instructions an iteration spends outside its

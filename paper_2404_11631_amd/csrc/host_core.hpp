@@ -28,7 +28,7 @@ void fill_desc(InstanceDesc &D, const sim_params *p, uint64_t R, uint64_t T, uin
 // Per-epoch table of a sample-size schedule (sim_params.n_schedule): N_k, 1/N_k and the
 // coefficients c1 = sigma/N_k, c2 = 2 lambda sigma/(N_k - 1) of every epoch k, in both
 // precisions, rounded exactly as fill_desc rounds the plain run's (so a constant schedule
-// reproduces it bit for bit). Byte offsets of each array in one buffer.
+// has its coefficients bit for bit). Byte offsets of each array in one buffer.
 struct SchedLayout {
     uint64_t epochs = 0, bytes = 0;
     uint64_t off_n = 0, off_inv_f = 0, off_inv_d = 0, off_c_f = 0, off_c_d = 0;   // c: [E][2 d] (c1 | c2)
